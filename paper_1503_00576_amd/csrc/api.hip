@@ -21,7 +21,6 @@ __global__ void k_part_count(const P *, const uint32_t *, uint32_t, int, uint32_
                              uint32_t *, const int32_t *);
 __global__ void k_degree_atomic(const int2 *, uint64_t, uint32_t, uint32_t, uint32_t *,
                                 int32_t *);
-__global__ void k_vkeys(const uint32_t *, uint32_t, int, uint64_t *);
 __global__ void k_orient(const int2 *, uint64_t, uint32_t, const uint32_t *, int, uint64_t *,
                          uint32_t *, const int32_t *);
 __global__ void k_orient_cells(const int2 *, uint64_t, uint32_t, const uint32_t *, int,
@@ -416,10 +415,8 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     }
     // the order of Section 2.2 as ranks: stable sort of (degree << b | id) on the degree bits
     if (n > 0) {
-        hipLaunchKernelGGL(k_vkeys, dim3(grid_for(n, 256)), dim3(256), 0, s, deg, n, b, ka);
-        TC_LAUNCH_CHECK();
-        // the last pass writes perm and rank
-        TC_HIP(sort_ranks(ka, kb, n, b, 2 * b, b, perm, rank, sort_scr, nullptr, s));
+        // the first pass reads the degrees, the last one writes perm and rank
+        TC_HIP(sort_ranks(deg, ka, kb, n, b, perm, rank, sort_scr, nullptr, s));
     }
     uint64_t *sorted = ka;
     if (m > 0) {

@@ -39,15 +39,22 @@ __device__ __forceinline__ uint32_t wave_bcast_from(uint32_t x, uint32_t src) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)x);
 }
 
-// inclusive prefix sum over the 64 lanes (inactive lanes must hold 0 and be active)
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
-    const uint32_t l = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t y = (uint32_t)__shfl_up((int)x, d, kWave);
-        if (l >= (uint32_t)d) x += y;
-    }
-    return x;
+// inclusive prefix sum over the 64 lanes (all lanes active): row shifts by 1, 2, 4, 8 inside each
+// 16-lane row (lanes shifted in from outside read 0), then the last lane of rows 0 and 2 into
+// rows 1 and 3, and lane 31 into rows 2 and 3; six vector adds, where shuffles through the LDS
+// crossbar cost six round trips of it
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ uint32_t dpp_add_step(uint32_t v) {
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRowMask, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    v = dpp_add_step<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_add_step<0x112, 0xf>(v);  // row_shr:2
+    v = dpp_add_step<0x114, 0xf>(v);  // row_shr:4
+    v = dpp_add_step<0x118, 0xf>(v);  // row_shr:8
+    v = dpp_add_step<0x142, 0xa>(v);  // row_bcast:15
+    v = dpp_add_step<0x143, 0xc>(v);  // row_bcast:31
+    return v;
 }
 
 // inclusive prefix maximum over the 64 lanes (all lanes active): row shifts by 1, 2, 4, 8
@@ -112,10 +119,11 @@ hipError_t sort_u64(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, i
 hipError_t sort_unzip(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, int hi_bit,
                       int b, uint32_t *col, uint32_t *src, void *scratch, int32_t *status,
                       hipStream_t s, bool onesweep = false);
-// the vertex order: keys (degree << b) | id sorted (stably) on bits lo_bit .. hi_bit, the last
-// pass writing perm[r] = id of position r and rank[id] = r (keys and tmp are clobbered)
-hipError_t sort_ranks(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, int hi_bit,
-                      int b, uint32_t *perm, uint32_t *rank, void *scratch, int32_t *status,
+// the vertex order: the ids 0 .. n - 1 sorted (stably) by degree (below 2^b; larger ones, which
+// only invalid input has, are cut off), the last pass writing perm[r] = id of position r and
+// rank[id] = r; keys and tmp: n keys of room each; same scratch as sort_u64
+hipError_t sort_ranks(const uint32_t *deg, uint64_t *keys, uint64_t *tmp, uint32_t n, int b,
+                      uint32_t *perm, uint32_t *rank, void *scratch, int32_t *status,
                       hipStream_t s);
 // The in-edge lists: the keys (cid[i] << 32) | i with cid[i] != drop sorted (stably) on their
 // bits 32 .. 32 + bits, written split: *list (list ids, in a or b, whichever the last pass

@@ -3,9 +3,10 @@
 //   k_part_*     degrees of the vertices (bucket partition + LDS counting) and the input
 //                checks of Section 3.1; in the one-direction format the same pass places
 //                the edges in cells of id ranges for k_orient_cells
-//   k_vkeys      packs (degree, id) so that a stable sort yields the total order of Section 2.2
-//                (degree first, ties by id); the position of a vertex in that order is its rank
-//                (the sort's last pass writes perm[r] = vertex of rank r, rank[v] = r)
+//   (sort.hip)   a stable sort of (degree, id) yields the total order of Section 2.2 (degree
+//                first, ties by id); the position of a vertex in that order is its rank (the
+//                sort's first pass reads the degrees, its last pass writes perm[r] = vertex of
+//                rank r, rank[v] = r)
 //   k_orient*    every edge becomes a packed key (rank s << b) | rank t with s < t, i.e. the
 //                edge kept only in its forward direction (Section 3.2, steps 5-6); in the
 //                paper's two-direction format backward entries are dropped
@@ -281,18 +282,6 @@ __global__ void k_degree_atomic(const int2 *__restrict__ edges, uint64_t m, uint
         atomicAdd(&deg[e.x], 1u);
         if (!both) atomicAdd(&deg[e.y], 1u);
     }
-}
-
-// vkeys[x] = (degree << b) | x, whose stable sort on the degree bits yields the total order
-// of Section 2.2 (degree first, ties by id)
-__global__ void k_vkeys(const uint32_t *__restrict__ deg, uint32_t n, int b,
-                        uint64_t *__restrict__ vkeys) {
-    uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= n) return;
-    const uint64_t lim = (1ull << b) - 1;
-    uint64_t d = deg[x];
-    if (d > lim) d = lim;  // only possible for invalid input, which is reported elsewhere
-    vkeys[x] = (d << b) | x;
 }
 
 __global__ void k_orient(const int2 *__restrict__ edges, uint64_t m, uint32_t both,

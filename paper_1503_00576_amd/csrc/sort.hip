@@ -37,90 +37,115 @@ hipError_t fill_u32(uint32_t *p, uint32_t value, uint64_t count, hipStream_t s) 
 
 // ======================================================================= scan
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kScanThreads * kScanItems;  // 4096
+// A tile is 16384 elements for 1024 threads: four rows of 4096, four consecutive elements per
+// thread and row (16-byte loads and stores, no transposition through LDS).  Up to one tile, one
+// launch; beyond, two: the tile totals, then the scan, each workgroup adding up the totals
+// before its own tile itself (at most 2^15 of them for 2^29 elements) instead of reading a
+// scanned table.  The scans of the preprocessing are bound by their launches, not by memory:
+// with 4096-element tiles and three to five launches each they took 260 of the 2150 us of a
+// count at R-MAT scale 20 and 125 of 385 us at 100,003 edges.
+constexpr int kScanThreads = 1024;
+constexpr int kScanRows = 4;
+constexpr int kScanWaves = kScanThreads / kWave;                // 16
+constexpr uint32_t kScanRow = kScanThreads * 4;                 // 4096
+constexpr uint32_t kScanTile = kScanRow * kScanRows;            // 16384
+static_assert(kScanRows * kScanWaves == kWave, "one wave scans the row-wave totals");
 
-__device__ __forceinline__ uint32_t pad_idx(uint32_t i) { return i + (i >> 5); }
+__device__ __forceinline__ uint4 scan_load4(const uint32_t *__restrict__ in, uint64_t i,
+                                            uint64_t N) {
+    if (i + 4 <= N) return *reinterpret_cast<const uint4 *>(in + i);
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    if (i < N) x.x = in[i];
+    if (i + 1 < N) x.y = in[i + 1];
+    if (i + 2 < N) x.z = in[i + 2];
+    return x;
+}
 
-// Block-level exclusive scan of one 4096-element tile.
-//   mode 0: write only the tile total to sums[blockIdx.x]
-//   mode 1: write the exclusive scan, offset by carry[blockIdx.x] (if carry != nullptr)
-__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const uint32_t *__restrict__ in,
-                                                            uint32_t *__restrict__ out,
-                                                            uint64_t N, int mode,
-                                                            uint32_t *__restrict__ sums,
-                                                            const uint32_t *__restrict__ carry) {
-    __shared__ uint32_t s[kScanTile + kScanTile / 32];
-    __shared__ uint32_t s_wave[kScanThreads / kWave];
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) {  // sum over the lanes, in all lanes
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(x), kWave - 1);
+}
+
+// sums[b] = total of tile b
+__global__ __launch_bounds__(kScanThreads) void k_scan_sums(const uint32_t *__restrict__ in,
+                                                            uint64_t N,
+                                                            uint32_t *__restrict__ sums) {
+    __shared__ uint32_t s_wave[kScanWaves];
     const uint32_t t = threadIdx.x;
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
-#pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        uint32_t i = j * kScanThreads + t;
-        s[pad_idx(i)] = (base + i < N) ? in[base + i] : 0u;
-    }
-    __syncthreads();
-    uint32_t v[kScanItems];
     uint32_t run = 0;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        v[j] = run;
-        run += s[pad_idx(t * kScanItems + j)];
+    for (int r = 0; r < kScanRows; ++r) {
+        const uint4 x = scan_load4(in, base + r * kScanRow + t * 4, N);
+        run += x.x + x.y + x.z + x.w;
     }
-    uint32_t incl = wave_incl_scan(run);
-    const uint32_t w = t / kWave;
-    if (lane_id() == kWave - 1) s_wave[w] = incl;
+    run = wave_total(run);
+    if (lane_id() == 0) s_wave[t / kWave] = run;
     __syncthreads();
-    uint32_t wave_off = 0, total = 0;
-#pragma unroll
-    for (int k = 0; k < kScanThreads / kWave; ++k) {
-        if ((uint32_t)k < w) wave_off += s_wave[k];
-        total += s_wave[k];
-    }
-    if (mode == 0) {
+    if (t < kWave) {
+        const uint32_t total = wave_total(t < kScanWaves ? s_wave[t] : 0u);
         if (t == 0) sums[blockIdx.x] = total;
-        return;
     }
-    uint32_t off = (incl - run) + wave_off + (carry ? carry[blockIdx.x] : 0u);
-    // all reads of s above happened before the barrier below
-    __syncthreads();
+}
+
+// the exclusive scan of tile b, after the totals of the tiles before it (in may be out: a
+// workgroup reads its whole tile before it writes)
+__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const uint32_t *in, uint32_t *out,
+                                                            uint64_t N,
+                                                            const uint32_t *__restrict__ sums) {
+    __shared__ uint32_t s_part[kScanRows * kScanWaves], s_carry[kScanWaves];
+    const uint32_t t = threadIdx.x, w = t / kWave, lane = lane_id();
+    const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
+    uint4 x[kScanRows];
+    uint32_t incl[kScanRows];
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) s[pad_idx(t * kScanItems + j)] = v[j] + off;
-    __syncthreads();
+    for (int r = 0; r < kScanRows; ++r) x[r] = scan_load4(in, base + r * kScanRow + t * 4, N);
+    uint32_t before = 0;
+    for (uint32_t k = t; k < blockIdx.x; k += kScanThreads) before += sums[k];
+    before = wave_total(before);
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        uint32_t i = j * kScanThreads + t;
-        if (base + i < N) out[base + i] = s[pad_idx(i)];
+    for (int r = 0; r < kScanRows; ++r) {
+        incl[r] = wave_incl_scan(x[r].x + x[r].y + x[r].z + x[r].w);
+        if (lane == kWave - 1) s_part[r * kScanWaves + w] = incl[r];
+    }
+    if (lane == 0) s_carry[w] = before;
+    __syncthreads();
+    // every wave scans the 64 (row, wave) totals in element order and adds up the carries
+    const uint32_t part = s_part[lane];
+    const uint32_t excl = wave_incl_scan(part) - part;
+    const uint32_t carry = wave_total(lane < kScanWaves ? s_carry[lane] : 0u);
+#pragma unroll
+    for (int r = 0; r < kScanRows; ++r) {
+        const uint64_t i = base + r * kScanRow + t * 4;
+        const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)excl, r * kScanWaves + w);
+        uint4 y;
+        y.x = carry + off + incl[r] - (x[r].x + x[r].y + x[r].z + x[r].w);
+        y.y = y.x + x[r].x;
+        y.z = y.y + x[r].y;
+        y.w = y.z + x[r].z;
+        if (i + 4 <= N) {
+            *reinterpret_cast<uint4 *>(out + i) = y;
+        } else {
+            if (i < N) out[i] = y.x;
+            if (i + 1 < N) out[i + 1] = y.y;
+            if (i + 2 < N) out[i + 2] = y.z;
+        }
     }
 }
 
 size_t scan_scratch_words(uint64_t N) {
-    uint64_t nb = (N + kScanTile - 1) / kScanTile;
-    uint64_t words = nb + 1;
-    if (nb > 1) words += scan_scratch_words(nb);
-    return (size_t)align_up(words, 64);
+    return (size_t)align_up((N + kScanTile - 1) / kScanTile + 1, 64);
 }
 
 hipError_t scan_exclusive_u32(const uint32_t *in, uint32_t *out, uint64_t N, uint32_t *scratch,
                               hipStream_t s) {
     if (N == 0) return hipSuccess;
-    uint32_t nb = ceil_div(N, kScanTile);
-    if (nb == 1) {
-        hipLaunchKernelGGL(k_scan_tile, dim3(1), dim3(kScanThreads), 0, s, in, out, N, 1,
-                           (uint32_t *)nullptr, (const uint32_t *)nullptr);
-        return hipGetLastError();
+    const uint32_t nb = ceil_div(N, kScanTile);
+    if (nb > 1) {
+        hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(kScanThreads), 0, s, in, N, scratch);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    uint32_t *sums = scratch;
-    uint32_t *rest = scratch + align_up((size_t)nb + 1, 64);
-    hipLaunchKernelGGL(k_scan_tile, dim3(nb), dim3(kScanThreads), 0, s, in, out, N, 0, sums,
-                       (const uint32_t *)nullptr);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = scan_exclusive_u32(sums, sums, nb, rest, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_tile, dim3(nb), dim3(kScanThreads), 0, s, in, out, N, 1,
-                       (uint32_t *)nullptr, (const uint32_t *)sums);
+    hipLaunchKernelGGL(k_scan_tile, dim3(nb), dim3(kScanThreads), 0, s, in, out, N, scratch);
     return hipGetLastError();
 }
 
@@ -176,6 +201,17 @@ struct KeysHiIndex {  // drops the keys whose value is `drop`
     __device__ __forceinline__ bool keep(uint64_t key) const {
         return (uint32_t)(key >> 32) != drop;
     }
+};
+
+// the vertex order's first pass: vertex i's key (degree << b) | i, formed from the degrees
+struct KeysDegree {
+    const uint32_t *deg;
+    int b;
+    __device__ __forceinline__ uint64_t operator()(uint64_t i) const {
+        const uint64_t lim = (1ull << b) - 1, d = deg[i];
+        return ((d < lim ? d : lim) << b) | i;  // (above lim only for invalid input)
+    }
+    __device__ __forceinline__ bool keep(uint64_t) const { return true; }
 };
 
 // Where a pass writes its keys: 64-bit keys, or split for the last pass of the in-edge list
@@ -259,6 +295,7 @@ struct SortTileLds {
     uint32_t glob[256];              // global start minus local start of each digit
     uint32_t dsum[4];                // per-wave sums of the digit scan (digits by 4 waves)
     uint32_t gsum[4];                // the same for the global digit counts (single sweep)
+    uint32_t gwave[kSortWaves];      // per-wave sums of the global counts (few tiles)
     uint32_t total;                  // keys of the tile that take part
 };
 
@@ -378,14 +415,61 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const Src in, uint3
         hist_tile<false>(in, count, shift, mask, hist, tiles, tile, h);
 }
 
+// How a scatter finds where its tile's digit runs start.  Few tiles (at most kRawTiles): from the
+// per-tile counts themselves, the digits' rows of the table added up by the waves, which saves
+// the scan's launches (a sort of 100,003 keys is bound by its launches, 4 to 10 us each: a whole
+// count of such a graph went from 384 to 309 us with this and the two-launch scan); a single
+// tile needs no table at all.  More tiles: from the scanned table (every workgroup would read
+// the whole table otherwise, 128 KB at 128 tiles).
+constexpr uint32_t kRawTiles = 128;
+
+// Global minus local start of every digit into L.glob (all threads; loc filled).
+__device__ __forceinline__ void tile_digit_starts(SortTileLds &L, const uint32_t *__restrict__ table,
+                                                  uint32_t tiles, uint32_t tile) {
+    const uint32_t t = threadIdx.x;
+    if (tiles == 1) {
+        if (t < 256) L.glob[t] = 0;
+    } else if (tiles <= kRawTiles) {
+        // a wave sums 32 digits' rows, lanes along the tiles; lane i keeps its digit i's sums
+        constexpr uint32_t kDigits = 256 / kSortWaves;
+        const uint32_t w = t / kWave, lane = lane_id();
+        uint32_t sum = 0, below = 0;
+        for (uint32_t k0 = 0; k0 < tiles; k0 += kWave) {
+            const uint32_t k = k0 + lane;
+#pragma unroll 8
+            for (uint32_t i = 0; i < kDigits; ++i) {
+                const uint32_t x = k < tiles ? table[(w * kDigits + i) * tiles + k] : 0u;
+                const uint32_t all = wave_total(x), part = wave_total(k < tile ? x : 0u);
+                if (lane == i) {
+                    sum += all;
+                    below += part;
+                }
+            }
+        }
+        const uint32_t incl = wave_incl_scan(sum);  // (lanes from kDigits on hold 0)
+        if (lane == kWave - 1) L.gwave[w] = incl;
+        __syncthreads();
+        uint32_t before = 0;
+        for (uint32_t k = 0; k < w; ++k) before += L.gwave[k];
+        if (lane < kDigits) {
+            const uint32_t d = w * kDigits + lane;
+            L.glob[d] = before + incl - sum + below - L.loc[d];
+        }
+    } else if (t < 256) {
+        L.glob[t] = table[(uint64_t)t * tiles + tile] - L.loc[t];
+    }
+}
+
 // Stable scatter of one tile: the keys are ranked and placed in LDS in digit order (a
 // tile-local counting sort), then written out digit run by digit run.
-//   offs: exclusive scan of the digit-major table of per-tile digit counts
+//   table: digit-major per-tile digit counts, scanned when there are more than kRawTiles tiles
+//   total: nullable, receives the number of keys of all tiles
 template <bool kFull, class Src, class Dst>
 __device__ __forceinline__ void scatter_tile(const Src in, const Dst out, uint32_t count,
                                              int shift, uint32_t mask,
-                                             const uint32_t *__restrict__ offs, uint32_t tiles,
-                                             uint32_t tile, SortTileLds &L) {
+                                             const uint32_t *__restrict__ table, uint32_t tiles,
+                                             uint32_t tile, uint32_t *__restrict__ total,
+                                             SortTileLds &L) {
     const uint32_t t = threadIdx.x, w = t / kWave;
     const uint64_t base = (uint64_t)tile * kSortTile;
     uint64_t keys[kSortItems];
@@ -394,9 +478,12 @@ __device__ __forceinline__ void scatter_tile(const Src in, const Dst out, uint32
     wave_lds_sync();
     uint32_t ranks[kSortItems];
     wave_rank_rows(keys, vmask, shift, mask, L.wcnt[w], ranks);
-    tile_digit_offsets(L);
-    if (t < 256) L.glob[t] = offs[(uint64_t)t * tiles + tile] - L.loc[t];
+    const uint32_t c = tile_digit_offsets(L);
     __syncthreads();
+    tile_digit_starts(L, table, tiles, tile);
+    __syncthreads();
+    // the last tile's last run ends at the number of keys
+    if (total && tile == tiles - 1 && t == 255) *total = L.glob[255] + L.loc[255] + c;
     stage_keys(L, keys, ranks, vmask, w, shift, mask);
     __syncthreads();
     write_staged(L, out, count, shift, mask, nullptr);
@@ -405,8 +492,8 @@ __device__ __forceinline__ void scatter_tile(const Src in, const Dst out, uint32
 template <class Src, class Dst>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const Src in, const Dst out, uint32_t count, const uint32_t *__restrict__ dcount, int shift,
-    uint32_t nbits, const uint32_t *__restrict__ offs, uint32_t tiles,
-    const int32_t *__restrict__ status) {
+    uint32_t nbits, const uint32_t *__restrict__ table, uint32_t tiles,
+    uint32_t *__restrict__ total, const int32_t *__restrict__ status) {
     if (status && *status) return;
     if (dcount) count = min(count, *dcount);
     __shared__ SortTileLds L;
@@ -414,9 +501,9 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     if ((uint64_t)tile * kSortTile >= count) return;  // past the keys (a device count)
     const uint32_t mask = (1u << nbits) - 1u;
     if ((uint64_t)(tile + 1) * kSortTile <= count)
-        scatter_tile<true>(in, out, count, shift, mask, offs, tiles, tile, L);
+        scatter_tile<true>(in, out, count, shift, mask, table, tiles, tile, total, L);
     else
-        scatter_tile<false>(in, out, count, shift, mask, offs, tiles, tile, L);
+        scatter_tile<false>(in, out, count, shift, mask, table, tiles, tile, total, L);
 }
 
 // ---------------------------------------------------------------- single-sweep variant
@@ -558,12 +645,6 @@ size_t sort_scratch_bytes(uint64_t count) {
     return 2 * align_up(hist * 4, 256) + align_up(scan_scratch_words(hist) * 4, 256);
 }
 
-// the number of keys a pass wrote: the end of the last digit run of the last tile
-__global__ void k_sort_total(const uint32_t *__restrict__ hist, const uint32_t *__restrict__ offs,
-                             uint64_t last, uint32_t *__restrict__ total) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *total = offs[last] + hist[last];
-}
-
 // One stable two-kernel pass on the digit at `shift` (at most 8 bits, below hi_bit) from the
 // keys `in` yields to dst.  dcount (nullable): the number of keys on the device (count: the
 // capacity); total (nullable): receives the number of keys written (the kept ones).
@@ -577,18 +658,19 @@ static hipError_t radix_pass(const Src in, const Dst dst, uint32_t count, int sh
     uint32_t *offs = (uint32_t *)((char *)scratch + align_up(hist_n * 4, 256));
     uint32_t *scan_scratch = (uint32_t *)((char *)scratch + 2 * align_up(hist_n * 4, 256));
     const uint32_t nbits = (uint32_t)((hi_bit - shift) < 8 ? (hi_bit - shift) : 8);
-    hipLaunchKernelGGL(k_radix_hist<Src>, dim3(tiles), dim3(kSortThreads), 0, s, in, count,
-                       dcount, shift, nbits, hist, tiles, status);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = scan_exclusive_u32(hist, offs, hist_n, scan_scratch, s);
-    if (e != hipSuccess) return e;
-    if (total) {
-        hipLaunchKernelGGL(k_sort_total, dim3(1), dim3(64), 0, s, hist, offs, hist_n - 1, total);
+    hipError_t e;
+    if (tiles > 1) {
+        hipLaunchKernelGGL(k_radix_hist<Src>, dim3(tiles), dim3(kSortThreads), 0, s, in, count,
+                           dcount, shift, nbits, hist, tiles, status);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    if (tiles > kRawTiles) {
+        e = scan_exclusive_u32(hist, offs, hist_n, scan_scratch, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((k_radix_scatter<Src, Dst>), dim3(tiles), dim3(kSortThreads), 0, s, in,
-                       dst, count, dcount, shift, nbits, offs, tiles, status);
+                       dst, count, dcount, shift, nbits, tiles > kRawTiles ? offs : hist, tiles,
+                       total, status);
     return hipGetLastError();
 }
 
@@ -652,17 +734,24 @@ hipError_t sort_unzip(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit,
                       scratch, status, s);
 }
 
-hipError_t sort_ranks(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, int hi_bit,
-                      int b, uint32_t *perm, uint32_t *rank, void *scratch, int32_t *status,
+hipError_t sort_ranks(const uint32_t *deg, uint64_t *keys, uint64_t *tmp, uint32_t n, int b,
+                      uint32_t *perm, uint32_t *rank, void *scratch, int32_t *status,
                       hipStream_t s) {
-    if (count == 0) return hipSuccess;
-    const int passes = hi_bit > lo_bit ? (hi_bit - lo_bit + 7) / 8 : 1;
-    const int last = hi_bit > lo_bit ? lo_bit + 8 * (passes - 1) : hi_bit;
-    uint64_t *mid = keys;
-    hipError_t e = sort_u64(keys, tmp, count, lo_bit, last, scratch, status, s, &mid);
+    if (n == 0) return hipSuccess;
+    const KeysDegree first{deg, b};
+    const OutPermRank last{perm, rank, (1ull << b) - 1};
+    if (b <= 8) return radix_pass(first, last, n, b, 2 * b, scratch, status, s);
+    hipError_t e = radix_pass(first, Out64{keys}, n, b, 2 * b, scratch, status, s);
+    uint64_t *src = keys, *dst = tmp;
+    int shift = b + 8;
+    for (; e == hipSuccess && shift + 8 < 2 * b; shift += 8) {
+        e = radix_pass(Keys64{src}, Out64{dst}, n, shift, 2 * b, scratch, status, s);
+        uint64_t *x = src;
+        src = dst;
+        dst = x;
+    }
     if (e != hipSuccess) return e;
-    return radix_pass(Keys64{mid}, OutPermRank{perm, rank, (1ull << b) - 1}, count, last, hi_bit,
-                      scratch, status, s);
+    return radix_pass(Keys64{src}, last, n, shift, 2 * b, scratch, status, s);
 }
 
 hipError_t sort_lists(const uint32_t *cid, uint32_t drop, uint32_t count, int bits,

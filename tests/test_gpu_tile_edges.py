@@ -1,0 +1,52 @@
+"""The scans and radix passes at the edges of their tiles and of the rules that choose their
+launches (GPU, exact): the sort against torch's stable sort, whole counts against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1503_00576_amd import api
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TILE, RAW = 8192, 128  # keys per tile; up to RAW tiles a pass reads the unscanned table
+
+
+@pytest.mark.parametrize("count", [1, 2, TILE - 1, TILE, TILE + 1, 64 * TILE, 64 * TILE + 1,
+                                   65 * TILE, RAW * TILE, RAW * TILE + 1, 3 * RAW * TILE - 5])
+@pytest.mark.parametrize("bits", [8, 21])
+def test_sort_at_tile_edges(count, bits):
+    gen = torch.Generator().manual_seed(count + bits)
+    keys = torch.randint(0, 1 << 40, (count,), generator=gen, dtype=torch.int64)
+    keys[: count // 3] &= ~0xFF  # a crowded digit
+    want = keys[torch.argsort(keys & ((1 << bits) - 1), stable=True)]
+    got = api.sort_u64(keys.to(DEV), bits).cpu()
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n", [2, 255, 256, 257, 16383, 16384, 16385, 3 * 16384 + 1])
+def test_counts_at_scan_edges(n):
+    """n + 1 row offsets on both sides of one scan tile (16384), one and two vertex passes."""
+    m = min(5 * n, n * (n - 1) // 2)
+    rng = np.random.default_rng(n)
+    a = rng.integers(0, n, 4 * m)
+    b = (a + 1 + (rng.integers(0, max(n - 1, 1), 4 * m) ** 2 // max(n - 1, 1)) % max(n - 1, 1)) % n
+    key = np.unique(np.minimum(a, b) * n + np.maximum(a, b))
+    key = key[key // n != key % n]
+    e = torch.tensor(np.stack([key // n, key % n], 1).astype(np.int32))
+    want, pv = oracle.count(e, n, per_vertex=True)
+    total, got = api.count_per_vertex(e.to(DEV), n)
+    assert total == want == api.count(e.to(DEV), n)
+    assert np.array_equal(got.cpu().numpy().astype(np.uint64), pv)
+    both = torch.cat([e, e.flip(1)])[torch.randperm(2 * len(key),
+                                                    generator=torch.Generator().manual_seed(n))]
+    assert api.count(both.to(DEV), n, both=True) == want
+
+
+def test_vertex_order_of_saturated_degrees():
+    """A star and a clique: degrees up to n - 1, ranks by (degree, id)."""
+    n = 300
+    e = [(0, x) for x in range(1, n)] + [(i, j) for i in range(200, 260) for j in range(i + 1, 260)]
+    out = api.preprocess(torch.tensor(e, dtype=torch.int32, device=DEV), n)
+    deg = np.bincount(np.array(e).ravel(), minlength=n)
+    assert np.array_equal(out["perm"].cpu().numpy(), np.lexsort((np.arange(n), deg)))
