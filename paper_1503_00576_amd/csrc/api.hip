@@ -25,6 +25,7 @@ __global__ void k_orient(const int2 *, uint64_t, uint32_t, const uint32_t *, int
                          uint32_t *, const int32_t *);
 __global__ void k_orient_cells(const int2 *, uint64_t, uint32_t, const uint32_t *, int,
                                uint64_t *, const int32_t *);
+uint32_t orient_tile();  // entries per workgroup of k_orient
 __global__ void k_both_check(const uint32_t *, uint32_t, int32_t *);
 __global__ void k_csr(const uint64_t *, uint32_t, uint32_t, int, uint32_t, uint32_t *,
                       uint32_t *, uint32_t *, uint32_t *, uint32_t *, int32_t *);
@@ -424,7 +425,7 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
             hipLaunchKernelGGL(k_orient_cells, dim3(kOrientGrid), dim3(256), 0, s, cells,
                                (uint64_t)m, n, rank, b, ka, status);
         } else {
-            hipLaunchKernelGGL(k_orient, dim3(grid_for(m, 256, 8192)), dim3(256), 0, s, edges,
+            hipLaunchKernelGGL(k_orient, dim3(grid_for(m, orient_tile())), dim3(256), 0, s, edges,
                                (uint64_t)m, (uint32_t)both, rank, b, ka, ctl + kCtlBoth, status);
         }
         TC_LAUNCH_CHECK();

@@ -50,3 +50,17 @@ def test_vertex_order_of_saturated_degrees():
     out = api.preprocess(torch.tensor(e, dtype=torch.int32, device=DEV), n)
     deg = np.bincount(np.array(e).ravel(), minlength=n)
     assert np.array_equal(out["perm"].cpu().numpy(), np.lexsort((np.arange(n), deg)))
+
+
+@pytest.mark.parametrize("m", [1, 2047, 2048, 2049, 3 * 2048])
+def test_two_direction_compaction_at_tile_edges(m):
+    """2 m entries on both sides of the orientation's tile (4096), forward entries first and
+    last; with and without the degree partition."""
+    n = m + 2
+    e = torch.tensor([(x, x + 1 + (x & 1)) for x in range(m)], dtype=torch.int32)
+    want = oracle.count(e, n)
+    for entries in (torch.cat([e, e.flip(1)]), torch.stack([e, e.flip(1)], 1).reshape(-1, 2)):
+        for part in (0, 1):
+            assert api.count(entries.to(DEV), n, both=True,
+                             options={"degree_partition": part}) == want
+    assert api.count(e.to(DEV), n, options={"degree_partition": 0}) == want
