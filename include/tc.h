@@ -328,14 +328,14 @@ int tc_split_subgraph_edges(const void *h_ws, uint32_t index, int32_t *h_out,
  * order of Section 2.2, so the oriented rows stay sorted without any sort; the counting kernel
  * computes Section 2.2's intersections grouped by u: for a vertex u with more than 256 forward
  * neighbours it stages N+(u) in LDS and streams the lists N+(v) of u's out-neighbours; the
- * other edges are taken in chunks of consecutive forward edges, one edge u -> v per lane,
- * with the chunk's short lists N+(u) staged in LDS and N+(v) streamed through them.
+ * other vertices' forward edges are taken one edge u -> v per lane, with the short lists N+(u)
+ * staged in LDS and N+(v) streamed through them.
  *
  * A plan binds a workspace of tc_batched_workspace_size(g_cap, n_cap, adj_cap) bytes and
  * captures the whole launch sequence once per mode (with / without per-vertex counts) into a
  * hipGraph on its first run; later runs only write a small argument block and replay the
  * graph, for any batch within the capacities.  tuning_json (nullable) may set "chunk_e"
- * (forward edges per chunk, 64 .. 1536, default 1024), "items_k" (out-neighbours of a large
+ * (forward edges staged at a time, 64 .. 1536, default 1024), "items_k" (out-neighbours of a large
  * vertex per work item, >= 16, default 256), "light_max" (vertices with at most this many
  * forward neighbours take the edge-per-lane path, 0 .. 256, default 256), "bitmap_span" and
  * "list_max" (a large vertex's N+(u) is an LDS bitmap when its id span is below bitmap_span,

@@ -8,14 +8,19 @@
 //
 // Preprocessing needs no sort: the degree of a vertex is its row length, and keeping in every
 // row only the neighbours that come later in the order of Section 2.2 ((degree, id)
-// ascending) is a stable filter, so the oriented rows stay sorted by id.  The counting kernel
-// (k_count_u) then stages N+(u) and streams N+(v) for the out-neighbours v.
+// ascending) is a stable filter, so the oriented rows stay sorted by id.  One pass over the
+// input checks it and writes every row's kept entries at the row's own place (the row's start
+// among all rows): nothing about the kept entries has to be known beforehand, so the input is
+// read once.  The counting kernels (count.hip) then stage N+(u) and stream N+(v) for the
+// out-neighbours v.
 //
 // Every kernel reads the sizes and the caller's pointers from an argument block at the start
 // of the workspace and runs over the plan's capacities, so one captured graph serves every
 // batch that fits the plan.
 #include <stdlib.h>
 #include <string.h>
+
+#include <type_traits>
 
 #include "internal.h"
 
@@ -29,10 +34,12 @@ struct BatchArgs {
     unsigned long long *totals;
     unsigned long long *per_vertex;
     int32_t *status;  // per graph, may be null
-    uint32_t G, N, kitem;
-    uint32_t A;      // adjacency entries in total
-    uint32_t chunk;  // forward edges per light chunk
+    uint32_t G, N;
+    uint32_t A;  // adjacency entries in total
 };
+
+// ctl: [0] heavy-item queue, [1] heavy items
+constexpr uint32_t kCtlWordsB = 2;
 
 __device__ __forceinline__ void graph_error(const BatchArgs &a, uint32_t g, int32_t code,
                                             int32_t *gstat) {
@@ -50,22 +57,20 @@ __device__ __forceinline__ uint32_t graph_of(const int64_t *vtx_off, uint32_t G,
     return lo;
 }
 
-__global__ void k_b_set_args(BatchArgs *dst, BatchArgs a) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = a;
-}
-
-// zero the outputs and the internal status / queues
-__global__ void k_b_clear(const BatchArgs *__restrict__ args, int32_t *__restrict__ gstat,
-                          unsigned long long *__restrict__ ghash,
-                          uint32_t *__restrict__ queue, uint32_t cap) {
-    const BatchArgs a = *args;
+// start of a run: the argument block, zeroed outputs, statuses and counters
+__global__ void k_b_begin(BatchArgs *dst, const BatchArgs a, int32_t *__restrict__ gstat,
+                          unsigned long long *__restrict__ ghash, uint32_t *__restrict__ gfwd,
+                          uint32_t *__restrict__ ctl) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 2) queue[i] = 0;
+    if (i == 0) *dst = a;
+    if (i < kCtlWordsB) ctl[i] = 0;
+    const uint32_t cap = a.per_vertex && a.N > a.G ? a.N : a.G;
     for (uint32_t x = i; x < cap; x += gridDim.x * blockDim.x) {
         if (x < a.G) {
             a.totals[x] = 0;
             gstat[x] = 0;
             ghash[x] = 0;
+            gfwd[x] = 0;
         }
         if (a.per_vertex && x < a.N) a.per_vertex[x] = 0;
     }
@@ -83,383 +88,276 @@ __device__ __forceinline__ uint64_t pair_hash(uint32_t x, uint32_t y) {
     return k;
 }
 
-// Per-vertex work over the input rows is done wave by wave: the wave takes 64 consecutive
-// vertices (lane k: vertex xb + k), whose rows are consecutive in the input, and walks their
-// entries 64 at a time, so that loads and stores are coalesced whatever the row lengths.
-// Entry idx of the walk belongs to the last lane k whose exclusive prefix off[k] <= idx.
-struct RowWalk {
-    uint32_t off[kWave + 1];  // exclusive prefix of the row lengths; off[64] = all entries
-    uint32_t ebeg[kWave];     // position of the row in the input's col
-    uint32_t len[kWave];      // row length (0 for rows that failed their checks)
-    uint32_t local[kWave];    // local vertex id
-    uint32_t rpb[kWave];      // index of the graph's row offsets in row_ptr
-    uint32_t ng[kWave];       // vertices of the graph
-    uint32_t g[kWave];        // graph
-    uint32_t acc[kWave];      // per-row count of forward entries (counted), or the row's next
-                              // output position (written)
-    uint32_t fend[kWave];     // end of the row's forward entries in the output (written)
-};
-
-__device__ __forceinline__ uint32_t walk_owner(const RowWalk &rw, uint32_t idx) {
-    uint32_t k = 0;
-#pragma unroll
-    for (uint32_t step = 32; step; step >>= 1)
-        if (rw.off[k + step] <= idx) k += step;
-    return k;
-}
-
-// lanes a .. b (inclusive) of a wave
-__device__ __forceinline__ uint64_t lane_range(uint32_t a, uint32_t b) {
-    return ((2ull << b) - 1ull) & ~((1ull << a) - 1ull);
-}
-
-// Loads the wave's 64 rows into `rw` (lane = vertex x) from already validated per-vertex
-// values; returns the number of entries.
-__device__ __forceinline__ uint32_t walk_begin(RowWalk &rw, uint32_t d, uint32_t ebeg,
-                                               uint32_t local, uint32_t rpb, uint32_t ng,
-                                               uint32_t g) {
-    const uint32_t lane = lane_id();
-    const uint32_t incl = wave_incl_scan(d);
-    const uint32_t total = wave_bcast(incl, kWave - 1);
-    rw.off[lane] = incl - d;
-    if (lane == 0) rw.off[kWave] = total;
-    rw.ebeg[lane] = ebeg;
-    rw.len[lane] = d;
-    rw.local[lane] = local;
-    rw.rpb[lane] = rpb;
-    rw.ng[lane] = ng;
-    rw.g[lane] = g;
-    rw.acc[lane] = 0;
-    wave_lds_sync();
-    return total;
-}
-
-// One step of the walk: the entry of this lane (if any) with its owner k, its index j in the
-// row, its value y (local id), whether it is a forward entry of an in-range id (the same
-// test in both kernels: the degree of y is its row length in the input), the previous entry
-// of the row (-1 at the row start), and the lanes of the owner's row in this step
-// [first, last].
-struct WalkEntry {
-    bool valid, ok, fwd;
-    uint32_t k, j, first, last;
-    int32_t y, prev;
-};
-
-// kWalkSteps consecutive steps of the walk at once: every load of all of them (entries,
-// previous entries, the row offsets behind the degree test) is issued before any is used,
-// so a wave waits once per kWalkSteps steps instead of once per step.  Addresses of lanes
-// past the end or with an out-of-range id are clamped onto valid ones and their values
-// ignored.
-constexpr int kWalkSteps = 4;
-constexpr int kFillSteps = 8;  // the forward fill's walk needs fewer registers per step
-
-// The argument block's pointers are generic; the walk reads through global-address-space
-// views so that its loads are global loads (waited for apart from the LDS traffic).
-typedef const __attribute__((address_space(1))) int32_t *gptr_i32;
-
-__device__ __forceinline__ void walk_entries(const RowWalk &rw, uint32_t base, uint32_t total,
-                                             const int32_t *col_p, const int32_t *row_ptr_p,
-                                             WalkEntry (&en)[kWalkSteps]) {
-    const gptr_i32 col = (gptr_i32)col_p, row_ptr = (gptr_i32)row_ptr_p;
-    const uint32_t lane = lane_id();
-    int32_t r0[kWalkSteps], r1[kWalkSteps];
-#pragma unroll
-    for (int u = 0; u < kWalkSteps; ++u) {
-        const uint32_t idx = base + (uint32_t)u * kWave + lane;
-        en[u].valid = idx < total;
-        const uint32_t k = walk_owner(rw, en[u].valid ? idx : total - 1);
-        en[u].k = k;
-        en[u].j = (en[u].valid ? idx : total - 1) - rw.off[k];
-        const uint32_t at = rw.ebeg[k] + en[u].j;
-        en[u].y = col[at];
-        en[u].prev = col[at - (en[u].j > 0 ? 1u : 0u)];
-    }
-#pragma unroll
-    for (int u = 0; u < kWalkSteps; ++u) {
-        const uint32_t k = en[u].k, lk = rw.local[k];
-        const int32_t y = en[u].y;
-        if (en[u].j == 0) en[u].prev = -1;
-        en[u].ok = en[u].valid && y >= 0 && (uint32_t)y < rw.ng[k] && (uint32_t)y != lk;
-        const uint32_t at = rw.rpb[k] + (en[u].ok ? (uint32_t)y : 0u);
-        r0[u] = row_ptr[at];
-        r1[u] = row_ptr[at + 1];
-    }
-#pragma unroll
-    for (int u = 0; u < kWalkSteps; ++u) {
-        const uint32_t k = en[u].k, lk = rw.local[k];
-        const int64_t dy = (int64_t)r1[u] - r0[u], dx = rw.len[k];
-        en[u].fwd = en[u].ok && (dy > dx || (dy == dx && (uint32_t)en[u].y > lk));
-        const uint32_t sb = base + (uint32_t)u * kWave;
-        const uint32_t rb = rw.off[k], re = rw.off[k] + rw.len[k];
-        en[u].first = (rb > sb ? rb : sb) - sb;
-        en[u].last = (re < sb + kWave ? re : sb + kWave) - 1 - sb;
-    }
-}
-
-// The steps of k_b_ffill's walk: the entries and their forward flags from k_b_setup (no degree
-// lookups); fills valid, fwd, k, first, last and y.
-__device__ __forceinline__ void walk_entries_flagged(const RowWalk &rw, uint32_t base,
-                                                     uint32_t total, const int32_t *col_p,
-                                                     const uint8_t *__restrict__ fflag,
-                                                     WalkEntry (&en)[kFillSteps]) {
-    const gptr_i32 col = (gptr_i32)col_p;
-    const uint32_t lane = lane_id();
-    uint32_t f[kFillSteps];
-#pragma unroll
-    for (int u = 0; u < kFillSteps; ++u) {
-        const uint32_t idx = base + (uint32_t)u * kWave + lane;
-        en[u].valid = idx < total;
-        const uint32_t k = walk_owner(rw, en[u].valid ? idx : total - 1);
-        en[u].k = k;
-        en[u].j = (en[u].valid ? idx : total - 1) - rw.off[k];
-        const uint32_t at = rw.ebeg[k] + en[u].j;
-        en[u].y = col[at];
-        f[u] = fflag[at];
-    }
-#pragma unroll
-    for (int u = 0; u < kFillSteps; ++u) {
-        const uint32_t k = en[u].k;
-        en[u].fwd = en[u].valid && f[u] != 0u;
-        const uint32_t sb = base + (uint32_t)u * kWave;
-        const uint32_t rb = rw.off[k], re = rw.off[k] + rw.len[k];
-        en[u].first = (rb > sb ? rb : sb) - sb;
-        en[u].last = (re < sb + kWave ? re : sb + kWave) - 1 - sb;
-    }
-}
-
-// Per vertex: graph id, degree (row length), forward out-degree (entries ncap.. stay zero for
-// the scan), checks of its row (offsets in range, ids in range, no self-loop, strictly
-// ascending), and its share of the graph's symmetry sum: sum over the row's entries (x, y) of
-// pair_hash(x, y) - pair_hash(y, x), which is zero over a graph whose rows are symmetric.
-// Graph ids are non-decreasing across a wave, so the shares are added per run of equal ids.
-__global__ __launch_bounds__(256) void k_b_setup(const BatchArgs *__restrict__ args,
-                                                 uint32_t ncap, uint32_t *__restrict__ gid,
-                                                 uint32_t *__restrict__ deg,
-                                                 uint32_t *__restrict__ fdeg,
-                                                 uint8_t *__restrict__ fflag,
-                                                 unsigned long long *__restrict__ ghash,
-                                                 int32_t *__restrict__ gstat) {
-    __shared__ RowWalk s_rw[4];
+// per vertex: its graph, and its row length once the offsets it relies on are checked (the whole
+// vertex range of its graph, whose row offsets the forward test reads); 0 for the vertices from
+// N on, so that the scan over ncap + 1 entries gives every row's place
+__global__ __launch_bounds__(256) void k_b_rows(const BatchArgs *__restrict__ args, uint32_t ncap,
+                                                uint32_t *__restrict__ gid,
+                                                uint32_t *__restrict__ deg,
+                                                int32_t *__restrict__ gstat) {
     const BatchArgs a = *args;
-    const uint32_t lane = lane_id(), w = threadIdx.x / kWave;
-    RowWalk &rw = s_rw[w];
-    const uint32_t x = (blockIdx.x * 4 + w) * kWave + lane;
-    uint32_t g = 0xFFFFFFFFu, d = 0, ebeg = 0, local = 0, rpb = 0, ng = 0;
+    const uint32_t x = blockIdx.x * 256u + threadIdx.x;
+    if (x > ncap) return;
+    uint32_t d = 0;
     if (x < a.N) {
-        g = graph_of(a.vtx_off, a.G, x);
+        const uint32_t g = graph_of(a.vtx_off, a.G, x);
         gid[x] = g;
         const int64_t v0 = a.vtx_off[g], n_g = a.vtx_off[g + 1] - v0;
         const int64_t a0 = a.adj_off[g], alen = a.adj_off[g + 1] - a0;
         const int64_t lx = (int64_t)x - v0;
-        // offsets arrays must be prefix sums: check what this vertex relies on (the whole
-        // vertex range of its graph, whose row offsets the forward test reads)
+        // offsets arrays must be prefix sums
         if (v0 < 0 || lx < 0 || lx >= n_g || v0 + n_g > (int64_t)a.N || a0 < 0 || alen < 0 ||
             a0 + alen > (int64_t)a.A) {
             graph_error(a, g, TC_E_ARG, gstat);
         } else {
             const int32_t *rp = a.row_ptr + v0 + g;
             const int64_t r0 = rp[lx], r1 = rp[lx + 1];
-            if (r0 < 0 || r1 < r0 || r1 > alen) {
+            if (r0 < 0 || r1 < r0 || r1 > alen)
                 graph_error(a, g, TC_E_ARG, gstat);
-            } else {
+            else
                 d = (uint32_t)(r1 - r0);
-                ebeg = (uint32_t)(a0 + r0);
-                local = (uint32_t)lx;
-                rpb = (uint32_t)(v0 + g);
-                ng = (uint32_t)n_g;
-            }
         }
     }
-    const uint32_t total = walk_begin(rw, d, ebeg, local, rpb, ng, g);
-    // this lane's symmetry shares, for graph hg (the graphs of a lane's entries never
-    // decrease; a change flushes the sum)
-    uint32_t hg = 0xFFFFFFFFu;
-    uint64_t hsum = 0;
-    for (uint32_t base = 0; base < total; base += kWalkSteps * kWave) {
-        WalkEntry ens[kWalkSteps];
-        walk_entries(rw, base, total, a.col, a.row_ptr, ens);
-#pragma unroll
-        for (int u = 0; u < kWalkSteps; ++u) {
-            const WalkEntry &en = ens[u];
-            if (en.valid) {
-                const uint32_t gk = rw.g[en.k], lk = rw.local[en.k];
-                if (!en.ok) {
-                    graph_error(a, gk,
-                                (en.y < 0 || (uint32_t)en.y >= rw.ng[en.k]) ? TC_E_RANGE
-                                                                            : TC_E_SELF_LOOP,
-                                gstat);
-                } else {
-                    if (en.j > 0 && en.y <= en.prev)
-                        graph_error(a, gk, en.y == en.prev ? TC_E_DUP_EDGE : TC_E_UNSORTED,
-                                    gstat);
-                    if (gk != hg) {
-                        if (hsum) atomicAdd(&ghash[hg], (unsigned long long)hsum);
-                        hg = gk;
-                        hsum = 0;
-                    }
-                    hsum += pair_hash(lk, (uint32_t)en.y) - pair_hash((uint32_t)en.y, lk);
-                }
-            }
-            if (en.valid) fflag[rw.ebeg[en.k] + en.j] = en.fwd ? 1u : 0u;
-            const uint64_t F = __ballot(en.valid && en.fwd);
-            // forward entries per row in this step, added by the row's last lane in the step
-            if (en.valid && lane == en.last)
-                rw.acc[en.k] += (uint32_t)__popcll(F & lane_range(en.first, lane));
-            wave_lds_sync();
-        }
-    }
-    if (x < ncap) deg[x] = d;
-    if (x <= ncap) fdeg[x] = rw.acc[lane];
-    // the lanes' last sums: one atomic when they all belong to one graph (the usual case)
-    const uint32_t hg0 = wave_bcast(hg, 0);
-    if (__ballot(hsum != 0 && hg != hg0) == 0) {
-        const uint64_t hs = wave_sum_u64(hsum);
-        if (lane == 0 && hs) atomicAdd(&ghash[hg0], (unsigned long long)hs);
-    } else if (hsum) {
-        atomicAdd(&ghash[hg], (unsigned long long)hsum);
-    }
+    deg[x] = d;
 }
 
-// the forward rows (union ids, input order kept) with the row of every entry
-__global__ __launch_bounds__(256) void k_b_ffill(const BatchArgs *__restrict__ args,
+// lanes a .. b - 1 of a wave (a <= b <= 64, a < 64)
+__device__ __forceinline__ uint64_t lanes_from_to(uint32_t a, uint32_t b) {
+    return (b >= 64 ? ~0ull : ((1ull << b) - 1ull)) & ~((1ull << a) - 1ull);
+}
+
+// The argument block's pointers are generic; the walk reads through global-address-space
+// views so that its loads are global loads (waited for apart from the LDS traffic).
+typedef const __attribute__((address_space(1))) int32_t *gptr_i32;
+
+// One pass over the rows: checks (ids in range, no self-loop, strictly ascending), the forward
+// rows written in place, and the graph's symmetry sum and forward entries.
+//
+// A wave takes 2^vshift consecutive vertices, graph by graph (nearly always one), and walks
+// their entries, consecutive in the input, 64 at a time: kWalkSteps steps together, whose loads
+// are issued before any is used.  Lane l's entry belongs to row k (round_owner); the row's
+// place in the input, length, first entry and output come from lane k's registers.  Rows
+// run over steps, so the forward entries a row had in earlier steps are carried along (only the
+// row of a step's first lane has any).
+//
+// Symmetry: an entry (x, y) adds the pair hash of {x, y} when it is a forward entry and takes it
+// away otherwise; the two entries of an edge are forward from exactly one side, so the sum over
+// a graph with symmetric rows is zero.
+//
+// It is bound by its vector instructions (65% of the issue slots) and the gathers of the degrees
+// (64 lines a step), so every per-row value that is the same over a graph is kept in scalar
+// registers, the entry before a lane's comes from its neighbour lane, one hash serves both
+// directions and a degree is one 4-byte lookup.  4096 graphs of 3300 vertices (2.4e8 entries):
+// 1.24 ms, where a checking pass and a second pass that wrote the rows took 1.28 + 0.65 ms.
+constexpr int kWalkSteps = 4;
+
+__global__ __launch_bounds__(256) void k_b_setup(const BatchArgs *__restrict__ args, uint32_t acap,
+                                                 uint32_t vshift,
                                                  const uint32_t *__restrict__ gid,
                                                  const uint32_t *__restrict__ deg,
-                                                 const uint32_t *__restrict__ frp,
-                                                 const uint8_t *__restrict__ fflag,
+                                                 const uint32_t *__restrict__ start,
+                                                 uint32_t light_max, uint32_t kitem,
+                                                 uint2 *__restrict__ frow,
                                                  uint32_t *__restrict__ fcol,
-                                                 uint32_t *__restrict__ fsrc) {
-    __shared__ RowWalk s_rw[4];
+                                                 uint2 *__restrict__ items,
+                                                 uint32_t *__restrict__ n_items,
+                                                 unsigned long long *__restrict__ ghash,
+                                                 uint32_t *__restrict__ gfwd,
+                                                 unsigned long long *__restrict__ whash,
+                                                 uint32_t *__restrict__ wfwd,
+                                                 int32_t *__restrict__ gstat) {
+    __shared__ uint32_t s_mark[4][kWave], s_fwd[4][kWave];
     const BatchArgs a = *args;
     const uint32_t lane = lane_id(), w = threadIdx.x / kWave;
-    RowWalk &rw = s_rw[w];
-    const uint32_t x = (blockIdx.x * 4 + w) * kWave + lane;
-    uint32_t g = 0xFFFFFFFFu, d = 0, ebeg = 0, local = 0, rpb = 0, ng = 0;
-    if (x < a.N && deg[x] > 0) {  // rows that passed k_b_setup's checks
+    uint32_t *mark = s_mark[w], *fcount = s_fwd[w];
+    const uint32_t x0 = (xcd_stretch_tile(blockIdx.x, gridDim.x) * 4 + w) << vshift;
+    if (x0 >= a.N) return;
+    const uint32_t x = x0 + lane;
+    const bool in = (lane >> vshift) == 0 && x < a.N;
+    uint32_t g = ~0u, d = 0, s = 0;
+    if (in) {
         g = gid[x];
-        const int64_t v0 = a.vtx_off[g];
-        const int32_t *rp = a.row_ptr + v0 + g;
-        local = (uint32_t)((int64_t)x - v0);
         d = deg[x];
-        ebeg = (uint32_t)(a.adj_off[g] + rp[local]);
-        rpb = (uint32_t)(v0 + g);
-        ng = (uint32_t)(a.vtx_off[g + 1] - v0);
-    }
-    const uint32_t total = walk_begin(rw, d, ebeg, local, rpb, ng, g);
-    rw.acc[lane] = x < a.N ? frp[x] : 0u;
-    rw.fend[lane] = x < a.N ? frp[x + 1] : 0u;
-    wave_lds_sync();
-    for (uint32_t base = 0; base < total; base += kFillSteps * kWave) {
-        WalkEntry ens[kFillSteps];
-        walk_entries_flagged(rw, base, total, a.col, fflag, ens);
-#pragma unroll
-        for (int u = 0; u < kFillSteps; ++u) {
-            const WalkEntry &en = ens[u];
-            const uint64_t F = __ballot(en.valid && en.fwd);
-            if (en.valid && en.fwd) {
-                const uint32_t xk = x - lane + en.k;
-                const uint32_t pos = rw.acc[en.k] + (uint32_t)__popcll(
-                                                        F & lane_range(en.first, lane) &
-                                                        ~(1ull << lane));
-                if (pos < rw.fend[en.k]) {  // always true: k_b_setup counted the same entries
-                    fsrc[pos] = xk;
-                    fcol[pos] = rw.rpb[en.k] - rw.g[en.k] + (uint32_t)en.y;
-                }
-            }
-            wave_lds_sync();  // every lane has read acc before the row's last lane adds to it
-            if (en.valid && lane == en.last)
-                rw.acc[en.k] += (uint32_t)__popcll(F & lane_range(en.first, lane));
-            wave_lds_sync();
+        s = start[x];
+        if (d > acap || s > acap - d) {  // only when the graphs' ranges overlap
+            graph_error(a, g, TC_E_ARG, gstat);
+            d = 0;
         }
     }
-}
-
-// work items: heavy rows (more than `light_max` forward neighbours) in chunks of kitem; the
-// light rows are counted in chunks of consecutive forward edges: light[0] = forward edges,
-// light[1] = chunks
-__global__ void k_b_items(const BatchArgs *__restrict__ args, uint32_t ncap,
-                          const uint32_t *__restrict__ fdeg, const uint32_t *__restrict__ frp,
-                          uint32_t light_max, uint32_t *__restrict__ items,
-                          uint32_t *__restrict__ light) {
-    const BatchArgs a = *args;
-    const uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x > ncap) return;
-    const uint32_t d = (x < a.N) ? fdeg[x] : 0u;
-    items[x] = d > light_max ? (d + a.kitem - 1) / a.kitem : 0u;
-    if (x == ncap) {
-        const uint32_t mf = frp[ncap];
-        light[0] = mf;
-        light[1] = (mf + a.chunk - 1) / a.chunk;
+    mark[lane] = 0;
+    fcount[lane] = 0;
+    const gptr_i32 col = (gptr_i32)a.col;
+    uint32_t round = 0;
+    uint64_t part_h = 0;  // lanes 0 and 1: this wave's parts of graphs that span waves
+    uint32_t part_f = 0;
+    for (uint64_t todo = __ballot(d > 0); todo;) {
+        const uint32_t gc = (uint32_t)__builtin_amdgcn_readlane((int)g, __ffsll((long long)todo) - 1);
+        const bool mine = d > 0 && g == gc;
+        todo &= ~__ballot(mine);
+        const int64_t v0 = a.vtx_off[gc];
+        const uint32_t ng = (uint32_t)(a.vtx_off[gc + 1] - v0);
+        const gptr_i32 rp = (gptr_i32)(a.row_ptr + v0 + gc);
+        const gptr_i32 gdeg = (gptr_i32)(deg + v0);
+        const uint32_t lx0 = x0 - (uint32_t)v0;  // local id of lane 0's vertex (modulo 2^32)
+        const uint32_t dm = mine ? d : 0u;
+        const uint32_t incl = wave_incl_scan(dm), off = incl - dm;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+        // the row's place in the input, less its place in the walk
+        const uint32_t in_at =
+            mine ? (uint32_t)(a.adj_off[gc] + rp[(uint32_t)(lx0 + lane)]) - off : 0u;
+        uint32_t carry = 0, carry_f = 0;
+        int32_t y_last = -1;
+        uint64_t hsum = 0;
+        // kWalkSteps steps from `base` on; full: every lane has an entry in each.  Conditions are
+        // combined without short circuits, so that a step has no branch but the stores'.
+        auto walk = [&](uint32_t base, auto full) {
+            uint32_t k[kWalkSteps];
+            int32_t y[kWalkSteps], dy[kWalkSteps];
+#pragma unroll
+            for (int u = 0; u < kWalkSteps; ++u) {
+                k[u] = round_owner(mark, off, dm, base + u * kWave, ++round, carry) - 1u;
+                const uint32_t at = wave_bcast_from(in_at, k[u]);
+                const uint32_t idx = base + u * kWave + lane;
+                y[u] = (full || idx < total) ? col[at + idx] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kWalkSteps; ++u)
+                dy[u] = gdeg[(uint32_t)y[u] < ng ? (uint32_t)y[u] : 0u];
+#pragma unroll
+            for (int u = 0; u < kWalkSteps; ++u) {
+                const uint32_t sb = base + u * kWave, idx = sb + lane;
+                const bool valid = full || idx < total;
+                const uint32_t dk = wave_bcast_from(d, k[u]), ok_ = wave_bcast_from(off, k[u]);
+                const uint32_t sk = wave_bcast_from(s, k[u]);
+                const uint32_t yu = (uint32_t)y[u], lk = valid ? lx0 + k[u] : 0u;
+                const bool ok = (yu < ng) & (yu != lk) & valid;
+                const bool fwd =
+                    ok & ((dy[u] > (int32_t)dk) | ((dy[u] == (int32_t)dk) & (yu > lk)));
+                // the entry before this one (lane 0: the previous step's last)
+                const int32_t prev = __builtin_amdgcn_update_dpp(y_last, y[u], 0x138, 0xf, 0xf,
+                                                                 false);  // wave_shr:1
+                y_last = __builtin_amdgcn_readlane(y[u], kWave - 1);
+                const bool bad = valid & (!ok | ((idx > ok_) & (y[u] <= prev)));
+                if (__ballot(bad)) {
+                    if (bad)
+                        graph_error(a, gc,
+                                    !ok ? (yu >= ng ? TC_E_RANGE : TC_E_SELF_LOOP)
+                                        : (y[u] == prev ? TC_E_DUP_EDGE : TC_E_UNSORTED),
+                                    gstat);
+                }
+                // (lanes without an entry hash the pair {0, 0} to 0; a graph with other entries
+                // that are not ok is reported whatever its sum)
+                const uint64_t h = pair_hash(min(lk, yu), max(lk, yu));
+                hsum += fwd ? h : 0ull - h;
+                // forward entries of the row before this one
+                const uint64_t F = __ballot(fwd);
+                const bool begun = ok_ >= sb;  // the row starts in this step
+                const uint32_t rank = (uint32_t)__popcll(
+                    F & lanes_from_to(begun ? (ok_ - sb) & 63u : 0u, lane)) + (begun ? 0u : carry_f);
+                if (fwd) fcol[sk + rank] = (uint32_t)v0 + yu;
+                const uint32_t upto = rank + (fwd ? 1u : 0u);
+                if (valid & (idx + 1 == ok_ + dk)) fcount[k[u]] = upto;
+                carry_f = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+            }
+        };
+        uint32_t base = 0;
+        for (; base + kWalkSteps * kWave <= total; base += kWalkSteps * kWave)
+            walk(base, std::true_type{});
+        if (base < total) walk(base, std::false_type{});
+        wave_lds_sync();
+        const uint64_t hs = wave_sum_u64(hsum);
+        const uint32_t fs = wave_total(mine ? fcount[lane] : 0u);
+        const uint32_t span = graph_span(a.vtx_off, gc, x0, vshift);
+        if (span == kSpanWhole) {
+            if (lane == 0) {
+                ghash[gc] = hs;
+                gfwd[gc] = fs;
+            }
+        } else if (lane == span) {
+            part_h = hs;
+            part_f = fs;
+        }
+    }
+    if (lane < 2) {
+        whash[2 * (x0 >> vshift) + lane] = part_h;
+        wfwd[2 * (x0 >> vshift) + lane] = part_f;
+    }
+    const uint32_t f = d > 0 ? fcount[lane] : 0u;
+    if (in) frow[x] = make_uint2(s, s + f);
+    // heavy rows (more than light_max forward neighbours) in items of kitem of them
+    const uint32_t ni = f > light_max ? (f + kitem - 1) / kitem : 0u;
+    if (__ballot(ni > 0)) {
+        const uint32_t iincl = wave_incl_scan(ni);
+        uint32_t at = 0;
+        if (lane == kWave - 1) at = atomicAdd(n_items, iincl);
+        at = wave_bcast(at, kWave - 1) + iincl - ni;
+        for (uint32_t j = 0; j < ni; ++j) items[at + j] = make_uint2(x, s + j * kitem);
     }
 }
 
-__global__ void k_b_item_fill(const uint32_t *__restrict__ items,
-                              const uint32_t *__restrict__ off, uint32_t ncap,
-                              uint32_t *__restrict__ item_u) {
-    const uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= ncap) return;
-    const uint32_t k = items[x], o = off[x];
-    for (uint32_t j = 0; j < k; ++j) item_u[o + j] = x;
-}
-
-// per-graph checks that need the whole graph, and the per-graph status out (the caller's
-// array, when given).  Offsets: the graph's vertex and adjacency ranges must lie inside the
-// batch (k_b_setup checked them only for graphs that have vertices).  Symmetry: the entries
-// must number twice the forward entries, and the graph's symmetry sum must be zero (a set of
-// entries that is not closed under mirroring passes this with probability about 2^-64).
-__global__ void k_b_finish(const BatchArgs *__restrict__ args, const uint32_t *__restrict__ frp,
-                           const unsigned long long *__restrict__ ghash,
-                           int32_t *__restrict__ gstat) {
+// one wave per graph: the sums of a graph that spans waves from their parts, the checks that
+// need the whole graph, and the status out (the caller's array, when given).  Offsets: the
+// graph's vertex and adjacency ranges must lie inside the batch (k_b_rows checked them only for
+// graphs that have vertices).  Symmetry: the entries must number twice the forward entries, and
+// the graph's symmetry sum must be zero (a set of entries that is not closed under mirroring
+// passes this with probability about 2^-64).
+__global__ __launch_bounds__(256) void k_b_finish(const BatchArgs *__restrict__ args,
+                                                  uint32_t vshift,
+                                                  const unsigned long long *__restrict__ ghash,
+                                                  const uint32_t *__restrict__ gfwd,
+                                                  const unsigned long long *__restrict__ whash,
+                                                  const uint32_t *__restrict__ wfwd,
+                                                  const unsigned long long *__restrict__ wtotal,
+                                                  const int32_t *__restrict__ gstat) {
     const BatchArgs a = *args;
-    const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t g = blockIdx.x * 4 + threadIdx.x / kWave, lane = lane_id();
     if (g >= a.G) return;
+    const int64_t v0 = a.vtx_off[g], v1 = a.vtx_off[g + 1];
+    const int64_t a0 = a.adj_off[g], a1 = a.adj_off[g + 1];
     int32_t st = gstat[g];
-    if (st == 0) {
-        const int64_t v0 = a.vtx_off[g], v1 = a.vtx_off[g + 1];
-        const int64_t a0 = a.adj_off[g], a1 = a.adj_off[g + 1];
-        if (v0 < 0 || v1 < v0 || v1 > (int64_t)a.N || a0 < 0 || a1 < a0 || a1 > (int64_t)a.A)
-            st = TC_E_ARG;
-        else if (2 * (int64_t)(frp[v1] - frp[v0]) != a1 - a0 || ghash[g] != 0)
-            st = TC_E_ASYMMETRIC;
-        gstat[g] = st;
+    const bool inside = v0 >= 0 && v1 >= v0 && v1 <= (int64_t)a.N && a0 >= 0 && a1 >= a0 &&
+                        a1 <= (int64_t)a.A;
+    if (st == 0 && !inside) st = TC_E_ARG;
+    if (inside) {
+        uint64_t h = 0, t = 0, f = 0;
+        const uint32_t w0 = (uint32_t)v0 >> vshift;
+        if (v1 > v0 && ((uint32_t)(v1 - 1) >> vshift) > w0) {
+            const uint32_t w1 = (uint32_t)(v1 - 1) >> vshift;
+            for (uint32_t w = w0 + lane; w <= w1; w += kWave) {
+                const uint32_t i = 2 * w + (w == w0 ? kSpanAfter : kSpanBefore);
+                h += whash[i];
+                f += wfwd[i];
+                t += wtotal[i];
+            }
+            h = wave_sum_u64(h);
+            f = wave_sum_u64(f);
+            t = wave_sum_u64(t);
+            if (lane == 0 && t) a.totals[g] += t;
+        } else {
+            h = ghash[g];
+            f = gfwd[g];
+        }
+        if (st == 0 && (2 * (int64_t)f != a1 - a0 || h != 0)) st = TC_E_ASYMMETRIC;
     }
-    if (a.status) a.status[g] = st;
+    if (a.status && lane == 0) a.status[g] = st;
 }
 
 // ------------------------------------------------------------------ workspace + plan
 
 struct BatchLayout {
-    size_t args, ctl, gstat, ghash, gid, deg, fdeg, frp, fcol, fsrc, fflag, items, ioff, item_u,
+    size_t args, ctl, gstat, ghash, gfwd, gid, deg, start, frow, fcol, items, whash, wfwd, wtotal,
         scan, total;
 };
 
 constexpr uint32_t kMinItemEdges = 16;
 
-static BatchLayout batch_layout(uint32_t gcap, uint32_t ncap, uint64_t acap) {
-    BatchLayout L;
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        size_t at = off;
-        off = align_up(off + (bytes ? bytes : 1), 256);
-        return at;
-    };
-    const uint64_t n1 = (uint64_t)ncap + 1;
-    L.args = take(sizeof(BatchArgs));
-    L.ctl = take(64 * 4);
-    L.gstat = take((size_t)gcap * 4);
-    L.ghash = take((size_t)gcap * 8);
-    L.gid = take((size_t)ncap * 4);
-    L.deg = take((size_t)ncap * 4);
-    L.fdeg = take(n1 * 4);
-    L.frp = take(n1 * 4);
-    L.fcol = take((size_t)acap * 4 + count_col_pad_bytes());
-    L.fsrc = take((size_t)acap * 4);
-    L.fflag = take((size_t)acap);  // one byte per input entry: forward (k_b_setup)
-    L.items = take(n1 * 4);
-    L.ioff = take(n1 * 4);
-    L.item_u = take(((size_t)acap / kMinItemEdges + n1 + 1) * 4);
-    L.scan = take(scan_scratch_words(n1) * 4);
-    L.total = off;
-    return L;
+// Vertices per wave of the setup and the light counting: 64, or fewer when that leaves the chip
+// idle (down to 8, below 8192 waves: two per SIMD).  Counting four R-MAT graphs of 15,360 vertices
+// together took 950 us when 38 waves shared them and takes 59 us with 1920.
+static uint32_t batch_vshift(uint32_t ncap) {
+    uint32_t v = 6;
+    while (v > 3 && (ncap >> v) < 8192u) --v;
+    return v;
 }
 
 }  // namespace tc
@@ -501,7 +399,36 @@ static uint32_t parse_tuning_or_zero(const char *json, const char *key, uint32_t
     return v >= 0 ? (uint32_t)(v > 0x7FFFFFFFl ? 0x7FFFFFFFl : v) : dflt;
 }
 
-// enqueue the whole sequence (this is what gets captured)
+static BatchLayout batch_layout(uint32_t gcap, uint32_t ncap, uint64_t acap) {
+    BatchLayout L;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        size_t at = off;
+        off = align_up(off + (bytes ? bytes : 1), 256);
+        return at;
+    };
+    const uint64_t n1 = (uint64_t)ncap + 1;
+    L.args = take(sizeof(BatchArgs));
+    L.ctl = take(64 * 4);
+    L.gstat = take((size_t)gcap * 4);
+    L.ghash = take((size_t)gcap * 8);
+    L.gfwd = take((size_t)gcap * 4);
+    L.gid = take((size_t)ncap * 4);
+    L.deg = take(n1 * 4);
+    L.start = take(n1 * 4);
+    L.frow = take((size_t)ncap * 8);
+    L.fcol = take((size_t)acap * 4 + count_col_pad_bytes());
+    L.items = take(((size_t)acap / kMinItemEdges + n1) * 8);
+    const size_t parts = 2 * (((size_t)ncap >> batch_vshift(ncap)) + 1);
+    L.whash = take(parts * 8);
+    L.wfwd = take(parts * 4);
+    L.wtotal = take(parts * 8);
+    L.scan = take(scan_scratch_words(n1) * 4);
+    L.total = off;
+    return L;
+}
+
+// enqueue the whole sequence after k_b_begin (this is what gets captured)
 static int batch_enqueue(tc_plan *p, bool pv, hipStream_t s) {
     const BatchLayout &L = p->L;
     char *ws = (char *)p->ws;
@@ -509,54 +436,46 @@ static int batch_enqueue(tc_plan *p, bool pv, hipStream_t s) {
     uint32_t *ctl = (uint32_t *)(ws + L.ctl);
     int32_t *gstat = (int32_t *)(ws + L.gstat);
     unsigned long long *ghash = (unsigned long long *)(ws + L.ghash);
+    unsigned long long *whash = (unsigned long long *)(ws + L.whash);
+    unsigned long long *wtotal = (unsigned long long *)(ws + L.wtotal);
+    uint32_t *gfwd = (uint32_t *)(ws + L.gfwd), *wfwd = (uint32_t *)(ws + L.wfwd);
     uint32_t *gid = (uint32_t *)(ws + L.gid), *deg = (uint32_t *)(ws + L.deg);
-    uint32_t *fdeg = (uint32_t *)(ws + L.fdeg), *frp = (uint32_t *)(ws + L.frp);
-    uint32_t *fcol = (uint32_t *)(ws + L.fcol), *items = (uint32_t *)(ws + L.items);
-    uint32_t *fsrc = (uint32_t *)(ws + L.fsrc);
-    uint32_t *ioff = (uint32_t *)(ws + L.ioff), *item_u = (uint32_t *)(ws + L.item_u);
-    uint32_t *scan = (uint32_t *)(ws + L.scan);
-    const uint32_t ncap = p->ncap, n1 = ncap + 1;
-    const uint32_t cap = ncap > p->gcap ? ncap : p->gcap;
+    uint32_t *start = (uint32_t *)(ws + L.start), *fcol = (uint32_t *)(ws + L.fcol);
+    uint2 *frow = (uint2 *)(ws + L.frow), *items = (uint2 *)(ws + L.items);
+    const uint32_t ncap = p->ncap, n1 = ncap + 1, vshift = batch_vshift(ncap);
     auto grid = [](uint64_t n) { return dim3((uint32_t)((n + 255) / 256)); };
-    hipLaunchKernelGGL(k_b_clear, dim3(1024), dim3(256), 0, s, args, gstat, ghash, ctl, cap);
-    // one wave per 64 vertices, four waves per workgroup
-    auto vgrid = [](uint64_t n) { return dim3((uint32_t)((n + 255) / 256)); };
-    uint8_t *fflag = (uint8_t *)(ws + L.fflag);
-    hipLaunchKernelGGL(k_b_setup, vgrid(n1), dim3(256), 0, s, args, ncap, gid, deg, fdeg, fflag,
-                       ghash, gstat);
+    hipLaunchKernelGGL(k_b_rows, grid(n1), dim3(256), 0, s, args, ncap, gid, deg, gstat);
     if (hipGetLastError() != hipSuccess) return TC_E_HIP;
-    if (scan_exclusive_u32(fdeg, frp, n1, scan, s) != hipSuccess) return TC_E_HIP;
-    hipLaunchKernelGGL(k_b_ffill, vgrid(ncap), dim3(256), 0, s, args, gid, deg, frp, fflag, fcol,
-                       fsrc);
-    // ctl: [0] heavy-item queue, [1] light-chunk queue, [2] forward edges, [3] light chunks
-    hipLaunchKernelGGL(k_b_items, grid(n1), dim3(256), 0, s, args, ncap, fdeg, frp,
-                       p->light_max, items, ctl + 2);
-    if (hipGetLastError() != hipSuccess) return TC_E_HIP;
-    if (scan_exclusive_u32(items, ioff, n1, scan, s) != hipSuccess) return TC_E_HIP;
-    hipLaunchKernelGGL(k_b_item_fill, grid(ncap), dim3(256), 0, s, items, ioff, ncap, item_u);
+    if (scan_exclusive_u32(deg, start, n1, (uint32_t *)(ws + L.scan), s) != hipSuccess)
+        return TC_E_HIP;
+    const uint32_t waves = ceil_div(ncap > 0 ? ncap : 1, 1ull << vshift);
+    hipLaunchKernelGGL(k_b_setup, dim3(ceil_div(waves, 4)), dim3(256), 0, s, args,
+                       (uint32_t)p->acap, vshift, gid, deg, start, p->light_max, p->kitem, frow,
+                       fcol, items, ctl + 1, ghash, gfwd, whash, wfwd, gstat);
     if (hipGetLastError() != hipSuccess) return TC_E_HIP;
     BatchKernelArgs ka;
-    ka.frp = frp;
+    ka.frow = frow;
     ka.fcol = fcol;
-    ka.fsrc = fsrc;
     ka.gid = gid;
-    ka.item_u = item_u;
-    ka.item_off = ioff;
-    ka.n_items = ioff + ncap;
-    ka.kitem = &args->kitem;
-    ka.chunk = &args->chunk;
-    ka.light = ctl + 2;
+    ka.items = items;
+    ka.n_items = ctl + 1;
+    ka.n = &args->N;
+    ka.vtx_off_pp = &args->vtx_off;
+    ka.wtotal = wtotal;
     ka.queue = ctl;
     ka.totals_pp = &args->totals;
     ka.tpv_pp = &args->per_vertex;
+    ka.kitem = p->kitem;
     ka.light_max = p->light_max;
     ka.wave_bits = p->wave_bits;
     ka.wave_list = pv ? (p->wave_list < count_wave_list(true) ? p->wave_list
                                                               : count_wave_list(true))
                       : p->wave_list;
-    if (launch_count_u(ka, pv, device_cu_count() * p->wgs_per_cu, s) != hipSuccess)
+    ka.window = count_light_window(p->chunk, p->light_max);
+    if (launch_count_u(ka, pv, device_cu_count() * p->wgs_per_cu, ncap, vshift, s) != hipSuccess)
         return TC_E_HIP;
-    hipLaunchKernelGGL(k_b_finish, grid(p->gcap), dim3(256), 0, s, args, frp, ghash, gstat);
+    hipLaunchKernelGGL(k_b_finish, dim3(ceil_div(p->gcap, 4)), dim3(256), 0, s, args, vshift,
+                       ghash, gfwd, whash, wfwd, wtotal, gstat);
     return hipGetLastError() == hipSuccess ? TC_OK : TC_E_HIP;
 }
 
@@ -608,11 +527,13 @@ static int plan_set_args(tc_plan *p, int32_t G, const int64_t *d_vtx_off,
     a.status = d_status;
     a.G = (uint32_t)G;
     a.N = (uint32_t)n_total;
-    a.kitem = p->kitem;
     a.A = (uint32_t)adj_total;
-    a.chunk = p->chunk;
-    hipLaunchKernelGGL(k_b_set_args, dim3(1), dim3(64), 0, s,
-                       (BatchArgs *)((char *)p->ws + p->L.args), a);
+    char *ws = (char *)p->ws;
+    const uint64_t cap = d_per_vertex && n_total > G ? (uint64_t)n_total : (uint64_t)G;
+    const uint32_t blocks = ceil_div(cap, 256) < 1024u ? ceil_div(cap, 256) : 1024u;
+    hipLaunchKernelGGL(k_b_begin, dim3(blocks), dim3(256), 0, s, (BatchArgs *)(ws + p->L.args), a,
+                       (int32_t *)(ws + p->L.gstat), (unsigned long long *)(ws + p->L.ghash),
+                       (uint32_t *)(ws + p->L.gfwd), (uint32_t *)(ws + p->L.ctl));
     return hipGetLastError() == hipSuccess ? TC_OK : TC_E_HIP;
 }
 

@@ -55,13 +55,15 @@ constexpr uint32_t kPanelRanks = kLdsWords - 32;      // mask table: one word pe
 // half of the workgroup's LDS (words 0 .. kPvWindow - 1, and word kPvWindow always zero)
 constexpr uint32_t kPvPanelWords = kLdsWords / 2;
 constexpr uint32_t kPvWindow = kPvPanelWords - 1;
-// batched kernel: rows with at most kLightMax forward entries are counted edge by edge; a
-// chunk of forward edges plus kLightMax entries on either side must fit one wave's slice
+// batched kernel: rows with at most kLightMax forward entries are counted edge by edge, at most
+// kLightChunkMax staged entries at a time
 constexpr uint32_t kLightMax = 256;
-constexpr uint32_t kLightChunkMax = kSliceWords - 2 * kLightMax;
-// light segments' pieces: their lists are short (a few elements), so shorter pieces waste
-// fewer lookups on masked positions
+constexpr uint32_t kLightChunkMax = 1536;
+// light rows' pieces: their lists are short (a few elements), so shorter pieces waste fewer
+// lookups on masked positions
 constexpr uint32_t kLightPiece = 8;
+constexpr int kLightThreads = 256;
+constexpr int kLightWaves = kLightThreads / kWave;
 
 // ------------------------------------------------------------------ membership probes
 
@@ -171,10 +173,12 @@ struct PanelSegs {
 };
 
 struct OutEdgeSegs {  // u-centric kernel: the whole list N+(v) of out-neighbour v, owner v
-    const uint32_t *row_ptr, *col;
+    const uint2 *frow;
+    const uint32_t *col;
     __device__ __forceinline__ SegRec rec(uint32_t e) const {
         const uint32_t v = col[e];
-        return SegRec{row_ptr[v], row_ptr[v + 1], 0u, 0u, v};
+        const uint2 r = frow[v];
+        return SegRec{r.x, r.y, 0u, 0u, v};
     }
 };
 
@@ -472,25 +476,6 @@ __device__ __forceinline__ uint32_t high_hits_u(const PanelHighProbe &probe,
     return hits;
 }
 
-// Owner of piece q0 + lane in a round of a piece sequence: every segment whose first piece
-// (my_off, of this lane's segment, which has p pieces) falls in the round marks that lane in
-// the wave's table (tagged with the round number, so older marks read as none), and the
-// running maximum over the lanes carries the last mark forward; lanes before the round's
-// first mark belong to carry, the previous round's last segment (plus one).  Returns the
-// owner plus one (all lanes active).
-__device__ __forceinline__ uint32_t round_owner(uint32_t *mark, uint32_t my_off, uint32_t p,
-                                                uint32_t q0, uint32_t round, uint32_t &carry) {
-    const uint32_t lane = lane_id();
-    const uint32_t pos = my_off - q0;
-    if (p && pos < kWave) mark[pos] = (round << 7) | (lane + 1u);
-    wave_lds_sync();
-    const uint32_t mv = mark[lane];
-    const uint32_t m1 = wave_incl_max((mv >> 7) == round ? (mv & 127u) : 0u);
-    const uint32_t owner1 = m1 ? m1 : carry;
-    carry = (uint32_t)__builtin_amdgcn_readlane((int)owner1, kWave - 1);
-    return owner1;
-}
-
 // The calling wave streams one batch of up to 64 segments (r: this lane's record, all zero
 // for no segment) through the probe for total counts and returns this lane's hits.  A segment
 // is the col range [b, en) whose entries from hb on are ranks >= hbase, found in hcol from
@@ -602,28 +587,26 @@ __device__ __forceinline__ uint32_t stream_t(uint32_t first, uint32_t e1, uint32
     return hits;
 }
 
-// Wave-private claims on a shared item counter: kClaim consecutive positions per atomic, so
+// Wave-private claims on a shared item counter: `claim` consecutive positions per atomic, so
 // that the counter (one address that every XCD's waves update) sees few operations when items
 // are small.  Items are sorted heaviest first, so a claim holds items of similar size.
-template <uint32_t kClaim>
 struct WaveQueue {
-    uint32_t next = 0, end = 0;
+    uint32_t claim, next = 0, end = 0;
     __device__ __forceinline__ bool pop(uint32_t *counter, uint32_t n_items, uint32_t &q) {
         if (next == end) {
             uint32_t c = 0;
-            if (lane_id() == 0) c = atomicAdd(counter, kClaim);
+            if (lane_id() == 0) c = atomicAdd(counter, claim);
             c = wave_bcast(c, 0);
             if (c >= n_items) return false;
             next = c;
-            end = min(c + kClaim, n_items);
+            end = min(c + claim, n_items);
         }
         q = next++;
         return true;
     }
 };
-constexpr uint32_t kClaimWave = 8;     // middle-vertex kernel, wave items
-constexpr uint32_t kClaimBatched = 64;  // batched kernel, heavy items
-constexpr uint32_t kClaimLight = 4;     // batched kernel, light chunks
+constexpr uint32_t kClaimWave = 8;      // middle-vertex kernel, wave items
+constexpr uint32_t kClaimBatched = 64;  // batched kernel, heavy items: at most
 
 struct ItemRange {
     uint32_t v, e0, e1, r0, d;
@@ -1123,7 +1106,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
     // alignment of s_mem; otherwise the span bitmap takes its items)
     const bool slices_aligned = (lds_addr(s_mem) & (kSliceWords * 4 - 1)) == 0;
     const uint32_t n_items_a = *n_items_a_ptr;
-    WaveQueue<kClaimWave> wq;
+    WaveQueue wq{kClaimWave};
     for (uint32_t q; wq.pop(queue_a, n_items_a, q);) {
         q = n_items_a - 1 - q;
         const ItemRange it = item_range(q, kitem_a, n1, item_v_a, item_off_a, cptr, row_ptr);
@@ -1213,144 +1196,42 @@ __global__ __launch_bounds__(kThreads) void k_count(
 
 // ------------------------------------------------------------------ batched kernel
 
-// Light segments of the batched kernel.  Segment i of [eb, e1) is edge e = eb + i (u -> v) of
-// the forward CSR, kept when 2 <= d+(u) <= light_max: it streams the whole list N+(v) and
-// looks every element up in N+(u), which the caller staged in LDS (`win` holds fcol from
-// position wbase on; binary search, the list is short).  Returns the hits of this lane's own
-// segment (at most d+(u)); per-vertex counts go to global counters: T(w) per hit, T(u) and
-// T(v) per segment.
-template <bool PV>
-__device__ __forceinline__ uint32_t run_light(uint32_t eb, uint32_t e1,
-                                              const uint32_t *__restrict__ frp,
-                                              const uint32_t *__restrict__ fcol,
-                                              const uint32_t *__restrict__ fsrc,
-                                              const uint32_t *__restrict__ gid,
-                                              const uint32_t *win, uint32_t wbase,
-                                              WaveScratch &ws,
-                                              unsigned long long *__restrict__ tpv,
-                                              uint32_t light_max, uint32_t &graph) {
-    const uint32_t lane = lane_id();
-    const uint32_t e = eb + lane;
-    uint32_t b = 0, en = 0, lo = 0, d = 0, u = 0, v = 0;
-    graph = 0xFFFFFFFFu;
-    if (e < e1) {  // two rounds of independent loads
-        u = fsrc[e];
-        v = fcol[e];
-        const uint32_t r0 = frp[u], r1 = frp[u + 1];
-        b = frp[v];
-        en = frp[v + 1];
-        graph = gid[u];
-        d = r1 - r0;
-        lo = r0 - wbase;
-        if (d < 2 || d > light_max) d = b = en = lo = 0;
-    }
-    const uint32_t a0 = b & ~3u;
-    const uint32_t p = (d && en > b) ? (en - a0 + kLightPiece - 1) / kLightPiece : 0u;
-    const uint32_t incl = wave_incl_scan(p);
-    const uint32_t Q = wave_bcast(incl, kWave - 1);
-    ws.off[lane] = incl - p;
-    ws.beg[lane] = a0;
-    ws.first[lane] = b;
-    ws.end[lane] = en;
-    ws.tag[lane] = lo;
-    ws.aux[lane] = d;
-    ws.cnt[lane] = 0;
-    wave_lds_sync();
-    for (uint32_t q0 = 0; q0 < Q; q0 += kWave) {
-        const uint32_t q = q0 + lane;
-        if (q < Q) {
-            uint32_t k = 0;
-#pragma unroll
-            for (uint32_t step = 32; step; step >>= 1)
-                if (ws.off[k + step] <= q) k += step;
-            const uint32_t start = ws.beg[k] + (q - ws.off[k]) * kLightPiece;
-            const uint32_t first = ws.first[k], stop = ws.end[k];
-            const uint4 *p4 = reinterpret_cast<const uint4 *>(fcol + start);
-            uint32_t wv[kLightPiece];
-#pragma unroll
-            for (uint32_t j = 0; j < kLightPiece / 4; ++j) {
-                const uint4 x = p4[j];
-                wv[4 * j] = x.x;
-                wv[4 * j + 1] = x.y;
-                wv[4 * j + 2] = x.z;
-                wv[4 * j + 3] = x.w;
-            }
-            const uint32_t *list = win + ws.tag[k];
-            const uint32_t dl = ws.aux[k];  // >= 2
-            const uint32_t lo_i = first > start ? first - start : 0u;
-            const uint32_t hi_i = min(stop - start, kLightPiece);
-            // the piece's lookups as binary searches in lockstep (one list per lane)
-            uint32_t base[kLightPiece];
-#pragma unroll
-            for (uint32_t i = 0; i < kLightPiece; ++i) base[i] = 0;
-            for (uint32_t n_left = dl; n_left > 1;) {
-                const uint32_t half = n_left >> 1;
-#pragma unroll
-                for (uint32_t i = 0; i < kLightPiece; ++i)
-                    base[i] = list[base[i] + half - 1] < wv[i] ? base[i] + half : base[i];
-                n_left -= half;
-            }
-            uint32_t packed = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < kLightPiece; ++i) {
-                const uint32_t pos = base[i] + (list[base[i]] < wv[i] ? 1u : 0u);
-                packed |= (list[min(pos, dl - 1u)] == wv[i] ? 1u : 0u) << i;
-            }
-            const uint32_t hmask = hi_i >= 32u ? ~0u : ((1u << hi_i) - 1u);
-            packed &= hmask & ~((1u << lo_i) - 1u);
-            const uint32_t hits = __popc(packed);
-            if (PV) {
-#pragma unroll
-                for (uint32_t i = 0; i < kLightPiece; ++i)
-                    if ((packed >> i) & 1u) atomicAdd(&tpv[wv[i]], 1ull);
-            }
-            if (hits) atomicAdd(&ws.cnt[k], hits);
-        }
-    }
-    wave_lds_sync();
-    const uint32_t h = ws.cnt[lane];
-    if (PV && h) {
-        atomicAdd(&tpv[u], (unsigned long long)h);
-        atomicAdd(&tpv[v], (unsigned long long)h);
-    }
-    return h;
-}
-
 // Batched counting over a disjoint union of small graphs in id space (their oriented lists
 // keep the input's id order, no relabelling).  Every triangle is found once, from its first
 // vertex u in the order of Section 2.2: for every out-neighbour v of u, the common elements of
 // N+(u) and N+(v).
-//   heavy items (u with d+(u) > light_max): (u, chunk of up to kitem out-neighbours of u);
-//     N+(u) is staged in the wave's LDS slice (bitmap over its id span, or a sorted list) and
-//     the whole list N+(v) of every out-neighbour v streams through it.  Hits go to the graph
-//     of u; per-vertex counts credit u (per item), v (per segment) and w (LDS counters by
+//   heavy items (k_count_u; u with d+(u) > light_max): (u, chunk of up to kitem out-neighbours
+//     of u); N+(u) is staged in the wave's LDS slice (bitmap over its id span, or a sorted list)
+//     and the whole list N+(v) of every out-neighbour v streams through it.  Hits go to the
+//     graph of u; per-vertex counts credit u (per item), v (per segment) and w (LDS counters by
 //     list position).
-//   light items: chunks of `chunk` consecutive forward edges, one edge per lane (run_light);
-//     the lists of the chunk's light rows lie inside the window [e0 - light_max, e1 +
-//     light_max) of fcol, which is staged in the wave's slice.  Graph ids are non-decreasing
-//     along the edges, so per-graph totals are summed per run of equal graph ids.
+//   light rows (k_count_light): a wave takes 2^vshift consecutive vertices, stages their light
+//     rows (whole rows, up to `window` entries at a time) in LDS, one edge u -> v per lane.
 
 template <bool PV>
 __global__ __launch_bounds__(kThreads) void k_count_u(const BatchKernelArgs a) {
     __shared__ uint32_t s_mem[kLdsWords];
     __shared__ WaveScratch s_ws[kWaves];
+    const uint32_t n_items = *a.n_items, kitem = a.kitem;
+    if (n_items == 0) return;
     const uint32_t t = threadIdx.x, w = t / kWave, lane = lane_id();
     WaveScratch &ws = s_ws[w];
     uint32_t *mem = s_mem + w * kSliceWords;
     for (uint32_t i = t; i < kLdsWords; i += kThreads) s_mem[i] = 0;
     __syncthreads();
-    const uint32_t *__restrict__ frp = a.frp;
     const uint32_t *__restrict__ fcol = a.fcol;
-    const uint32_t n_items = *a.n_items, kitem = *a.kitem;
     unsigned long long *totals = *a.totals_pp;
     unsigned long long *tpv = PV ? *a.tpv_pp : nullptr;
-    const OutEdgeSegs segs{frp, fcol};
-    WaveQueue<kClaimBatched> wq;
+    const OutEdgeSegs segs{a.frow, fcol};
+    // few items: one per claim, so that they spread over the waves (64 per claim put the hub
+    // rows of a few small graphs on two or three waves)
+    const uint32_t share = n_items / (gridDim.x * kWaves * 4);
+    WaveQueue wq{min(max(share, 1u), kClaimBatched)};
     for (uint32_t q; wq.pop(a.queue, n_items, q);) {
-        q = n_items - 1 - q;
-        const uint32_t u = a.item_u[q];
-        const uint32_t r0 = frp[u], d = frp[u + 1] - r0;
-        const uint32_t e0 = r0 + (q - a.item_off[u]) * kitem;
+        const uint2 item = a.items[q];
+        const uint32_t u = item.x, e0 = item.y;
+        const uint2 ru = a.frow[u];
+        const uint32_t r0 = ru.x, d = ru.y - r0;
         const uint32_t e1 = min(e0 + kitem, r0 + d);
         uint32_t lo = ~0u, hi = 0;  // the id span of N+(u) (rows of invalid graphs may be
         for (uint32_t i = lane; i < d; i += kWave) {  // unsorted, so take min and max)
@@ -1403,44 +1284,225 @@ __global__ __launch_bounds__(kThreads) void k_count_u(const BatchKernelArgs a) {
             if (PV) atomicAdd(&tpv[u], (unsigned long long)item_hits);
         }
     }
-    // light chunks
-    const uint32_t mf = a.light[0], n_chunks = a.light[1], chunk = *a.chunk;
-    WaveQueue<kClaimLight> lq;
-    for (uint32_t q; lq.pop(a.queue + 1, n_chunks, q);) {
-        const uint32_t e0 = q * chunk, e1 = min(e0 + chunk, mf);
-        // the rows of the chunk's first and last edges, clipped to light_max (<= kLightMax)
-        // entries around the chunk (a light row that meets the chunk lies inside)
-        const uint32_t lm = a.light_max;
-        const uint32_t rb = frp[a.fsrc[e0]], re = frp[a.fsrc[e1 - 1] + 1];
-        const uint32_t wbase = max(rb, e0 > lm ? e0 - lm : 0u);
-        const uint32_t wend = min(re, e1 + lm);
-        for (uint32_t i = wbase + lane; i < wend; i += kWave) mem[i - wbase] = fcol[i];
-        wave_lds_sync();
-        for (uint32_t eb = e0; eb < e1; eb += kWave) {
-            uint32_t g;
-            uint32_t h =
-                run_light<PV>(eb, e1, frp, fcol, a.fsrc, a.gid, mem, wbase, ws, tpv, lm, g);
-            // per-graph sums over runs of equal graph ids (non-decreasing along the edges)
-            for (int o = 1; o < kWave; o <<= 1) {
-                const uint32_t hv = (uint32_t)__shfl_up((int)h, o, kWave);
-                const uint32_t gv = (uint32_t)__shfl_up((int)g, o, kWave);
-                if (lane >= (uint32_t)o && gv == g) h += hv;
-            }
-            const uint32_t gn = (uint32_t)__shfl_down((int)g, 1, kWave);
-            if ((lane == kWave - 1 || gn != g) && g != 0xFFFFFFFFu && h)
-                atomicAdd(&totals[g], (unsigned long long)h);
+}
+
+// ------------------------------------------------------------------ light rows
+
+// four entries from a 4-byte aligned position
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// A piece of up to kLightPiece entries of N+(v) (wv, the first `cnt` of them valid) against the
+// staged list at LDS byte address lb (d >= 1 ascending entries): bit kLightPiece - 1 - i of the
+// result is set when wv[i] is in the list, and at[i] is the byte address of the last list entry
+// <= wv[i] (lb when none is).  The piece's binary searches advance in lockstep, three vector
+// operations and one LDS read per step; lanes whose range is down to one entry stay put.
+__device__ __forceinline__ uint32_t light_piece(const uint32_t (&wv)[kLightPiece], uint32_t cnt,
+                                                uint32_t lb, uint32_t d,
+                                                uint32_t (&at)[kLightPiece]) {
+#pragma unroll
+    for (uint32_t i = 0; i < kLightPiece; ++i) at[i] = lb;
+    uint32_t left = cnt ? d * 4u : 4u;  // bytes
+    // the longest range of the wave sets the steps (a scalar loop)
+    uint32_t most = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(left), kWave - 1);
+    for (; most > 4u; most -= (most >> 1) & ~3u) {
+        const uint32_t half = (left >> 1) & ~3u;
+#pragma unroll
+        for (uint32_t i = 0; i < kLightPiece; ++i) {
+            const uint32_t mid = at[i] + half;
+            at[i] = lds_word(mid) <= wv[i] ? mid : at[i];
         }
-        wave_lds_sync();  // the next chunk's window overwrites this one (nothing after the
-                          // light chunks needs a zeroed slice)
+        left -= half;
+    }
+    uint32_t packed = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kLightPiece; ++i)
+        packed = packed + packed + (lds_word(at[i]) == wv[i] ? 1u : 0u);
+    return packed & ~((1u << (kLightPiece - min(cnt, kLightPiece))) - 1u);
+}
+
+__device__ __forceinline__ void load_light_piece(const uint32_t *__restrict__ fcol, uint32_t at,
+                                                 uint32_t (&wv)[kLightPiece]) {
+    const u32x4_a4 *p = reinterpret_cast<const u32x4_a4 *>(fcol + at);
+#pragma unroll
+    for (uint32_t j = 0; j < kLightPiece / 4; ++j) {
+        const u32x4_a4 x = p[j];
+        wv[4 * j] = x[0];
+        wv[4 * j + 1] = x[1];
+        wv[4 * j + 2] = x[2];
+        wv[4 * j + 3] = x[3];
     }
 }
 
-hipError_t launch_count_u(const BatchKernelArgs &a, bool per_vertex, uint32_t grid,
-                          hipStream_t s) {
-    if (per_vertex)
-        hipLaunchKernelGGL(k_count_u<true>, dim3(grid), dim3(kThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_count_u<false>, dim3(grid), dim3(kThreads), 0, s, a);
+// Bound by its vector instructions on 4096 graphs of 3300 vertices (80% of the issue slots), not
+// by memory: so the first piece of every list runs on the lane that owns the edge, with nothing
+// passed between lanes; only the further pieces of longer lists are dealt out, in full rounds
+// of 64 (a part of a round waits for the next 64 edges' pieces).  A wave's hits need no
+// attribution to edges for totals: rows of one graph are taken together and summed once.  An XCD
+// takes stretches of consecutive rows (xcd_stretch_tile), since a graph's lists are read by its
+// neighbours: dealt round-robin, every XCD's L2 fetched every graph (1.2e8 lines missed instead of
+// 4.4e7).  The batch above: 1.74 ms, 3.0 ms when a persistent kernel took chunks of edges.
+//
+// Per-vertex counts: a triangle u, v, w (v and w in N+(u)) is found from the edge u -> v with w
+// in N+(v), and credits the window's counters of the entries v and w of row u.  They are added
+// to T once per entry (one memory atomic per edge that closes triangles, where crediting u, v
+// and w by themselves took one per triangle and two per edge), and T(u) is half of their sum:
+// 300 graphs of 9.0e6 edges took 1630 us, bound by those atomics, and take 340 us.
+template <bool PV>
+__global__ __launch_bounds__(kLightThreads, 8) void k_count_light(const BatchKernelArgs a,
+                                                               uint32_t vshift) {
+    extern __shared__ uint32_t s_dyn[];
+    const uint32_t w = threadIdx.x / kWave, lane = lane_id();
+    const uint32_t per = a.window + a.window / 4 + kWave + (PV ? a.window : 0u);
+    uint32_t *mark = s_dyn + w * per;                           // kWave words
+    uint32_t *list = mark + kWave;                              // window entries
+    uint8_t *own = (uint8_t *)(list + a.window);                // the row of every entry
+    uint32_t *cnt3 = list + a.window + a.window / 4;            // PV: counters of the entries
+    const uint32_t N = *a.n;
+    const uint32_t x0 = (xcd_stretch_tile(blockIdx.x, gridDim.x) * kLightWaves + w) << vshift;
+    if (x0 >= N) return;
+    const uint32_t *__restrict__ fcol = a.fcol;
+    const uint32_t x = x0 + lane;
+    uint2 row = make_uint2(0u, 0u);
+    uint32_t g = ~0u;
+    if ((lane >> vshift) == 0 && x < N) {
+        row = a.frow[x];
+        g = a.gid[x];
+    }
+    uint32_t len = row.y - row.x;
+    if (len < 2 || len > a.light_max) len = 0;
+    unsigned long long *totals = *a.totals_pp;
+    unsigned long long *tpv = PV ? *a.tpv_pp : nullptr;
+    const int64_t *vtx_off = *a.vtx_off_pp;
+    uint64_t part = 0;  // lanes 0 and 1: this wave's parts of graphs that span waves
+    mark[lane] = 0;
+    uint32_t round = 0;
+    const uint32_t list_b = lds_addr(list);
+    for (uint64_t todo = __ballot(len > 0); todo;) {
+        // the rows of one graph (nearly always all of the wave's)
+        const uint32_t gc = (uint32_t)__builtin_amdgcn_readlane((int)g, __ffsll((long long)todo) - 1);
+        const bool mine = len > 0 && g == gc;
+        todo &= ~__ballot(mine);
+        const uint32_t mlen = mine ? len : 0u;
+        const uint32_t incl = wave_incl_scan(mlen);
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+        uint32_t hits = 0;
+        for (uint32_t w0 = 0; w0 < all;) {  // windows of whole rows (window >= light_max)
+            const bool in = mine && incl - mlen >= w0 && incl <= w0 + a.window;
+            const uint64_t in_mask = __ballot(in);
+            const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane(
+                (int)incl, 63 - __builtin_clzll(in_mask));
+            const uint32_t n = w1 - w0;
+            const uint32_t off = incl - mlen - w0;
+            // stage the rows, and the row of every entry
+            uint32_t carry = 0;
+            const uint32_t delta = row.x - off;
+            for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
+                const uint32_t k = round_owner(mark, off, in, i0, ++round, carry) - 1u;
+                const uint32_t dk = wave_bcast_from(delta, k);
+                const uint32_t i = i0 + lane;
+                if (i < n) {
+                    list[i] = fcol[dk + i];
+                    own[i] = (uint8_t)k;
+                    if (PV) cnt3[i] = 0;
+                }
+            }
+            wave_lds_sync();
+            const uint32_t ol = in ? (off | (mlen << 16)) : 0u;
+            // pieces waiting for a full round: lane l < waiting holds one (its start in fcol,
+            // entries, staged list and edge)
+            uint32_t waiting = 0, pb = 0, pc = 0, pr = 0, pe = 0;
+            uint32_t wv[kLightPiece], at[kLightPiece];
+            auto credit = [&](uint32_t packed, uint32_t edge) {
+                hits += (uint32_t)__popc(packed);
+                if (PV && packed) {
+                    atomicAdd(&cnt3[edge], (uint32_t)__popc(packed));
+#pragma unroll
+                    for (uint32_t j = 0; j < kLightPiece; ++j)
+                        if ((packed >> (kLightPiece - 1 - j)) & 1u)
+                            atomicAdd(&cnt3[(at[j] - list_b) >> 2], 1u);
+                }
+            };
+            auto run_waiting = [&]() {
+                if (pc) load_light_piece(fcol, pb, wv);
+                credit(light_piece(wv, pc, list_b + (pr & 0xFFFFu) * 4u, pr >> 16, at), pe);
+            };
+            for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
+                const uint32_t i = i0 + lane;
+                const bool valid = i < n;
+                const uint32_t rk = wave_bcast_from(ol, valid ? (uint32_t)own[i] : 0u);
+                uint2 rv = make_uint2(0u, 0u);
+                if (valid) rv = a.frow[list[i]];
+                const uint32_t c = rv.y - rv.x;
+                if (c) load_light_piece(fcol, rv.x, wv);
+                credit(light_piece(wv, c, list_b + (rk & 0xFFFFu) * 4u, rk >> 16, at), i);
+                // further pieces of longer lists, after the waiting ones; the last, partly
+                // filled round waits
+                const uint32_t p = c > kLightPiece ? (c - 1) / kLightPiece : 0u;
+                if (__ballot(p != 0) == 0) continue;
+                const uint32_t pincl = wave_incl_scan(p);
+                const uint32_t my_off = waiting + pincl - p;
+                const uint32_t Q =
+                    waiting + (uint32_t)__builtin_amdgcn_readlane((int)pincl, kWave - 1);
+                uint32_t pcarry = 0;
+                for (uint32_t q0 = 0; q0 < Q; q0 += kWave) {
+                    const uint32_t k = round_owner(mark, my_off, p, q0, ++round, pcarry) - 1u;
+                    const uint32_t q = q0 + lane - wave_bcast_from(my_off, k);
+                    const uint32_t b = wave_bcast_from(rv.x, k) + (q + 1u) * kLightPiece;
+                    const uint32_t en = wave_bcast_from(rv.y, k);
+                    const uint32_t rq = wave_bcast_from(rk, k);
+                    if (q0 + lane >= waiting) {
+                        pb = b;
+                        pc = q0 + lane < Q ? en - b : 0u;
+                        pr = rq;
+                        pe = i0 + k;
+                    }
+                    waiting = Q - q0;  // (from this round on)
+                    if (waiting < kWave) break;
+                    run_waiting();
+                    waiting = 0;
+                }
+            }
+            if (waiting) run_waiting();
+            wave_lds_sync();
+            if (PV) {
+                for (uint32_t i = lane; i < n; i += kWave)
+                    if (cnt3[i]) atomicAdd(&tpv[list[i]], (unsigned long long)cnt3[i]);
+                uint32_t sum = 0;
+                if (in)
+                    for (uint32_t j = 0; j < mlen; ++j) sum += cnt3[off + j];
+                if (sum) atomicAdd(&tpv[x], (unsigned long long)(sum / 2));
+                wave_lds_sync();
+            }
+            w0 = w1;
+        }
+        const uint64_t sum = wave_sum_u64(hits);
+        const uint32_t span = graph_span(vtx_off, gc, x0, vshift);
+        if (span == kSpanWhole) {
+            if (lane == 0 && sum) totals[gc] += sum;  // (no other wave adds to it meanwhile)
+        } else if (lane == span) {
+            part = sum;
+        }
+    }
+    if (lane < 2) a.wtotal[2 * (x0 >> vshift) + lane] = part;
+}
+
+uint32_t count_light_window(uint32_t chunk, uint32_t light_max) {
+    const uint32_t w = chunk > light_max ? chunk : light_max;
+    return (w + 63u) & ~63u;
+}
+
+hipError_t launch_count_u(const BatchKernelArgs &a, bool per_vertex, uint32_t heavy_wgs,
+                          uint32_t ncap, uint32_t vshift, hipStream_t s) {
+    const dim3 lg(ceil_div(ceil_div(ncap > 0 ? ncap : 1, 1ull << vshift), kLightWaves));
+    const size_t lds = (size_t)kLightWaves * 4 *
+                       (a.window + a.window / 4 + kWave + (per_vertex ? a.window : 0));
+    if (per_vertex) {
+        hipLaunchKernelGGL(k_count_u<true>, dim3(heavy_wgs), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(k_count_light<true>, lg, dim3(kLightThreads), lds, s, a, vshift);
+    } else {
+        hipLaunchKernelGGL(k_count_u<false>, dim3(heavy_wgs), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(k_count_light<false>, lg, dim3(kLightThreads), lds, s, a, vshift);
+    }
     return hipGetLastError();
 }
 

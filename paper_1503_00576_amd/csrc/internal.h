@@ -74,6 +74,29 @@ __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
     return v;
 }
 
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) {  // sum over the lanes, in all lanes
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(x), kWave - 1);
+}
+
+// Owner of element base + lane of a sequence cut into runs, one run per lane: every run whose
+// start (my_off, of this lane's run, non-empty when `any`) falls in the 64 elements from base on
+// marks that lane in the wave's table (tagged with the round number, so older marks read as
+// none; rounds count from 1, the table cleared beforehand), and the running maximum over the
+// lanes carries the last mark forward; lanes before the round's first mark belong to carry, the
+// previous round's last run (plus one).  Returns the owner plus one (all lanes active).
+__device__ __forceinline__ uint32_t round_owner(uint32_t *mark, uint32_t my_off, uint32_t any,
+                                                uint32_t base, uint32_t round, uint32_t &carry) {
+    const uint32_t lane = lane_id();
+    const uint32_t pos = my_off - base;
+    if (any && pos < kWave) mark[pos] = (round << 7) | (lane + 1u);
+    wave_lds_sync();
+    const uint32_t mv = mark[lane];
+    const uint32_t m1 = wave_incl_max((mv >> 7) == round ? (mv & 127u) : 0u);
+    const uint32_t owner1 = m1 ? m1 : carry;
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)owner1, kWave - 1);
+    return owner1;
+}
+
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t x) {
 #pragma unroll
     for (int d = kWave / 2; d >= 1; d >>= 1) {
@@ -101,6 +124,16 @@ constexpr uint32_t kXcds = 8;
 __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t nb) {
     const uint32_t x = b % kXcds, i = b / kXcds, q = nb / kXcds, r = nb % kXcds;
     return x * q + (x < r ? x : r) + i;
+}
+
+// The same in stretches of 64 tiles per XCD, so that a grid whose tiles differ in work stays
+// balanced over the XCDs (the tiles after the last full set of stretches keep their places).
+constexpr uint32_t kXcdStretch = 64;
+__device__ __forceinline__ uint32_t xcd_stretch_tile(uint32_t b, uint32_t nb) {
+    constexpr uint32_t set = kXcds * kXcdStretch;
+    if (b >= nb / set * set) return b;
+    const uint32_t i = b % set;
+    return b - i + (i % kXcds) * kXcdStretch + i / kXcds;
 }
 
 // exclusive scan of uint32 (in may equal out); scratch: scan_scratch_words(N) words
@@ -195,23 +228,45 @@ hipError_t launch_hub_fill(const uint32_t *src, const uint32_t *col, const uint3
 hipError_t launch_hub_count(const uint8_t *A, const uint8_t *At, uint32_t hp, uint32_t h0,
                             unsigned long long *total, unsigned long long *tpv, bool per_vertex,
                             const int32_t *status, hipStream_t s);
+// A wave's sums for the graphs of its vertices.  A graph that lies in one wave's vertices gets its
+// sum directly; one that spans waves has a part from each, without atomics (the waves of a graph
+// run together and would queue on its address, 11 ns each: 36 us for 1920 waves of four graphs):
+// wave w keeps the part of the graph that began before its vertices at entry 2 w, the part of the
+// graph that begins in them and goes on at entry 2 w + 1.  k_b_finish adds them up.
+enum { kSpanBefore = 0, kSpanAfter = 1, kSpanWhole = 2 };
+__device__ __forceinline__ uint32_t graph_span(const int64_t *vtx_off, uint32_t g, uint32_t x0,
+                                               uint32_t vshift) {
+    if (vtx_off[g] < (int64_t)x0) return kSpanBefore;
+    return vtx_off[g + 1] > (int64_t)x0 + (1ll << vshift) ? kSpanAfter : kSpanWhole;
+}
+
+// batched counting over the union's oriented rows (batched.hip): row x is fcol[frow[x].x ..
+// frow[x].y), ids of the union
 struct BatchKernelArgs {
-    const uint32_t *frp, *fcol, *fsrc, *gid;
-    const uint32_t *item_u, *item_off, *n_items;  // heavy items
-    const uint32_t *kitem, *chunk;                // sizes (device)
-    const uint32_t *light;                        // [0] forward edges, [1] light chunks
-    uint32_t *queue;                              // [0] heavy items, [1] light chunks
+    const uint2 *frow;
+    const uint32_t *fcol, *gid;
+    const uint2 *items;       // heavy items (row, first entry); *n_items of them
+    const uint32_t *n_items;
+    const uint32_t *n;        // vertices (device)
+    const int64_t *const *vtx_off_pp;  // the graphs' vertex offsets
+    unsigned long long *wtotal;        // the waves' parts of graphs that span waves
+    uint32_t *queue;
     unsigned long long *const *totals_pp;
     unsigned long long *const *tpv_pp;
+    uint32_t kitem;       // entries per heavy item
     uint32_t light_max;   // rows with at most this many forward entries are light (<= 256)
     uint32_t wave_bits;   // heavy items use a bitmap below this id span (<= kWaveBits)
     uint32_t wave_list;   // ... else a sorted LDS list of at most this many entries
+    uint32_t window;      // entries of light rows staged at a time (count_light_window)
 };
-hipError_t launch_count_u(const BatchKernelArgs &a, bool per_vertex, uint32_t grid,
-                          hipStream_t s);
-// batched kernel: rows with at most count_light_max() forward entries are counted edge by
-// edge in chunks of at most count_light_chunk_max() forward edges
+// heavy items on heavy_wgs workgroups; light rows of up to ncap vertices, one wave per
+// 2^vshift of them
+hipError_t launch_count_u(const BatchKernelArgs &a, bool per_vertex, uint32_t heavy_wgs,
+                          uint32_t ncap, uint32_t vshift, hipStream_t s);
+// batched kernels: rows with at most count_light_max() forward entries are counted edge by
+// edge, count_light_window(chunk, light_max) staged entries at a time
 uint32_t count_light_max();
 uint32_t count_light_chunk_max();
+uint32_t count_light_window(uint32_t chunk, uint32_t light_max);
 
 }  // namespace tc

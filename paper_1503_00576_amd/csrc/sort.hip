@@ -61,10 +61,6 @@ __device__ __forceinline__ uint4 scan_load4(const uint32_t *__restrict__ in, uin
     return x;
 }
 
-__device__ __forceinline__ uint32_t wave_total(uint32_t x) {  // sum over the lanes, in all lanes
-    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(x), kWave - 1);
-}
-
 // sums[b] = total of tile b
 __global__ __launch_bounds__(kScanThreads) void k_scan_sums(const uint32_t *__restrict__ in,
                                                             uint64_t N,

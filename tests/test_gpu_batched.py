@@ -346,3 +346,51 @@ def test_autotune_batched(tmp_path):
     check(res, gs, want)
     plan.close()
     assert autotune.tune_batched(b, cache=cache, candidates=cands[:1])[0] == best
+
+
+@pytest.mark.parametrize("where", [1, 62, 63, 64, 65, 127, 128, 255, 256])
+def test_bad_order_at_walk_steps(where):
+    """A descending and a repeated pair at the setup walk's step and lane edges, in the middle
+    graph of three: reported for that graph only."""
+    k = 300
+    star = torch.tensor([(0, x) for x in range(1, k)], dtype=torch.int32)
+    gs = [synth.watts_strogatz(20, 3, 0.1, 5), star, synth.watts_strogatz(33, 4, 0.1, 6)]
+    gs = [(gs[0], 20), (gs[1], k), (gs[2], 33)]
+    want = [oracle.count(e, n) for e, n in gs]
+    packed = synth.pack_symmetric(gs)
+    base = int(packed["adj_off"][1])
+    for kind, status in (("swap", api.E_UNSORTED), ("repeat", api.E_DUP_EDGE)):
+        b = as_batch(packed)
+        col = packed["col"].clone()
+        if kind == "swap":
+            col[base + where], col[base + where - 1] = (int(packed["col"][base + where - 1]),
+                                                        int(packed["col"][base + where]))
+        else:
+            col[base + where] = col[base + where - 1]
+        b.col = col.to(DEV)
+        res = api.count_batched_async(b, per_vertex=True)
+        assert res.status.tolist() == [0, status, 0]
+        tot = res.totals.tolist()
+        assert tot[0] == want[0] and tot[2] == want[2]
+
+
+@pytest.mark.parametrize("tuning", [{"light_max": 64, "chunk_e": 64}, {"light_max": 256},
+                                    {"light_max": 255, "chunk_e": 64}, {"light_max": 0},
+                                    {"light_max": 2, "chunk_e": 1536, "items_k": 16}])
+@pytest.mark.parametrize("many", [False, True])
+def test_light_rows_at_window_edges(tuning, many):
+    """Rows around light_max, windows that hold one row, waves that straddle graphs, pieces of
+    1, 7, 8, 9, 16, 17 entries; few vertices per wave (small capacity) and 64 (large)."""
+    gs = []
+    for k in (2, 3, 8, 9, 10, 17, 18, 64, 65, 66, 256, 257, 258):
+        gs.append((torch.tensor([(i, j) for i in range(k) for j in range(i + 1, k)],
+                                dtype=torch.int32), k))
+        gs.append((torch.zeros((0, 2), dtype=torch.int32), 1))
+    gs.append((synth.erdos_renyi(300, 0.5, 3), 300))
+    want = oracle_per_graph(gs)
+    b = as_batch(synth.pack_symmetric(gs))
+    cap = (64 * 8192 if many else b.n_total) + 1
+    plan = api.BatchPlan(b.G, cap, b.adj_total, tuning, device=DEV)
+    for pv in (True, False):
+        check(plan.run_async(b, per_vertex=pv), gs, want, per_vertex=pv)
+    plan.close()
