@@ -35,10 +35,7 @@ __global__ void k_row_sort(uint32_t *, const uint32_t *, const uint32_t *, uint3
                            uint32_t, uint32_t *, uint32_t *, uint32_t *, int32_t *);
 __global__ void k_row_sort_long(uint32_t *, const uint32_t *, const uint32_t *,
                                 const uint32_t *, uint32_t, uint32_t *, int32_t *);
-__global__ void k_hlen(const uint32_t *, const uint32_t *, uint32_t, uint32_t, uint32_t *);
-__global__ void k_rowlen(const uint32_t *, const uint32_t *, uint32_t, uint32_t *);
-__global__ void k_vrange(const uint32_t *, const uint32_t *, uint32_t, uint32_t, uint64_t *);
-__global__ void k_panel_range(const uint64_t *, uint32_t, uint32_t, uint32_t, uint32_t,
+__global__ void k_panel_range(const uint32_t *, const uint32_t *, uint32_t, uint32_t, uint32_t,
                               uint64_t *);
 __global__ void k_csc_keys(const uint32_t *, const uint32_t *, const uint32_t *,
                            const uint32_t *, const uint32_t *, uint32_t, const uint64_t *,
@@ -46,12 +43,10 @@ __global__ void k_csc_keys(const uint32_t *, const uint32_t *, const uint32_t *,
                            uint32_t *, uint4 *, uint16_t *, const int32_t *);
 __global__ void k_csc_final(const uint32_t *, uint32_t, const uint32_t *, uint64_t, uint32_t *,
                             uint32_t *, const int32_t *);
-__global__ void k_items(const uint32_t *, const uint32_t *, const uint32_t *, uint32_t, uint32_t,
-                        uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t *,
-                        uint32_t *,
-                        uint32_t *, uint32_t *, const int32_t *);
-__global__ void k_item_fill(const uint32_t *, const uint32_t *, uint64_t, uint32_t *,
-                            const int32_t *);
+__global__ void k_items(const uint32_t *, const uint32_t *, const uint32_t *, const uint32_t *,
+                        uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t,
+                        uint32_t, uint32_t *, uint32_t *, uint32_t *, uint32_t *, const int32_t *);
+__global__ void k_item_fill(const ItemLists, uint64_t, const int32_t *);
 __global__ void k_pv_out(const unsigned long long *, const uint32_t *, uint32_t,
                          unsigned long long *);
 __global__ void k_zero_u64(unsigned long long *, uint64_t);
@@ -78,8 +73,7 @@ int device_cu_count() {
 
 struct Layout {
     size_t ctl, part_hist, part_offs, part_scan, deg, perm, rank, keys_a, keys_b, sort_scratch,
-        rs, re, rowlen, row_ptr, col, hcol, hrow, hstart, src, vrange, prange, eu, lrs, lre, cnt,
-        cptr, cbeg, items[4], off[4], item_v[4], scan_scratch, tpv, hub_a, hub_at, rchunk,
+        rs, re, row_ptr, col, hcol, hrow, hstart, src, prange, eu, lrs, lre, cptr, cbeg, items[4], off[4], item_v[4], scan_scratch, tpv, hub_a, hub_at, rchunk,
         long_rows, total_bytes;
     uint32_t part_tiles;  // 0: degrees by atomics (inputs too large for the partition)
     int part_shift;
@@ -101,15 +95,21 @@ enum {
     kCtlStatus = 0, kCtlBoth = 1, kCtlQueueA = 2, kCtlQueueB = 3, kCtlFinger = 4, kCtlRun = 5,
     kCtlQueueC = 6, kCtlLongRows = 7, kCtlKept = 8, kCtlWords = 64
 };
-// start of a preprocessing: clear the control words and record the layout's fingerprint
-__global__ void k_ctl_init(uint32_t *__restrict__ ctl, uint32_t finger) {
+// start of a preprocessing: clear the control words, record the layout's fingerprint, and clear the
+// word after the degree partition's table (nullable), which its scan reads as well
+__global__ void k_ctl_init(uint32_t *__restrict__ ctl, uint32_t finger,
+                           uint32_t *__restrict__ part_end) {
     const uint32_t t = threadIdx.x;
     ctl[t] = t == kCtlFinger ? finger : 0u;  // 64 threads, one word each
+    if (part_end && t == 0) *part_end = 0u;
 }
 
 // start of a count on a prepared workspace: its status is the preprocessing's, or a mismatch
-// when the workspace was prepared for another layout; the item queues restart
-__global__ void k_ctl_check(uint32_t *__restrict__ ctl, uint32_t finger) {
+// when the workspace was prepared for another layout (no counting kernel adds to it, so the
+// caller's word is written here); the item queues and the total restart
+__global__ void k_count_begin(uint32_t *__restrict__ ctl, uint32_t finger,
+                              unsigned long long *__restrict__ total,
+                              int32_t *__restrict__ d_status) {
     if (threadIdx.x != 0) return;
     int32_t st = (int32_t)ctl[kCtlStatus];
     if (st == 0 && ctl[kCtlFinger] != finger) st = TC_E_MISMATCH;
@@ -117,6 +117,8 @@ __global__ void k_ctl_check(uint32_t *__restrict__ ctl, uint32_t finger) {
     ctl[kCtlQueueA] = 0;
     ctl[kCtlQueueB] = 0;
     ctl[kCtlQueueC] = 0;
+    *total = 0ull;
+    if (d_status) *d_status = st;
 }
 
 constexpr uint32_t kPartTileEdges = 4096;  // edges per tile of the degree partition
@@ -269,7 +271,6 @@ static bool make_layout(int64_t n, int64_t m, uint32_t flags, const tc_options *
     L.sort_scratch = take(sort_scratch_bytes(L.kcap));  // edge, vertex and in-edge sorts
     L.rs = take(n1 * 4);
     L.re = take(n1 * 4);
-    L.rowlen = take(n1 * 4);
     L.row_ptr = take(n1 * 4);
     L.col = take((size_t)L.mf * 4 + count_col_pad_bytes());  // piece reads may pass the end
     L.hcol = take((size_t)L.hcap * 2);
@@ -279,12 +280,10 @@ static bool make_layout(int64_t n, int64_t m, uint32_t flags, const tc_options *
     // rows sorted in place after a sort by source only: chunk table and the long rows' list
     L.rchunk = take(((size_t)L.mf / row_sort_chunk() + 2) * 4);
     L.long_rows = take(((size_t)L.mf / (row_sort_wave() + 1) + 2) * 4);
-    L.vrange = take((size_t)n * 8);
     L.prange = take((size_t)L.panels * 8);
     L.eu = take((size_t)L.mf * 16);  // also the cell-ordered edges (8 bytes per entry)
     L.lrs = take(l1 * 4);
     L.lre = take(l1 * 4);
-    L.cnt = take(l1 * 4);
     L.cptr = take(l1 * 4);
     L.cbeg = take((size_t)L.mf * 4);
     for (int k = 0; k < 4; ++k) {
@@ -372,19 +371,43 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     uint32_t *scan_scr = at<uint32_t>(ws, L.scan_scratch);
     // cell-ordered edges for the orientation: the in-edge payload buffer, unused until later
     int2 *cells = L.cell_shift >= 0 ? at<int2>(ws, L.eu) : nullptr;
-    hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, s, ctl, L.finger);
+    uint32_t *ph = at<uint32_t>(ws, L.part_hist), *po = at<uint32_t>(ws, L.part_offs);
+    const uint64_t hp = (L.cell_shift >= 0 ? 512ull : 256ull) * L.part_tiles;
+    hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, s, ctl, L.finger,
+                       m > 0 && L.part_tiles ? ph + hp : nullptr);
     TC_LAUNCH_CHECK();
     const bool onesweep = L.opt.sort_onesweep != 0;
     const bool row_sort = L.opt.row_sort && L.mf < kRowSortMaxEdges;
-    TC_HIP(fill_u32(deg, 0u, n, s));
+    const uint64_t l1 = L.lists + 1;
+    uint32_t *rs = at<uint32_t>(ws, L.rs), *re = at<uint32_t>(ws, L.re);
+    uint32_t *hrow = at<uint32_t>(ws, L.hrow);
+    uint32_t *lrs = at<uint32_t>(ws, L.lrs), *lre = at<uint32_t>(ws, L.lre);
+    uint16_t *hcol = at<uint16_t>(ws, L.hcol);
+    // everything that later kernels add to or mark, cleared by one launch
+    {
+        FillList f;
+        f.add(deg, 0u, n);
+        if (mf == 0) {
+            f.add(row_ptr, 0u, n1);
+        } else {
+            f.add(rs, 0u, n1);
+            f.add(re, 0u, n1);
+            f.add(hrow, ~0u, n);
+            f.add((uint32_t *)hcol, 0u, L.hcap / 2);  // zeros, the parts' padding
+            f.add(lrs, 0u, l1);
+            f.add(lre, 0u, l1);
+            if (L.hp) {
+                f.add((uint32_t *)at<uint8_t>(ws, L.hub_a), 0u, (uint64_t)L.hp * L.hp / 4);
+                f.add((uint32_t *)at<uint8_t>(ws, L.hub_at), 0u, (uint64_t)L.hp * L.hp / 4);
+            }
+        }
+        TC_HIP(fill_all(f, s));
+    }
     if (m > 0 && L.part_tiles) {
         const uint32_t tiles = L.part_tiles;
-        const uint64_t hp = (L.cell_shift >= 0 ? 512ull : 256ull) * tiles;
-        uint32_t *ph = at<uint32_t>(ws, L.part_hist), *po = at<uint32_t>(ws, L.part_offs);
         // the endpoints' offsets inside their buckets, 2 bytes each when a bucket holds at most
         // 2^16 ids, else 4 (either fits the 8-byte key buffer)
         const bool narrow = L.part_shift <= 16;
-        TC_HIP(fill_u32(ph + hp, 0u, 1, s));
         hipLaunchKernelGGL(k_part_hist, dim3(tiles), dim3(256), 0, s, edges, (uint64_t)m, n,
                            (uint32_t)both, L.part_shift, L.cell_shift, ph, tiles, status);
         TC_LAUNCH_CHECK();
@@ -438,17 +461,8 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
         else
             TC_HIP(sort_u64(ka, kb, mf, 0, 2 * b, sort_scr, status, s, &sorted, onesweep));
     }
-    if (mf == 0) {
-        TC_HIP(fill_u32(row_ptr, 0u, n1, s));
-        return TC_OK;
-    }
+    if (mf == 0) return TC_OK;
     // node array: row boundaries -> row lengths -> exclusive scan
-    uint32_t *rs = at<uint32_t>(ws, L.rs), *re = at<uint32_t>(ws, L.re);
-    uint32_t *rowlen = at<uint32_t>(ws, L.rowlen);
-    TC_HIP(fill_u32(rs, 0u, n1, s));
-    TC_HIP(fill_u32(re, 0u, n1, s));
-    uint32_t *hrow = at<uint32_t>(ws, L.hrow);
-    TC_HIP(fill_u32(hrow, ~0u, n, s));
     uint32_t *rchunk = at<uint32_t>(ws, L.rchunk);
     // 4 entries per thread (prep.hip, kCsrKeys)
     if (row_sort)
@@ -458,51 +472,38 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
         hipLaunchKernelGGL(k_csr, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, sorted, mf, n,
                            b, L.hbase, col, src, rs, re, hrow, status);
     TC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_rowlen, dim3(grid_for(n1, 256)), dim3(256), 0, s, rs, re, n, rowlen);
-    TC_LAUNCH_CHECK();
-    TC_HIP(scan_exclusive_u32(rowlen, row_ptr, n1, scan_scr, s));
+    TC_HIP(scan_row_bounds(rs, re, n, row_ptr, scan_scr, s));
     if (row_sort) {  // every row sorted in place, with the duplicate check and hrow
         const uint32_t chunks = ceil_div(mf, row_sort_chunk());
         uint32_t *long_rows = at<uint32_t>(ws, L.long_rows);
+        // a simple graph's rows hold fewer than sqrt(2 mf) entries
+        const bool any_long = 2 * (uint64_t)mf > (uint64_t)row_sort_wave() * row_sort_wave();
         hipLaunchKernelGGL(k_row_sort, dim3(chunks), dim3(256), 0, s, col, row_ptr, rchunk,
-                           chunks, n, L.hbase, hrow, long_rows, ctl + kCtlLongRows, status);
+                           chunks, n, L.hbase, hrow, long_rows,
+                           any_long ? ctl + kCtlLongRows : nullptr, status);
         TC_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_row_sort_long, dim3(device_cu_count()), dim3(1024), 0, s, col,
-                           row_ptr, long_rows, ctl + kCtlLongRows, L.hbase, hrow, status);
-        TC_LAUNCH_CHECK();
+        if (any_long) {
+            hipLaunchKernelGGL(k_row_sort_long, dim3(device_cu_count()), dim3(1024), 0, s, col,
+                               row_ptr, long_rows, ctl + kCtlLongRows, L.hbase, hrow, status);
+            TC_LAUNCH_CHECK();
+        }
     }
-    // every row's part of hcol (row lengths are no longer needed: their array takes the parts'
-    // sizes); hcol starts as zeros, the parts' padding
+    // every row's part of hcol
     uint32_t *hstart = at<uint32_t>(ws, L.hstart);
-    uint16_t *hcol = at<uint16_t>(ws, L.hcol);
-    hipLaunchKernelGGL(k_hlen, dim3(grid_for(n1, 256)), dim3(256), 0, s, row_ptr, hrow, n,
-                       count_hcol_pad(), rowlen);
-    TC_LAUNCH_CHECK();
-    TC_HIP(scan_exclusive_u32(rowlen, hstart, n1, scan_scr, s));
-    TC_HIP(fill_u32((uint32_t *)hcol, 0u, L.hcap / 2, s));
+    TC_HIP(scan_high_rows(row_ptr, hrow, n, count_hcol_pad(), hstart, scan_scr, s));
     // the hub matrices
     if (L.hp) {
         uint8_t *ha = at<uint8_t>(ws, L.hub_a), *hat = at<uint8_t>(ws, L.hub_at);
-        TC_HIP(fill_u32((uint32_t *)ha, 0u, (uint64_t)L.hp * L.hp / 4, s));
-        TC_HIP(fill_u32((uint32_t *)hat, 0u, (uint64_t)L.hp * L.hp / 4, s));
         TC_HIP(launch_hub_fill(src, col, row_ptr, mf, L.h0, L.hp, ha, hat, status, s));
     }
     // in-edge lists (grouped by list c = row block * (n + 1) + v) and the counting kernel's
     // work items
-    const uint64_t l1 = L.lists + 1;
-    uint32_t *lrs = at<uint32_t>(ws, L.lrs), *lre = at<uint32_t>(ws, L.lre);
-    uint32_t *cnt = at<uint32_t>(ws, L.cnt), *cptr = at<uint32_t>(ws, L.cptr);
-    uint64_t *vr = at<uint64_t>(ws, L.vrange);
-    uint32_t *items[4], *offs[4], *iv[4];
+    uint32_t *cptr = at<uint32_t>(ws, L.cptr);
+    ItemLists q;
     for (int k = 0; k < 4; ++k) {
-        items[k] = at<uint32_t>(ws, L.items[k]);
-        offs[k] = at<uint32_t>(ws, L.off[k]);
-        iv[k] = at<uint32_t>(ws, L.item_v[k]);
-    }
-    if (L.panels) {  // spans of the panel region's out-lists
-        hipLaunchKernelGGL(k_vrange, dim3(grid_for(n - L.p0, 256)), dim3(256), 0, s, row_ptr, col,
-                           L.p0, n, vr);
-        TC_LAUNCH_CHECK();
+        q.items[k] = at<uint32_t>(ws, L.items[k]);
+        q.off[k] = at<uint32_t>(ws, L.off[k]);
+        q.list[k] = at<uint32_t>(ws, L.item_v[k]);
     }
     // the in-edge keys: 32-bit list ids in the buffer of the sorted edge keys (no longer
     // needed), sorted into 64-bit (list, position) keys in the other buffer
@@ -512,8 +513,8 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     uint4 *eu = at<uint4>(ws, L.eu);
     uint64_t *pr = at<uint64_t>(ws, L.prange);
     if (L.panels) {
-        hipLaunchKernelGGL(k_panel_range, dim3(grid_for(L.panels, 256)), dim3(256), 0, s, vr, n,
-                           L.p0, count_panel(), L.panels, pr);
+        hipLaunchKernelGGL(k_panel_range, dim3(grid_for(32ull * L.panels, 256)), dim3(256), 0, s,
+                           row_ptr, col, n, L.p0, L.panels, pr);
         TC_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(k_csc_keys, dim3(grid_for(mf, 256 * kCscPerThread)), dim3(256), 0, s, col,
@@ -525,47 +526,37 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     uint32_t *clist = nullptr;
     TC_HIP(sort_lists(cid, (uint32_t)L.lists, mf, id_bits_for64(l1), ck, ck2,
                       at<uint32_t>(ws, L.cbeg), ctl + kCtlKept, sort_scr, status, s, &clist));
-    TC_HIP(fill_u32(lrs, 0u, l1, s));
-    TC_HIP(fill_u32(lre, 0u, l1, s));
     hipLaunchKernelGGL(k_csc_final, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, clist, mf,
                        ctl + kCtlKept, L.lists, lrs, lre,
                        status);  // 4 ids per thread (prep.hip, kCscFinalKeys)
     TC_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_rowlen, dim3(grid_for(l1, 256)), dim3(256), 0, s, lrs, lre,
-                       (uint32_t)L.lists, cnt);
-    TC_LAUNCH_CHECK();
-    TC_HIP(scan_exclusive_u32(cnt, cptr, l1, scan_scr, s));
+    TC_HIP(scan_row_bounds(lrs, lre, L.lists, cptr, scan_scr, s));
     const tc_options &o = L.opt;
     const uint32_t wl_pv = o.wave_list_max < count_wave_list(true) ? o.wave_list_max
                                                                      : count_wave_list(true);
-    hipLaunchKernelGGL(k_items, dim3(grid_for(l1, 256)), dim3(256), 0, s, row_ptr, col, cnt, n,
-                       L.nblk, L.p0, o.wave_bitmap_span, o.wave_list_max, wl_pv,
-                       o.wave_item_edges, o.block_item_edges, items[0], items[1], items[2],
-                       items[3], status);
+    hipLaunchKernelGGL(k_items, dim3(grid_for(l1, 256)), dim3(256), 0, s, row_ptr, col, lrs, lre,
+                       n, L.nblk, L.p0, o.wave_bitmap_span, o.wave_list_max, wl_pv,
+                       o.wave_item_edges, o.block_item_edges, q.items[0], q.items[1], q.items[2],
+                       q.items[3], status);
     TC_LAUNCH_CHECK();
-    for (int k = 0; k < 4; ++k) TC_HIP(scan_exclusive_u32(items[k], offs[k], l1, scan_scr, s));
-    for (int k = 0; k < 4; ++k) {
-        hipLaunchKernelGGL(k_item_fill, dim3(grid_for(L.lists, 256)), dim3(256), 0, s, items[k],
-                           offs[k], L.lists, iv[k], status);
-        TC_LAUNCH_CHECK();
-    }
+    TC_HIP(scan_four_u32(q.items, q.off, l1, scan_scr, s));
+    hipLaunchKernelGGL(k_item_fill, dim3(grid_for(L.lists, 256), 4), dim3(256), 0, s, q, L.lists,
+                       status);
+    TC_LAUNCH_CHECK();
     return TC_OK;
 }
 
 // Counting phase on a prepared workspace.
 static int run_count_prepared(void *ws, const Layout &L, hipStream_t s, uint64_t *d_total,
-                              uint64_t *d_pv) {
+                              uint64_t *d_pv, int32_t *d_status) {
     const bool pv = d_pv != nullptr;
     const uint32_t n = L.n;
     uint32_t *ctl = at<uint32_t>(ws, L.ctl);
-    // this count's status: the preprocessing's, or a mismatch of the prepared layout (the
-    // check also resets the item queues)
+    // this count's status: the preprocessing's, or a mismatch of the prepared layout
     int32_t *status = (int32_t *)ctl + kCtlRun;
-    hipLaunchKernelGGL(k_ctl_check, dim3(1), dim3(64), 0, s, ctl, L.finger);
-    TC_LAUNCH_CHECK();
     unsigned long long *total = (unsigned long long *)d_total;
     unsigned long long *tpv = at<unsigned long long>(ws, L.tpv);
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, total, (uint64_t)1);
+    hipLaunchKernelGGL(k_count_begin, dim3(1), dim3(64), 0, s, ctl, L.finger, total, d_status);
     TC_LAUNCH_CHECK();
     if (pv && n > 0) {
         hipLaunchKernelGGL(k_zero_u64, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, tpv,
@@ -616,11 +607,10 @@ static int run_count_prepared(void *ws, const Layout &L, hipStream_t s, uint64_t
     return TC_OK;
 }
 
-static int copy_status(void *ws, const Layout &L, int32_t *d_status, hipStream_t s,
-                       int word) {
+static int copy_status(void *ws, const Layout &L, int32_t *d_status, hipStream_t s) {
     if (!d_status) return TC_OK;
-    hipLaunchKernelGGL(k_copy_status, dim3(1), dim3(64), 0, s, at<int32_t>(ws, L.ctl) + word,
-                       d_status);
+    hipLaunchKernelGGL(k_copy_status, dim3(1), dim3(64), 0, s,
+                       at<int32_t>(ws, L.ctl) + kCtlStatus, d_status);
     TC_LAUNCH_CHECK();
     return TC_OK;
 }
@@ -635,9 +625,7 @@ static int run_count(const int32_t *d_edges, int64_t n, int64_t m, uint32_t flag
     if (!d_total) return TC_E_ARG;
     st = run_preprocess(d_edges, flags, ws, L, s);
     if (st) return st;
-    st = run_count_prepared(ws, L, s, d_total, L.n > 0 ? d_pv : nullptr);
-    if (st) return st;
-    return copy_status(ws, L, d_status, s, kCtlRun);
+    return run_count_prepared(ws, L, s, d_total, L.n > 0 ? d_pv : nullptr, d_status);
 }
 
 // ------------------------------------------------------------------ static scratch
@@ -744,7 +732,7 @@ int tc_preprocess(const int32_t *d_edges, int64_t n, int64_t m, uint32_t flags,
     if (st) return st;
     st = run_preprocess(d_edges, flags, d_ws, L, (hipStream_t)stream);
     if (st) return st;
-    return copy_status(d_ws, L, d_status, (hipStream_t)stream, kCtlStatus);
+    return copy_status(d_ws, L, d_status, (hipStream_t)stream);
 }
 
 int tc_count_noalloc(const int32_t *d_edges, int64_t n, int64_t m, uint32_t flags,
@@ -769,10 +757,8 @@ int tc_count_prepared(int64_t n, int64_t m, uint32_t flags, const tc_options *op
     if (n >= (1ll << 31) || m >= (1ll << 32)) return TC_E_TOO_LARGE;
     if (!make_layout(n, m, flags, opts, L) || !d_total) return TC_E_ARG;
     if (!d_ws || ((uintptr_t)d_ws & 255) || ws_bytes < L.total_bytes) return TC_E_WORKSPACE;
-    int st = run_count_prepared(d_ws, L, (hipStream_t)stream, d_total,
-                                L.n > 0 ? d_per_vertex : nullptr);
-    if (st) return st;
-    return copy_status(d_ws, L, d_status, (hipStream_t)stream, kCtlRun);
+    return run_count_prepared(d_ws, L, (hipStream_t)stream, d_total,
+                              L.n > 0 ? d_per_vertex : nullptr, d_status);
 }
 
 size_t tc_sort_workspace_size(int64_t count) {

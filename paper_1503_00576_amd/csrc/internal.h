@@ -136,8 +136,16 @@ __device__ __forceinline__ uint32_t xcd_stretch_tile(uint32_t b, uint32_t nb) {
     return b - i + (i % kXcds) * kXcdStretch + i / kXcds;
 }
 
-// exclusive scan of uint32 (in may equal out); scratch: scan_scratch_words(N) words
+// exclusive scans of uint32; scratch: scan_scratch_words(N) words.  Of an array (in may equal
+// out), of four at once, of row lengths from the rows' bounds, of the rows' room in hcol (the
+// last two also write out[rows], the total)
 size_t scan_scratch_words(uint64_t N);
+hipError_t scan_four_u32(uint32_t *const in[4], uint32_t *const out[4], uint64_t N,
+                         uint32_t *scratch, hipStream_t s);
+hipError_t scan_row_bounds(const uint32_t *rs, const uint32_t *re, uint64_t rows, uint32_t *out,
+                           uint32_t *scratch, hipStream_t s);
+hipError_t scan_high_rows(const uint32_t *row_ptr, const uint32_t *hrow, uint64_t rows,
+                          uint32_t pad, uint32_t *out, uint32_t *scratch, hipStream_t s);
 hipError_t scan_exclusive_u32(const uint32_t *in, uint32_t *out, uint64_t N, uint32_t *scratch,
                               hipStream_t s);
 
@@ -167,9 +175,29 @@ hipError_t sort_lists(const uint32_t *cid, uint32_t drop, uint32_t count, int bi
                       uint64_t *a, uint64_t *b, uint32_t *cbeg, uint32_t *kept, void *scratch,
                       int32_t *status, hipStream_t s, uint32_t **list);
 
+// arrays filled by one launch (16-byte aligned)
+struct Fill {
+    uint32_t *p;
+    uint64_t words;
+    uint32_t value;
+};
+struct FillList {
+    Fill a[10];
+    int count = 0;
+    void add(uint32_t *p, uint32_t value, uint64_t words) {
+        if (words) a[count++] = Fill{p, words, value};
+    }
+};
+hipError_t fill_all(const FillList &f, hipStream_t s);
 hipError_t fill_u32(uint32_t *p, uint32_t value, uint64_t count, hipStream_t s);
 
 int device_cu_count();
+
+// the work items' four queues: wave / workgroup items of totals, then of per-vertex counts; list c
+// has items[k][c] items, the first at list[k][off[k][c]]
+struct ItemLists {
+    uint32_t *items[4], *off[4], *list[4];
+};
 
 // counting kernels (count.hip)
 struct CountArgs {

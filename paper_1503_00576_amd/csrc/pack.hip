@@ -14,8 +14,6 @@
 
 namespace tc {
 
-__global__ void k_rowlen(const uint32_t *, const uint32_t *, uint32_t, uint32_t *);  // prep.hip
-
 constexpr uint32_t kPackThreads = 256;
 
 // last g in [0, G) with off[g] <= x (off non-decreasing on valid input; any input gives a g
@@ -33,18 +31,36 @@ __device__ __forceinline__ uint32_t last_le(const int64_t *__restrict__ off, uin
 
 // The offsets must be prefix sums over the batch (non-decreasing, from 0 to N and to M);
 // otherwise graph ranges may overlap, so any violation marks every graph of the batch.
-// Pass 1 clears the statuses and raises *bad on a violation; pass 2 marks the graphs.
+__device__ __forceinline__ bool pk_graph_ok(const int64_t *__restrict__ vtx_off,
+                                            const int64_t *__restrict__ edge_off, uint32_t G,
+                                            uint64_t N, uint64_t M, uint32_t g) {
+    const int64_t v0 = vtx_off[g], v1 = vtx_off[g + 1], e0 = edge_off[g], e1 = edge_off[g + 1];
+    return v0 >= 0 && v1 >= v0 && (uint64_t)v1 <= N && e0 >= 0 && e1 >= e0 && (uint64_t)e1 <= M &&
+           (g > 0 || (v0 == 0 && e0 == 0)) && (g + 1 < G || ((uint64_t)v1 == N && (uint64_t)e1 == M));
+}
+
+// Up to kPackOneWg graphs: one workgroup checks them and writes the statuses (a launch of its
+// own costs more than four graphs per thread).  More: a first launch clears the statuses and
+// raises *bad (cleared beforehand) on a violation, a second one marks the graphs.
+constexpr uint32_t kPackOneWg = 4096;
+__global__ __launch_bounds__(1024) void k_pk_graphs_one(const int64_t *__restrict__ vtx_off,
+                                                        const int64_t *__restrict__ edge_off,
+                                                        uint32_t G, uint64_t N, uint64_t M,
+                                                        int32_t *__restrict__ status) {
+    bool ok = true;
+    for (uint32_t g = threadIdx.x; g < G; g += blockDim.x)
+        ok &= pk_graph_ok(vtx_off, edge_off, G, N, M, g);
+    const int32_t st = __syncthreads_and(ok) ? 0 : TC_E_ARG;
+    for (uint32_t g = threadIdx.x; g < G; g += blockDim.x) status[g] = st;
+}
+
 __global__ void k_pk_graphs(const int64_t *__restrict__ vtx_off,
                             const int64_t *__restrict__ edge_off, uint32_t G, uint64_t N,
                             uint64_t M, int32_t *__restrict__ status, uint32_t *__restrict__ bad) {
     const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= G) return;
-    const int64_t v0 = vtx_off[g], v1 = vtx_off[g + 1], e0 = edge_off[g], e1 = edge_off[g + 1];
-    const bool ok = v0 >= 0 && v1 >= v0 && (uint64_t)v1 <= N && e0 >= 0 && e1 >= e0 &&
-                    (uint64_t)e1 <= M && (g > 0 || (v0 == 0 && e0 == 0)) &&
-                    (g + 1 < G || ((uint64_t)v1 == N && (uint64_t)e1 == M));
     status[g] = 0;
-    if (!ok) atomicOr(bad, 1u);
+    if (!pk_graph_ok(vtx_off, edge_off, G, N, M, g)) atomicOr(bad, 1u);
 }
 
 __global__ void k_pk_mark(uint32_t G, const uint32_t *__restrict__ bad,
@@ -126,7 +142,7 @@ __global__ void k_pk_offsets(const uint32_t *__restrict__ grp,
 }
 
 struct PackLayout {
-    size_t ctl, keys_a, keys_b, sort_scratch, rs, re, rowlen, grp, scan, total;
+    size_t ctl, keys_a, keys_b, sort_scratch, rs, re, grp, scan, total;
 };
 
 static PackLayout pack_layout(uint64_t N, uint64_t M) {
@@ -144,7 +160,6 @@ static PackLayout pack_layout(uint64_t N, uint64_t M) {
     L.sort_scratch = take(sort_scratch_bytes(K));
     L.rs = take(n1 * 4);
     L.re = take(n1 * 4);
-    L.rowlen = take(n1 * 4);
     L.grp = take(n1 * 4);
     L.scan = take(scan_scratch_words(n1) * 4);
     L.total = off;
@@ -183,7 +198,7 @@ int tc_batched_pack(int32_t G, const int64_t *d_vtx_off, const int64_t *d_edge_o
     char *ws = (char *)d_ws;
     uint64_t *ka = (uint64_t *)(ws + L.keys_a), *kb = (uint64_t *)(ws + L.keys_b);
     uint32_t *rs = (uint32_t *)(ws + L.rs), *re = (uint32_t *)(ws + L.re);
-    uint32_t *rowlen = (uint32_t *)(ws + L.rowlen), *grp = (uint32_t *)(ws + L.grp);
+    uint32_t *grp = (uint32_t *)(ws + L.grp);
     int b = 1;  // bits of a union row id below the sentinel: 2^b - 1 >= N
     while (b < 31 && (1ull << b) - 1 < N) ++b;
     const uint32_t T = kPackThreads;
@@ -193,14 +208,21 @@ int tc_batched_pack(int32_t G, const int64_t *d_vtx_off, const int64_t *d_edge_o
         return (uint32_t)(g < cap ? g : cap);
     };
     uint32_t *bad = (uint32_t *)(ws + L.ctl);
-    if (fill_u32(bad, 0u, 1, s) != hipSuccess) return TC_E_HIP;
-    hipLaunchKernelGGL(k_pk_graphs, dim3(blocks(G, T, 1u << 30)), dim3(T), 0, s, d_vtx_off,
-                       d_edge_off, (uint32_t)G, N, M, d_status, bad);
-    hipLaunchKernelGGL(k_pk_mark, dim3(blocks(G, T, 1u << 30)), dim3(T), 0, s, (uint32_t)G,
-                       bad, d_status);
+    FillList f;
+    f.add(rs, 0u, N + 1);
+    f.add(re, 0u, N + 1);
+    f.add(bad, 0u, 1);
+    if (fill_all(f, s) != hipSuccess) return TC_E_HIP;
+    if ((uint32_t)G <= kPackOneWg) {
+        hipLaunchKernelGGL(k_pk_graphs_one, dim3(1), dim3(1024), 0, s, d_vtx_off, d_edge_off,
+                           (uint32_t)G, N, M, d_status);
+    } else {
+        hipLaunchKernelGGL(k_pk_graphs, dim3(blocks(G, T, 1u << 30)), dim3(T), 0, s, d_vtx_off,
+                           d_edge_off, (uint32_t)G, N, M, d_status, bad);
+        hipLaunchKernelGGL(k_pk_mark, dim3(blocks(G, T, 1u << 30)), dim3(T), 0, s, (uint32_t)G,
+                           bad, d_status);
+    }
     if (hipGetLastError() != hipSuccess) return TC_E_HIP;
-    if (fill_u32(rs, 0u, N + 1, s) != hipSuccess || fill_u32(re, 0u, N + 1, s) != hipSuccess)
-        return TC_E_HIP;
     uint64_t *sorted = ka;
     if (M > 0) {
         hipLaunchKernelGGL(k_pk_keys, dim3(blocks(M, T, 65536)), dim3(T), 0, s,
@@ -214,11 +236,8 @@ int tc_batched_pack(int32_t G, const int64_t *d_vtx_off, const int64_t *d_edge_o
                            (uint32_t)K, N, b, d_col, rs, re);
         if (hipGetLastError() != hipSuccess) return TC_E_HIP;
     }
-    // row lengths (entry N is 0) and their exclusive scan: grp[N] = valid entries
-    hipLaunchKernelGGL(k_rowlen, dim3(blocks(N + 1, T, 1u << 30)), dim3(T), 0, s, rs, re,
-                       (uint32_t)N, rowlen);
-    if (hipGetLastError() != hipSuccess) return TC_E_HIP;
-    if (scan_exclusive_u32(rowlen, grp, N + 1, (uint32_t *)(ws + L.scan), s) != hipSuccess)
+    // row lengths and their exclusive scan: grp[N] = valid entries
+    if (scan_row_bounds(rs, re, N, grp, (uint32_t *)(ws + L.scan), s) != hipSuccess)
         return TC_E_HIP;
     const uint64_t work = N > (uint64_t)G + 1 ? N : (uint64_t)G + 1;
     hipLaunchKernelGGL(k_pk_offsets, dim3(blocks(work, T, 1u << 30)), dim3(T), 0, s, grp,

@@ -605,7 +605,8 @@ __device__ __forceinline__ void sort_row_class(uint32_t *__restrict__ col,
 // Rows starting in chunk c (rows rchunk[c] .. rchunk[c + 1] - 1), listed in LDS by class:
 // the non-empty rows of at most kRowWave entries by G = the smallest power of two with
 // G kRowLane >= length (C = log2 G), each class sorted by groups of G lanes; longer rows go
-// to the list for k_row_sort_long.  At most kRowChunk non-empty rows start in a chunk.
+// to the list for k_row_sort_long (n_long null: a graph whose rows cannot be longer without
+// repeated edges, reported as such).  At most kRowChunk non-empty rows start in a chunk.
 __device__ __forceinline__ uint32_t row_class(uint32_t len) {  // len >= 1
     if (len > kRowWave) return kRowClasses;
     return len <= kRowLane ? 0u : 32u - (uint32_t)__builtin_clz(len - 1) - 4u;
@@ -632,7 +633,8 @@ __global__ __launch_bounds__(256) void k_row_sort(uint32_t *__restrict__ col,
         if (len == 0) continue;
         const uint32_t cls = row_class(len);
         if (cls < kRowClasses) atomicAdd(&ccount[cls], 1u);
-        else long_rows[atomicAdd(n_long, 1u)] = r;
+        else if (n_long) long_rows[atomicAdd(n_long, 1u)] = r;
+        else set_status(status, TC_E_DUP_EDGE);
     }
     __syncthreads();
     if (t == 0) {
@@ -722,55 +724,27 @@ __global__ __launch_bounds__(1024) void k_row_sort_long(uint32_t *__restrict__ c
 uint32_t row_sort_chunk() { return kRowChunk; }
 uint32_t row_sort_wave() { return kRowWave; }
 
-// row length = end - start (both zero for empty rows); entry n is 0 so that the exclusive
-// scan over n + 1 entries ends with row_ptr[n] = m_fwd
-__global__ void k_rowlen(const uint32_t *__restrict__ rs, const uint32_t *__restrict__ re,
-                         uint32_t n, uint32_t *__restrict__ len) {
-    uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r > n) return;
-    len[r] = r < n ? re[r] - rs[r] : 0u;
-}
-
-// Room of every row's entries >= hbase in hcol: none for a row without such entries, else
-// their number rounded up to a multiple of 8, plus `pad` zeros (the counting kernel's pieces,
-// read from 8-aligned positions inside the row's part, never leave it).  Entry n is 0, so that
-// the exclusive scan ends with the total.
-__global__ void k_hlen(const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ hrow,
-                       uint32_t n, uint32_t pad, uint32_t *__restrict__ hlen) {
-    const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r > n) return;
-    uint32_t len = 0;
-    if (r < n && hrow[r] != ~0u) len = ((row_ptr[r + 1] - hrow[r] + 7u) & ~7u) + pad;
-    hlen[r] = len;
-}
-
-// Rank span of every out-list from rank v0 on (the panel region, whose spans k_panel_range
-// combines): (min << 32) | max, or 0xFFFFFFFF00000000 (min > max) if empty.
-__global__ void k_vrange(const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ col,
-                         uint32_t v0, uint32_t n, uint64_t *__restrict__ vr) {
-    uint32_t v = v0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    const uint32_t r0 = row_ptr[v], r1 = row_ptr[v + 1];
-    vr[v] = r1 > r0 ? ((uint64_t)col[r0] << 32) | col[r1 - 1] : 0xFFFFFFFF00000000ull;
-}
-
-// Rank span of the union of the out-lists of every panel (ranks p0 + i * kp .. + kp - 1), in
-// the format of k_vrange.
-__global__ void k_panel_range(const uint64_t *__restrict__ vr, uint32_t n, uint32_t p0,
-                              uint32_t kp, uint32_t panels, uint64_t *__restrict__ pr) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= panels) return;
-    const uint32_t P = p0 + i * kp, pe = min(P + kp, n);
+// Rank span of the union of the out-lists of every panel (ranks p0 + i * 32 .. + 31):
+// (min << 32) | max, or 0xFFFFFFFF00000000 (min > max) if all are empty.  32 lanes per panel.
+__global__ __launch_bounds__(256) void k_panel_range(const uint32_t *__restrict__ row_ptr,
+                                                     const uint32_t *__restrict__ col, uint32_t n,
+                                                     uint32_t p0, uint32_t panels,
+                                                     uint64_t *__restrict__ pr) {
+    const uint32_t i = (blockIdx.x * 256u + threadIdx.x) / 32u, j = threadIdx.x % 32u;
+    const uint32_t v = p0 + i * 32u + j;
     uint32_t lo = 0xFFFFFFFFu, hi = 0;
-    for (uint32_t v = P; v < pe; ++v) {
-        const uint64_t r = vr[v];
-        const uint32_t l = (uint32_t)(r >> 32), h = (uint32_t)r;
-        if (l <= h) {
-            lo = min(lo, l);
-            hi = max(hi, h);
+    if (i < panels && v < n) {
+        const uint32_t r0 = row_ptr[v], r1 = row_ptr[v + 1];
+        if (r1 > r0) {
+            lo = col[r0];
+            hi = col[r1 - 1];
         }
     }
-    pr[i] = ((uint64_t)lo << 32) | hi;
+    for (int o = 16; o; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, kWave));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, kWave));
+    }
+    if (i < panels && j == 0) pr[i] = ((uint64_t)lo << 32) | hi;
 }
 
 // In-edge u -> v (CSR position e) can close a triangle u < v < w only through an element w of
@@ -788,7 +762,7 @@ __global__ void k_panel_range(const uint64_t *__restrict__ vr, uint32_t n, uint3
 // entry or, for any other kept entry, the col position where the suffix's entries >= hbase
 // start, the hcol position where they start, u).  In-edges from hubs (u >= h0) are left out:
 // their triangles are counted on the matrix cores.  Every entry >= hbase is also written to
-// its row's part of hcol (hrow and hstart: k_csr, k_hlen and a scan).
+// its row's part of hcol (hrow and hstart: the row sort or k_csr, and a scan).
 // Each thread takes kCscEdges entries a block apart and issues every stage's loads for all of
 // them before using any (the stages depend on each other: entry -> row -> row end).
 constexpr uint32_t kCscEdges = 4;
@@ -919,7 +893,8 @@ __global__ void k_csc_final(const uint32_t *__restrict__ list, uint32_t mf,
 // graph can be counted either way.  Panel lists (first rank >= p0) always go to the
 // per-workgroup queue.
 __global__ void k_items(const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ col,
-                        const uint32_t *__restrict__ cnt, uint32_t n, uint32_t nblk, uint32_t p0,
+                        const uint32_t *__restrict__ lrs, const uint32_t *__restrict__ lre,
+                        uint32_t n, uint32_t nblk, uint32_t p0,
                         uint32_t wave_span, uint32_t wave_list, uint32_t wave_list_pv,
                         uint32_t ka, uint32_t kb,
                         uint32_t *__restrict__ ia, uint32_t *__restrict__ ib,
@@ -931,12 +906,13 @@ __global__ void k_items(const uint32_t *__restrict__ row_ptr, const uint32_t *__
     if (c > total) return;
     uint32_t a = 0, b = 0, apv = 0, bpv = 0;
     const uint32_t v = c < total ? (uint32_t)(c % (n + 1)) : n;
-    if (v < n && cnt[c] > 0 && v >= p0) {
-        b = bpv = (cnt[c] + kb - 1) / kb;
-    } else if (v < n && cnt[c] > 0 && row_ptr[v + 1] > row_ptr[v]) {  // N+(v) non-empty
+    const uint32_t cnt = v < n ? lre[c] - lrs[c] : 0u;  // in-edges
+    if (cnt > 0 && v >= p0) {
+        b = bpv = (cnt + kb - 1) / kb;
+    } else if (cnt > 0 && row_ptr[v + 1] > row_ptr[v]) {  // N+(v) non-empty
         const uint32_t r0 = row_ptr[v], d = row_ptr[v + 1] - r0;
         const uint32_t span = col[r0 + d - 1] - col[r0];
-        const uint32_t na = (cnt[c] + ka - 1) / ka, nb = (cnt[c] + kb - 1) / kb;
+        const uint32_t na = (cnt + ka - 1) / ka, nb = (cnt + kb - 1) / kb;
         if (span < wave_span || d <= wave_list) a = na; else b = nb;
         if (d <= wave_list_pv) apv = na; else bpv = nb;
     }
@@ -946,14 +922,13 @@ __global__ void k_items(const uint32_t *__restrict__ row_ptr, const uint32_t *__
     ib_pv[c] = bpv;
 }
 
-__global__ void k_item_fill(const uint32_t *__restrict__ items, const uint32_t *__restrict__ off,
-                            uint64_t total, uint32_t *__restrict__ item_c,
-                            const int32_t *__restrict__ status) {
+// the item lists of the four queues (blockIdx.y) from their items' counts and offsets
+__global__ void k_item_fill(const ItemLists q, uint64_t total, const int32_t *__restrict__ status) {
     if (*status) return;
-    uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= total) return;
-    uint32_t k = items[c], o = off[c];
-    for (uint32_t j = 0; j < k; ++j) item_c[o + j] = (uint32_t)c;
+    const uint32_t k = q.items[blockIdx.y][c], o = q.off[blockIdx.y][c];
+    for (uint32_t j = 0; j < k; ++j) q.list[blockIdx.y][o + j] = (uint32_t)c;
 }
 
 // per-vertex counts back from rank space to vertex ids

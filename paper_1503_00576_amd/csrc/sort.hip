@@ -21,18 +21,31 @@ namespace tc {
 
 // ======================================================================= fill
 
-__global__ void k_fill_u32(uint32_t *__restrict__ p, uint32_t value, uint64_t count) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (; i < count; i += stride) p[i] = value;
+// Several arrays cleared by one launch: blockIdx.y picks the array (16-byte aligned), its blocks
+// stride over it.
+__global__ __launch_bounds__(256) void k_fill(const FillList f) {
+    const Fill a = f.a[blockIdx.y];
+    const uint64_t stride = (uint64_t)gridDim.x * 256, quads = a.words / 4;
+    uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < a.words % 4) a.p[quads * 4 + i] = a.value;
+    const uint4 v = make_uint4(a.value, a.value, a.value, a.value);
+    for (; i < quads; i += stride) reinterpret_cast<uint4 *>(a.p)[i] = v;
+}
+
+hipError_t fill_all(const FillList &f, hipStream_t s) {
+    uint64_t most = 0;
+    for (int k = 0; k < f.count; ++k) most = f.a[k].words > most ? f.a[k].words : most;
+    if (most == 0) return hipSuccess;
+    const uint64_t blocks = (most / 4 + 256) / 256;
+    hipLaunchKernelGGL(k_fill, dim3((uint32_t)(blocks < 8192 ? blocks : 8192), (uint32_t)f.count),
+                       dim3(256), 0, s, f);
+    return hipGetLastError();
 }
 
 hipError_t fill_u32(uint32_t *p, uint32_t value, uint64_t count, hipStream_t s) {
-    if (count == 0) return hipSuccess;
-    uint64_t blocks = (count + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(k_fill_u32, dim3((uint32_t)blocks), dim3(256), 0, s, p, value, count);
-    return hipGetLastError();
+    FillList f;
+    f.add(p, value, count);
+    return fill_all(f, s);
 }
 
 // ======================================================================= scan
@@ -51,27 +64,62 @@ constexpr uint32_t kScanRow = kScanThreads * 4;                 // 4096
 constexpr uint32_t kScanTile = kScanRow * kScanRows;            // 16384
 static_assert(kScanRows * kScanWaves == kWave, "one wave scans the row-wave totals");
 
-__device__ __forceinline__ uint4 scan_load4(const uint32_t *__restrict__ in, uint64_t i,
-                                            uint64_t N) {
-    if (i + 4 <= N) return *reinterpret_cast<const uint4 *>(in + i);
-    uint4 x = make_uint4(0u, 0u, 0u, 0u);
-    if (i < N) x.x = in[i];
-    if (i + 1 < N) x.y = in[i + 1];
-    if (i + 2 < N) x.z = in[i + 2];
-    return x;
+// What a scan adds up: an array, or values formed from the arrays behind them, so that they need
+// no launch and no array of their own.  at(y, i, N): elements i .. i + 3 of sequence y (0 from N on).
+struct ScanArrays {  // sequence y: an array (16-byte aligned)
+    const uint32_t *p[4];
+    __device__ __forceinline__ uint4 at(uint32_t y, uint64_t i, uint64_t N) const {
+        const uint32_t *in = p[y];
+        if (i + 4 <= N) return *reinterpret_cast<const uint4 *>(in + i);
+        uint4 x = make_uint4(0u, 0u, 0u, 0u);
+        if (i < N) x.x = in[i];
+        if (i + 1 < N) x.y = in[i + 1];
+        if (i + 2 < N) x.z = in[i + 2];
+        return x;
+    }
+};
+template <class F>
+__device__ __forceinline__ uint4 four(const F f, uint64_t i, uint64_t N) {
+    return make_uint4(i < N ? f(i) : 0u, i + 1 < N ? f(i + 1) : 0u, i + 2 < N ? f(i + 2) : 0u,
+                      i + 3 < N ? f(i + 3) : 0u);
 }
+struct ScanRows {  // row lengths from the rows' bounds (both 0 for an empty row)
+    const uint32_t *rs, *re;
+    __device__ __forceinline__ uint4 at(uint32_t, uint64_t i, uint64_t N) const {
+        return four([&](uint64_t r) { return re[r] - rs[r]; }, i, N);
+    }
+};
+// Room of every row's entries >= hbase in hcol: none for a row without such entries, else their
+// number rounded up to a multiple of 8, plus `pad` zeros (the counting kernel's pieces, read
+// from 8-aligned positions inside the row's part, never leave it).
+struct ScanHigh {
+    const uint32_t *row_ptr, *hrow;
+    uint32_t pad;
+    __device__ __forceinline__ uint4 at(uint32_t, uint64_t i, uint64_t N) const {
+        return four(
+            [&](uint64_t r) {
+                const uint32_t h = hrow[r];
+                return h != ~0u ? ((row_ptr[r + 1] - h + 7u) & ~7u) + pad : 0u;
+            },
+            i, N);
+    }
+};
+struct ScanOut {
+    uint32_t *p[4];
+};
 
-// sums[b] = total of tile b
-__global__ __launch_bounds__(kScanThreads) void k_scan_sums(const uint32_t *__restrict__ in,
-                                                            uint64_t N,
-                                                            uint32_t *__restrict__ sums) {
+// sums[b] = total of tile b (of sequence y: after y * stride)
+template <class In>
+__global__ __launch_bounds__(kScanThreads) void k_scan_sums(const In in, uint64_t N,
+                                                            uint32_t *__restrict__ sums,
+                                                            uint32_t stride) {
     __shared__ uint32_t s_wave[kScanWaves];
     const uint32_t t = threadIdx.x;
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
     uint32_t run = 0;
 #pragma unroll
     for (int r = 0; r < kScanRows; ++r) {
-        const uint4 x = scan_load4(in, base + r * kScanRow + t * 4, N);
+        const uint4 x = in.at(blockIdx.y, base + r * kScanRow + t * 4, N);
         run += x.x + x.y + x.z + x.w;
     }
     run = wave_total(run);
@@ -79,24 +127,28 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(const uint32_t *__re
     __syncthreads();
     if (t < kWave) {
         const uint32_t total = wave_total(t < kScanWaves ? s_wave[t] : 0u);
-        if (t == 0) sums[blockIdx.x] = total;
+        if (t == 0) sums[blockIdx.y * stride + blockIdx.x] = total;
     }
 }
 
-// the exclusive scan of tile b, after the totals of the tiles before it (in may be out: a
-// workgroup reads its whole tile before it writes)
-__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const uint32_t *in, uint32_t *out,
-                                                            uint64_t N,
-                                                            const uint32_t *__restrict__ sums) {
+// out[i] = sum of the elements before i, for i < N + tail (the elements from N on are 0), of tile
+// b, after the totals of the tiles before it (an input array may be its output: a workgroup
+// reads its whole tile before it writes)
+template <class In>
+__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const In in, const ScanOut outs,
+                                                            uint64_t N, uint32_t tail,
+                                                            const uint32_t *__restrict__ sums,
+                                                            uint32_t stride) {
     __shared__ uint32_t s_part[kScanRows * kScanWaves], s_carry[kScanWaves];
     const uint32_t t = threadIdx.x, w = t / kWave, lane = lane_id();
-    const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
+    const uint64_t base = (uint64_t)blockIdx.x * kScanTile, M = N + tail;
+    uint32_t *out = outs.p[blockIdx.y];
     uint4 x[kScanRows];
     uint32_t incl[kScanRows];
 #pragma unroll
-    for (int r = 0; r < kScanRows; ++r) x[r] = scan_load4(in, base + r * kScanRow + t * 4, N);
+    for (int r = 0; r < kScanRows; ++r) x[r] = in.at(blockIdx.y, base + r * kScanRow + t * 4, N);
     uint32_t before = 0;
-    for (uint32_t k = t; k < blockIdx.x; k += kScanThreads) before += sums[k];
+    for (uint32_t k = t; k < blockIdx.x; k += kScanThreads) before += sums[blockIdx.y * stride + k];
     before = wave_total(before);
 #pragma unroll
     for (int r = 0; r < kScanRows; ++r) {
@@ -118,31 +170,54 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tile(const uint32_t *in, 
         y.y = y.x + x[r].x;
         y.z = y.y + x[r].y;
         y.w = y.z + x[r].z;
-        if (i + 4 <= N) {
+        if (i + 4 <= M) {
             *reinterpret_cast<uint4 *>(out + i) = y;
         } else {
-            if (i < N) out[i] = y.x;
-            if (i + 1 < N) out[i + 1] = y.y;
-            if (i + 2 < N) out[i + 2] = y.z;
+            if (i < M) out[i] = y.x;
+            if (i + 1 < M) out[i + 1] = y.y;
+            if (i + 2 < M) out[i + 2] = y.z;
         }
     }
 }
 
-size_t scan_scratch_words(uint64_t N) {
-    return (size_t)align_up((N + kScanTile - 1) / kScanTile + 1, 64);
+size_t scan_scratch_words(uint64_t N) {  // up to four sequences of N elements
+    return (size_t)align_up(4 * ((N + kScanTile - 1) / kScanTile + 1), 64);
+}
+
+template <class In>
+static hipError_t scan_any(const In &in, const ScanOut &out, uint32_t seqs, uint64_t N,
+                           uint32_t tail, uint32_t *scratch, hipStream_t s) {
+    if (N + tail == 0) return hipSuccess;
+    const uint32_t nb = ceil_div(N + tail, kScanTile);
+    if (nb > 1) {
+        hipLaunchKernelGGL(k_scan_sums<In>, dim3(nb, seqs), dim3(kScanThreads), 0, s, in, N,
+                           scratch, nb);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_scan_tile<In>, dim3(nb, seqs), dim3(kScanThreads), 0, s, in, out, N, tail,
+                       scratch, nb);
+    return hipGetLastError();
 }
 
 hipError_t scan_exclusive_u32(const uint32_t *in, uint32_t *out, uint64_t N, uint32_t *scratch,
                               hipStream_t s) {
-    if (N == 0) return hipSuccess;
-    const uint32_t nb = ceil_div(N, kScanTile);
-    if (nb > 1) {
-        hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(kScanThreads), 0, s, in, N, scratch);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_scan_tile, dim3(nb), dim3(kScanThreads), 0, s, in, out, N, scratch);
-    return hipGetLastError();
+    return scan_any(ScanArrays{{in, in, in, in}}, ScanOut{{out, out, out, out}}, 1, N, 0, scratch,
+                    s);
+}
+hipError_t scan_four_u32(uint32_t *const in[4], uint32_t *const out[4], uint64_t N,
+                         uint32_t *scratch, hipStream_t s) {
+    return scan_any(ScanArrays{{in[0], in[1], in[2], in[3]}},
+                    ScanOut{{out[0], out[1], out[2], out[3]}}, 4, N, 0, scratch, s);
+}
+hipError_t scan_row_bounds(const uint32_t *rs, const uint32_t *re, uint64_t rows, uint32_t *out,
+                           uint32_t *scratch, hipStream_t s) {
+    return scan_any(ScanRows{rs, re}, ScanOut{{out, out, out, out}}, 1, rows, 1, scratch, s);
+}
+hipError_t scan_high_rows(const uint32_t *row_ptr, const uint32_t *hrow, uint64_t rows,
+                          uint32_t pad, uint32_t *out, uint32_t *scratch, hipStream_t s) {
+    return scan_any(ScanHigh{row_ptr, hrow, pad}, ScanOut{{out, out, out, out}}, 1, rows, 1,
+                    scratch, s);
 }
 
 // ======================================================================= radix sort
@@ -420,22 +495,36 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const Src in, uint3
 constexpr uint32_t kRawTiles = 128;
 
 // Global minus local start of every digit into L.glob (all threads; loc filled).
+// (kFew: at most kRawTiles tiles; an instance of its own, since its registers would halve the
+// occupancy of the other)
+template <bool kFew>
 __device__ __forceinline__ void tile_digit_starts(SortTileLds &L, const uint32_t *__restrict__ table,
                                                   uint32_t tiles, uint32_t tile) {
     const uint32_t t = threadIdx.x;
-    if (tiles == 1) {
+    if constexpr (!kFew) {
+        if (t < 256) L.glob[t] = table[(uint64_t)t * tiles + tile] - L.loc[t];
+    } else if (tiles == 1) {
         if (t < 256) L.glob[t] = 0;
-    } else if (tiles <= kRawTiles) {
+    } else {
         // a wave sums 32 digits' rows, lanes along the tiles; lane i keeps its digit i's sums
         constexpr uint32_t kDigits = 256 / kSortWaves;
         const uint32_t w = t / kWave, lane = lane_id();
         uint32_t sum = 0, below = 0;
         for (uint32_t k0 = 0; k0 < tiles; k0 += kWave) {
             const uint32_t k = k0 + lane;
-#pragma unroll 8
+            uint32_t x[kDigits];  // (all loads in flight together)
+#pragma unroll
+            for (uint32_t i = 0; i < kDigits; ++i)
+                x[i] = k < tiles ? table[(w * kDigits + i) * tiles + k] : 0u;
+#pragma unroll
             for (uint32_t i = 0; i < kDigits; ++i) {
-                const uint32_t x = k < tiles ? table[(w * kDigits + i) * tiles + k] : 0u;
-                const uint32_t all = wave_total(x), part = wave_total(k < tile ? x : 0u);
+                const uint32_t in = wave_incl_scan(x[i]);
+                const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)in, kWave - 1);
+                // the tiles before this one: all of the 64, or those up to its own lane
+                const uint32_t part =
+                    tile >= k0 + kWave ? all
+                    : tile > k0 ? (uint32_t)__builtin_amdgcn_readlane((int)in, (int)(tile - 1 - k0))
+                                : 0u;
                 if (lane == i) {
                     sum += all;
                     below += part;
@@ -451,8 +540,6 @@ __device__ __forceinline__ void tile_digit_starts(SortTileLds &L, const uint32_t
             const uint32_t d = w * kDigits + lane;
             L.glob[d] = before + incl - sum + below - L.loc[d];
         }
-    } else if (t < 256) {
-        L.glob[t] = table[(uint64_t)t * tiles + tile] - L.loc[t];
     }
 }
 
@@ -460,7 +547,7 @@ __device__ __forceinline__ void tile_digit_starts(SortTileLds &L, const uint32_t
 // tile-local counting sort), then written out digit run by digit run.
 //   table: digit-major per-tile digit counts, scanned when there are more than kRawTiles tiles
 //   total: nullable, receives the number of keys of all tiles
-template <bool kFull, class Src, class Dst>
+template <bool kFull, bool kFew, class Src, class Dst>
 __device__ __forceinline__ void scatter_tile(const Src in, const Dst out, uint32_t count,
                                              int shift, uint32_t mask,
                                              const uint32_t *__restrict__ table, uint32_t tiles,
@@ -476,7 +563,7 @@ __device__ __forceinline__ void scatter_tile(const Src in, const Dst out, uint32
     wave_rank_rows(keys, vmask, shift, mask, L.wcnt[w], ranks);
     const uint32_t c = tile_digit_offsets(L);
     __syncthreads();
-    tile_digit_starts(L, table, tiles, tile);
+    tile_digit_starts<kFew>(L, table, tiles, tile);
     __syncthreads();
     // the last tile's last run ends at the number of keys
     if (total && tile == tiles - 1 && t == 255) *total = L.glob[255] + L.loc[255] + c;
@@ -485,7 +572,7 @@ __device__ __forceinline__ void scatter_tile(const Src in, const Dst out, uint32
     write_staged(L, out, count, shift, mask, nullptr);
 }
 
-template <class Src, class Dst>
+template <bool kFew, class Src, class Dst>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const Src in, const Dst out, uint32_t count, const uint32_t *__restrict__ dcount, int shift,
     uint32_t nbits, const uint32_t *__restrict__ table, uint32_t tiles,
@@ -497,9 +584,9 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     if ((uint64_t)tile * kSortTile >= count) return;  // past the keys (a device count)
     const uint32_t mask = (1u << nbits) - 1u;
     if ((uint64_t)(tile + 1) * kSortTile <= count)
-        scatter_tile<true>(in, out, count, shift, mask, table, tiles, tile, total, L);
+        scatter_tile<true, kFew>(in, out, count, shift, mask, table, tiles, tile, total, L);
     else
-        scatter_tile<false>(in, out, count, shift, mask, table, tiles, tile, total, L);
+        scatter_tile<false, kFew>(in, out, count, shift, mask, table, tiles, tile, total, L);
 }
 
 // ---------------------------------------------------------------- single-sweep variant
@@ -663,10 +750,12 @@ static hipError_t radix_pass(const Src in, const Dst dst, uint32_t count, int sh
     if (tiles > kRawTiles) {
         e = scan_exclusive_u32(hist, offs, hist_n, scan_scratch, s);
         if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_radix_scatter<false, Src, Dst>), dim3(tiles), dim3(kSortThreads), 0,
+                           s, in, dst, count, dcount, shift, nbits, offs, tiles, total, status);
+    } else {
+        hipLaunchKernelGGL((k_radix_scatter<true, Src, Dst>), dim3(tiles), dim3(kSortThreads), 0,
+                           s, in, dst, count, dcount, shift, nbits, hist, tiles, total, status);
     }
-    hipLaunchKernelGGL((k_radix_scatter<Src, Dst>), dim3(tiles), dim3(kSortThreads), 0, s, in,
-                       dst, count, dcount, shift, nbits, tiles > kRawTiles ? offs : hist, tiles,
-                       total, status);
     return hipGetLastError();
 }
 
