@@ -45,7 +45,8 @@ __global__ void k_csc_final(const uint32_t *, uint32_t, const uint32_t *, uint64
                             uint32_t *, const int32_t *);
 __global__ void k_items(const uint32_t *, const uint32_t *, const uint32_t *, const uint32_t *,
                         uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t,
-                        uint32_t, uint32_t *, uint32_t *, uint32_t *, uint32_t *, const int32_t *);
+                        uint32_t, uint32_t, uint32_t *, uint32_t *, uint32_t *, uint32_t *,
+                        const int32_t *);
 __global__ void k_item_fill(const ItemLists, uint64_t, const int32_t *);
 __global__ void k_pv_out(const unsigned long long *, const uint32_t *, uint32_t,
                          unsigned long long *);
@@ -72,7 +73,7 @@ int device_cu_count() {
 // ------------------------------------------------------------------ workspace layout
 
 struct Layout {
-    size_t ctl, part_hist, part_offs, part_scan, deg, perm, rank, keys_a, keys_b, sort_scratch,
+    size_t ctl, light_total, part_hist, part_offs, part_scan, deg, perm, rank, keys_a, keys_b, sort_scratch,
         rs, re, row_ptr, col, hcol, hrow, hstart, src, prange, eu, lrs, lre, cptr, cbeg, items[4], off[4], item_v[4], scan_scratch, tpv, hub_a, hub_at, rchunk,
         long_rows, total_bytes;
     uint32_t part_tiles;  // 0: degrees by atomics (inputs too large for the partition)
@@ -109,7 +110,10 @@ __global__ void k_ctl_init(uint32_t *__restrict__ ctl, uint32_t finger,
 // caller's word is written here); the item queues and the total restart
 __global__ void k_count_begin(uint32_t *__restrict__ ctl, uint32_t finger,
                               unsigned long long *__restrict__ total,
+                              unsigned long long *__restrict__ light_total,
                               int32_t *__restrict__ d_status) {
+    static_assert(kLightTotals == 64, "one per thread");
+    light_total[threadIdx.x * kLightTotalStep] = 0ull;
     if (threadIdx.x != 0) return;
     int32_t st = (int32_t)ctl[kCtlStatus];
     if (st == 0 && ctl[kCtlFinger] != finger) st = TC_E_MISMATCH;
@@ -242,6 +246,7 @@ static bool make_layout(int64_t n, int64_t m, uint32_t flags, const tc_options *
         return at;
     };
     L.ctl = take(kCtlWords * 4);
+    L.light_total = take(kLightTotals * kLightTotalStep * 8);
     // degree partition: buckets of 2^part_shift ids, at most 256 of them
     {
         const uint64_t endpoints = (flags & TC_EDGES_BOTH) ? (uint64_t)m : 2ull * (uint64_t)m;
@@ -311,6 +316,15 @@ static bool make_layout(int64_t n, int64_t m, uint32_t flags, const tc_options *
         L.finger = fnv_words(w, sizeof(w) / 4) | 1u;
     }
     return true;
+}
+
+// Lists of at most this many in-edges and entries are light (count.hip); with a form limit of the
+// wave items lowered they are wave items as well, so that small graphs reach those forms
+static uint32_t light_lists(const Layout &L) {
+    return L.opt.wave_bitmap_span == count_wave_span() &&
+                   L.opt.wave_list_max == count_wave_list(false)
+               ? count_light_list()
+               : 0u;
 }
 
 template <class T>
@@ -536,8 +550,8 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
                                                                      : count_wave_list(true);
     hipLaunchKernelGGL(k_items, dim3(grid_for(l1, 256)), dim3(256), 0, s, row_ptr, col, lrs, lre,
                        n, L.nblk, L.p0, o.wave_bitmap_span, o.wave_list_max, wl_pv,
-                       o.wave_item_edges, o.block_item_edges, q.items[0], q.items[1], q.items[2],
-                       q.items[3], status);
+                       o.wave_item_edges, o.block_item_edges, light_lists(L), q.items[0],
+                       q.items[1], q.items[2], q.items[3], status);
     TC_LAUNCH_CHECK();
     TC_HIP(scan_four_u32(q.items, q.off, l1, scan_scr, s));
     hipLaunchKernelGGL(k_item_fill, dim3(grid_for(L.lists, 256), 4), dim3(256), 0, s, q, L.lists,
@@ -556,7 +570,9 @@ static int run_count_prepared(void *ws, const Layout &L, hipStream_t s, uint64_t
     int32_t *status = (int32_t *)ctl + kCtlRun;
     unsigned long long *total = (unsigned long long *)d_total;
     unsigned long long *tpv = at<unsigned long long>(ws, L.tpv);
-    hipLaunchKernelGGL(k_count_begin, dim3(1), dim3(64), 0, s, ctl, L.finger, total, d_status);
+    unsigned long long *light_total = at<unsigned long long>(ws, L.light_total);
+    hipLaunchKernelGGL(k_count_begin, dim3(1), dim3(64), 0, s, ctl, L.finger, total,
+                       light_total, d_status);
     TC_LAUNCH_CHECK();
     if (pv && n > 0) {
         hipLaunchKernelGGL(k_zero_u64, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, tpv,
@@ -594,6 +610,9 @@ static int run_count_prepared(void *ws, const Layout &L, hipStream_t s, uint64_t
                                                                 : count_block_list(pv);
         a.kitem_a = o.wave_item_edges;
         a.kitem_b = o.block_item_edges;
+        a.lists = (uint32_t)L.lists;
+        a.light = light_lists(L);
+        a.light_total = light_total;
         a.status = status;
         TC_HIP(launch_count(a, pv, s));
         TC_HIP(launch_hub_count(at<uint8_t>(ws, L.hub_a), at<uint8_t>(ws, L.hub_at), L.hp, L.h0,

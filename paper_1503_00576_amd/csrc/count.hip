@@ -62,6 +62,14 @@ constexpr uint32_t kLightChunkMax = 1536;
 // light rows' pieces: their lists are short (a few elements), so shorter pieces waste fewer
 // lookups on masked positions
 constexpr uint32_t kLightPiece = 8;
+// middle-vertex kernels: a list with at most kLightList in-edges u -> v and at most that many
+// entries in N+(v) is light.  A wave item costs about 560 vector instructions and a chain of
+// loads whatever its size, and eight of them an atomic on the queue; with 8 in-edges of 8 entries
+// each (a small-world graph of 1,000,003 vertices) that was nearly all of the counting kernel's
+// 1.43 ms, and light lists take 0.14 + 0.03 ms.  R-MAT 23: 14.5 -> 13.1 + 0.2 ms.  Limits of 32
+// and 128 measured slower at R-MAT 20 (2041 and 2353 us a count against 1960)
+constexpr uint32_t kLightList = 64;
+constexpr uint32_t kLightListWindow = 512;  // staged entries per wave
 constexpr int kLightThreads = 256;
 constexpr int kLightWaves = kLightThreads / kWave;
 
@@ -591,11 +599,17 @@ __device__ __forceinline__ uint32_t stream_t(uint32_t first, uint32_t e1, uint32
 // that the counter (one address that every XCD's waves update) sees few operations when items
 // are small.  Items are sorted heaviest first, so a claim holds items of similar size.
 struct WaveQueue {
+    static constexpr uint32_t kNearEnd = 8192;  // claims: two of every wave
     uint32_t claim, next = 0, end = 0;
     __device__ __forceinline__ bool pop(uint32_t *counter, uint32_t n_items, uint32_t &q) {
         if (next == end) {
-            uint32_t c = 0;
-            if (lane_id() == 0) c = atomicAdd(counter, claim);
+            // near the queue's end, a look before the claim: a drained queue (or an empty one)
+            // costs a load, where the 4096 waves' atomics on it took 45 us, 11 ns each
+            uint32_t c = n_items;
+            if (lane_id() == 0 && n_items &&
+                (end + kNearEnd * claim < n_items ||
+                 __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n_items))
+                c = atomicAdd(counter, claim);
             c = wave_bcast(c, 0);
             if (c >= n_items) return false;
             next = c;
@@ -988,7 +1002,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
     unsigned long long *__restrict__ tpv, uint32_t n1, uint32_t p0, uint32_t wave_bits,
     uint32_t block_bits, uint32_t block_list, uint32_t kitem_a, uint32_t kitem_b,
     const uint16_t *__restrict__ hcol, const uint32_t *__restrict__ hrow, uint32_t hbase,
-    const int32_t *__restrict__ status) {
+    const unsigned long long *__restrict__ light_total, const int32_t *__restrict__ status) {
     // 8 KiB aligned: a wave slice's base has zero low bits, so bitmap addresses OR it in
     __shared__ __attribute__((aligned(kSliceWords * 4))) uint32_t s_mem[kLdsWords];
     __shared__ WaveScratch s_ws[kWaves];
@@ -999,6 +1013,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
     const InEdgeSegs segs{cbeg, er};
     for (uint32_t i = t; i < kLdsWords; i += kThreads) s_mem[i] = 0;
     uint64_t acc = 0;
+    if (blockIdx.x == 0 && t < kLightTotals) acc = light_total[t * kLightTotalStep];
 
     // phase 1: workgroup items
     const uint32_t n_items_b = *n_items_b_ptr;
@@ -1486,6 +1501,148 @@ __global__ __launch_bounds__(kLightThreads, 8) void k_count_light(const BatchKer
     if (lane < 2) a.wtotal[2 * (x0 >> vshift) + lane] = part;
 }
 
+// ------------------------------------------------------------------ light middle vertices
+//
+// The lists of vertices v below the panels with few in-edges and a short N+(v) (kLightList): a wave
+// takes 64 consecutive lists, stages their N+(v) in LDS (whole lists, a window at a time) and
+// takes their in-edges u -> v one per lane, whatever list they belong to: the suffix of N+(u)
+// after v (short as well: u comes before v in the order of degrees) is looked up in N+(v) by
+// binary search, its first piece on the edge's own lane, further pieces in full rounds.
+//
+// Per-vertex counts: a hit credits an LDS counter of N+(v)'s entry (added to T(w) once per entry,
+// and their sum to T(v)) and T(u) once per piece.
+template <bool PV>
+__global__ __launch_bounds__(kLightThreads) void k_count_light_lists(
+    const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ col,
+    const uint32_t *__restrict__ cptr, const uint32_t *__restrict__ cbeg,
+    const uint4 *__restrict__ er, uint32_t lists, uint32_t n1, uint32_t p0, uint32_t light,
+    unsigned long long *__restrict__ light_total, unsigned long long *__restrict__ tpv,
+    const int32_t *__restrict__ status) {
+    __shared__ uint32_t s_mark[kLightWaves][kWave];
+    __shared__ uint32_t s_list[kLightWaves][kLightListWindow];
+    __shared__ uint32_t s_cnt[kLightWaves][PV ? kLightListWindow : 1];
+    if (*status) return;
+    const uint32_t w = threadIdx.x / kWave, lane = lane_id();
+    const uint32_t tile = xcd_stretch_tile(blockIdx.x, gridDim.x);
+    const uint32_t c = (tile * kLightWaves + w) * kWave + lane;
+    uint32_t *mark = s_mark[w], *list = s_list[w], *cnt3 = s_cnt[w];
+    uint32_t cb = 0, in_edges = 0, r0 = 0, d = 0, v = 0;
+    if (c < lists) {
+        v = c < n1 ? c : c % n1;
+        if (v < p0) {
+            cb = cptr[c];
+            in_edges = cptr[c + 1] - cb;
+            r0 = row_ptr[v];
+            d = row_ptr[v + 1] - r0;
+        }
+    }
+    if (in_edges > light || d > light || in_edges == 0) d = 0;
+    mark[lane] = 0;
+    uint32_t round = 0, hits = 0;
+    const uint32_t list_b = lds_addr(list);
+    const uint32_t incl = wave_incl_scan(d);
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    for (uint32_t w0 = 0; w0 < all;) {  // windows of whole lists
+        const bool in = d > 0 && incl - d >= w0 && incl <= w0 + kLightListWindow;
+        const uint64_t in_mask = __ballot(in);
+        const uint32_t w1 =
+            (uint32_t)__builtin_amdgcn_readlane((int)incl, 63 - __builtin_clzll(in_mask));
+        const uint32_t n = w1 - w0, off = incl - d - w0;
+        const uint32_t delta = r0 - off;
+        uint32_t carry = 0;
+        for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
+            const uint32_t k = round_owner(mark, off, in, i0, ++round, carry) - 1u;
+            const uint32_t dk = wave_bcast_from(delta, k);
+            const uint32_t i = i0 + lane;
+            if (i < n) {
+                list[i] = col[dk + i];
+                if (PV) cnt3[i] = 0;
+            }
+        }
+        wave_lds_sync();
+        const uint32_t ol = off | (d << 16);
+        const uint32_t ne = in ? in_edges : 0u;
+        const uint32_t eincl = wave_incl_scan(ne), eoff = eincl - ne;
+        const uint32_t edges = (uint32_t)__builtin_amdgcn_readlane((int)eincl, kWave - 1);
+        const uint32_t edelta = cb - eoff;
+        // pieces waiting for a full round: lane l < waiting holds one
+        uint32_t waiting = 0, pb = 0, pc = 0, pr = 0, pu = 0, ecarry = 0;
+        uint32_t wv[kLightPiece], at[kLightPiece];
+#pragma unroll
+        for (uint32_t j = 0; j < kLightPiece; ++j) wv[j] = 0;
+        auto credit = [&](uint32_t packed, uint32_t u) {
+            hits += (uint32_t)__popc(packed);
+            if (PV && packed) {
+                atomicAdd(&tpv[u], (unsigned long long)__popc(packed));
+#pragma unroll
+                for (uint32_t j = 0; j < kLightPiece; ++j)
+                    if ((packed >> (kLightPiece - 1 - j)) & 1u)
+                        atomicAdd(&cnt3[(at[j] - list_b) >> 2], 1u);
+            }
+        };
+        auto run_waiting = [&]() {
+            if (pc) load_light_piece(col, pb, wv);
+            credit(light_piece(wv, pc, list_b + (pr & 0xFFFFu) * 4u, pr >> 16, at), pu);
+        };
+        for (uint32_t i0 = 0; i0 < edges; i0 += kWave) {
+            const uint32_t k = round_owner(mark, eoff, ne, i0, ++round, ecarry) - 1u;
+            const uint32_t j = wave_bcast_from(edelta, k) + i0 + lane;
+            const uint32_t rk = wave_bcast_from(ol, k);
+            uint32_t b = 0, en = 0, u = 0;
+            if (i0 + lane < edges) {
+                b = cbeg[j];
+                const uint4 r = er[b - 1];
+                en = r.x;
+                u = r.w;
+            }
+            const uint32_t len = en - b;
+            if (len) load_light_piece(col, b, wv);
+            credit(light_piece(wv, len, list_b + (rk & 0xFFFFu) * 4u, rk >> 16, at), u);
+            const uint32_t p = len > kLightPiece ? (len - 1) / kLightPiece : 0u;
+            if (__ballot(p != 0) == 0) continue;
+            const uint32_t pincl = wave_incl_scan(p);
+            const uint32_t my_off = waiting + pincl - p;
+            const uint32_t Q =
+                waiting + (uint32_t)__builtin_amdgcn_readlane((int)pincl, kWave - 1);
+            uint32_t pcarry = 0;
+            for (uint32_t q0 = 0; q0 < Q; q0 += kWave) {
+                const uint32_t kq = round_owner(mark, my_off, p, q0, ++round, pcarry) - 1u;
+                const uint32_t q = q0 + lane - wave_bcast_from(my_off, kq);
+                const uint32_t qb = wave_bcast_from(b, kq) + (q + 1u) * kLightPiece;
+                const uint32_t qe = wave_bcast_from(en, kq);
+                const uint32_t rq = wave_bcast_from(rk, kq);
+                const uint32_t uq = PV ? wave_bcast_from(u, kq) : 0u;
+                if (q0 + lane >= waiting) {
+                    pb = qb;
+                    pc = q0 + lane < Q ? qe - qb : 0u;
+                    pr = rq;
+                    pu = uq;
+                }
+                waiting = Q - q0;  // (from this round on)
+                if (waiting < kWave) break;
+                run_waiting();
+                waiting = 0;
+            }
+        }
+        if (waiting) run_waiting();
+        wave_lds_sync();
+        if (PV) {
+            for (uint32_t i = lane; i < n; i += kWave)
+                if (cnt3[i]) atomicAdd(&tpv[list[i]], (unsigned long long)cnt3[i]);
+            uint32_t sum = 0;
+            if (in)
+                for (uint32_t j = 0; j < d; ++j) sum += cnt3[off + j];
+            if (sum) atomicAdd(&tpv[v], (unsigned long long)sum);
+            wave_lds_sync();
+        }
+        w0 = w1;
+    }
+    const uint64_t sum = wave_sum_u64(hits);
+    // (one counter for all waves would queue them, 11 ns each)
+    if (lane == 0 && sum)
+        atomicAdd(&light_total[tile % kLightTotals * kLightTotalStep], (unsigned long long)sum);
+}
+
 uint32_t count_light_window(uint32_t chunk, uint32_t light_max) {
     const uint32_t w = chunk > light_max ? chunk : light_max;
     return (w + 63u) & ~63u;
@@ -1521,9 +1678,25 @@ uint32_t count_wgs_per_cu() { return kWgsPerCu; }
 uint32_t count_light_max() { return kLightMax; }
 uint32_t count_light_chunk_max() { return kLightChunkMax; }
 uint32_t count_panel_ranks() { return kPanelRanks; }
+uint32_t count_light_list() { return kLightList; }
 
 hipError_t launch_count(const CountArgs &x, bool per_vertex, hipStream_t s) {
     const dim3 grid(device_cu_count() * kWgsPerCu), block(kThreads);
+    if (x.light && x.p0 > 0) {  // before k_count, which adds their totals
+        // with one row block only the lists below the panels can be light
+        const uint32_t lists = x.lists <= x.n1 ? x.p0 : x.lists;
+        const dim3 lg(ceil_div(lists, kLightThreads)), lb(kLightThreads);
+        if (per_vertex)
+            hipLaunchKernelGGL(k_count_light_lists<true>, lg, lb, 0, s, x.row_ptr, x.col, x.cptr,
+                               x.cbeg, x.er, lists, x.n1, x.p0, x.light, x.light_total, x.tpv,
+                               x.status);
+        else
+            hipLaunchKernelGGL(k_count_light_lists<false>, lg, lb, 0, s, x.row_ptr, x.col, x.cptr,
+                               x.cbeg, x.er, lists, x.n1, x.p0, x.light, x.light_total, x.tpv,
+                               x.status);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     if (per_vertex && x.p0 + 1 < x.n1) {  // panels: those that fit first, on their own queue
         hipLaunchKernelGGL(k_count_panel_pv, grid, block, 0, s, x.row_ptr, x.col, x.cptr,
                            x.cbeg, x.er, x.item_v_b, x.item_off_b,
@@ -1537,13 +1710,13 @@ hipError_t launch_count(const CountArgs &x, bool per_vertex, hipStream_t s) {
                            x.er, x.item_v_a, x.item_off_a, x.n_items_a,
                            x.item_v_b, x.item_off_b, x.n_items_b, x.queue_a, x.queue_b, x.total,
                            x.tpv, x.n1, x.p0, x.wave_bits, x.block_bits, x.block_list,
-                           x.kitem_a, x.kitem_b, x.hcol, x.hrow, x.hbase, x.status);
+                           x.kitem_a, x.kitem_b, x.hcol, x.hrow, x.hbase, x.light_total, x.status);
     else
         hipLaunchKernelGGL(k_count<false>, grid, block, 0, s, x.row_ptr, x.col, x.cptr, x.cbeg,
                            x.er, x.item_v_a, x.item_off_a, x.n_items_a,
                            x.item_v_b, x.item_off_b, x.n_items_b, x.queue_a, x.queue_b, x.total,
                            x.tpv, x.n1, x.p0, x.wave_bits, x.block_bits, x.block_list,
-                           x.kitem_a, x.kitem_b, x.hcol, x.hrow, x.hbase, x.status);
+                           x.kitem_a, x.kitem_b, x.hcol, x.hrow, x.hbase, x.light_total, x.status);
     return hipGetLastError();
 }
 

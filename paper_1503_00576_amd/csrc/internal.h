@@ -224,8 +224,14 @@ struct CountArgs {
     uint32_t block_list;  // ... else an LDS list of at most this many entries (<= kBlockList)
     uint32_t kitem_a;     // in-edges per wave item
     uint32_t kitem_b;     // in-edges per workgroup item
+    uint32_t lists;       // in-edge lists in all
+    uint32_t light;       // lists of at most this many in-edges and entries of N+(v) are light
+                          // (0: none); k_items gives them no items
+    unsigned long long *light_total;  // kLightTotals counters a cache line apart, cleared
     const int32_t *status;
 };
+constexpr uint32_t kLightTotals = 64, kLightTotalStep = 16;
+uint32_t count_light_list();  // the largest light list
 hipError_t launch_count(const CountArgs &a, bool per_vertex, hipStream_t s);
 // LDS limits of the counting kernels' per-item structures (the defaults of the options)
 uint32_t count_wave_span();         // wave bitmap: rank span below this

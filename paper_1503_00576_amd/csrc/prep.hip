@@ -891,12 +891,12 @@ __global__ void k_csc_final(const uint32_t *__restrict__ list, uint32_t mf,
 // its rank span or as a sorted list; for per-vertex counts as a list with counters),
 // otherwise to the per-workgroup queue.  Both classifications are prepared, so a prepared
 // graph can be counted either way.  Panel lists (first rank >= p0) always go to the
-// per-workgroup queue.
+// per-workgroup queue; light lists (at most `light` in-edges and entries) to neither.
 __global__ void k_items(const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ col,
                         const uint32_t *__restrict__ lrs, const uint32_t *__restrict__ lre,
                         uint32_t n, uint32_t nblk, uint32_t p0,
                         uint32_t wave_span, uint32_t wave_list, uint32_t wave_list_pv,
-                        uint32_t ka, uint32_t kb,
+                        uint32_t ka, uint32_t kb, uint32_t light,
                         uint32_t *__restrict__ ia, uint32_t *__restrict__ ib,
                         uint32_t *__restrict__ ia_pv, uint32_t *__restrict__ ib_pv,
                         const int32_t *__restrict__ status) {
@@ -913,8 +913,10 @@ __global__ void k_items(const uint32_t *__restrict__ row_ptr, const uint32_t *__
         const uint32_t r0 = row_ptr[v], d = row_ptr[v + 1] - r0;
         const uint32_t span = col[r0 + d - 1] - col[r0];
         const uint32_t na = (cnt + ka - 1) / ka, nb = (cnt + kb - 1) / kb;
-        if (span < wave_span || d <= wave_list) a = na; else b = nb;
-        if (d <= wave_list_pv) apv = na; else bpv = nb;
+        if (cnt > light || d > light) {
+            if (span < wave_span || d <= wave_list) a = na; else b = nb;
+            if (d <= wave_list_pv) apv = na; else bpv = nb;
+        }
     }
     ia[c] = a;
     ib[c] = b;

@@ -561,3 +561,21 @@ def test_autotune_single(tmp_path):
     assert api.count(e, n, options=best) == want
     again, _ = autotune.tune_single(e, n, cache=cache, candidates=cands[:1])
     assert again == best
+
+
+@pytest.mark.parametrize("row_blocks", [1, 3])
+@pytest.mark.parametrize("k", [2, 7, 8, 9, 10, 17, 63, 64, 65, 66, 67, 130])
+def test_light_lists_at_their_limits(k, row_blocks):
+    """Middle vertices with up to 64 in-edges and out-entries (light lists) and just above, in
+    one graph with low-degree ones: cliques of k, 130 copies of a small one (windows of several
+    lists), a wheel, all below the panel region (panel_ranks = 0)."""
+    edges, base = [], 0
+    for size, copies in ((k, 2), (9, 130)):
+        for _ in range(copies):
+            edges += [(base + i, base + j) for i in range(size) for j in range(i + 1, size)]
+            base += size
+    edges += [(base, base + i) for i in range(1, 81)]
+    edges += [(base + i, base + i % 80 + 1) for i in range(1, 81)]
+    n = base + 81
+    check_vs_oracle(np.array(edges, dtype=np.int32), n,
+                    options={"panel_ranks": 0, "row_blocks": row_blocks}, prepared_pv=True)
