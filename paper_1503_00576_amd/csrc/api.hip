@@ -93,18 +93,9 @@ struct Layout {
 // ctl words: status of the preprocessing, forward-entry counter (two-direction format), the
 // two item queues, the fingerprint of the prepared layout, status of the current count
 enum {
-    kCtlStatus = 0, kCtlBoth = 1, kCtlQueueA = 2, kCtlQueueB = 3, kCtlFinger = 4, kCtlRun = 5,
-    kCtlQueueC = 6, kCtlLongRows = 7, kCtlKept = 8, kCtlWords = 64
+    kCtlStatus = 0, kCtlBoth = 1, kCtlQueueA = 2, kCtlQueueB = 3, kCtlRun = 5, kCtlQueueC = 6,
+    kCtlLongRows = 7, kCtlKept = 8, kCtlFinger = 60, kCtlWords = 64
 };
-// start of a preprocessing: clear the control words, record the layout's fingerprint, and clear the
-// word after the degree partition's table (nullable), which its scan reads as well
-__global__ void k_ctl_init(uint32_t *__restrict__ ctl, uint32_t finger,
-                           uint32_t *__restrict__ part_end) {
-    const uint32_t t = threadIdx.x;
-    ctl[t] = t == kCtlFinger ? finger : 0u;  // 64 threads, one word each
-    if (part_end && t == 0) *part_end = 0u;
-}
-
 // start of a count on a prepared workspace: its status is the preprocessing's, or a mismatch
 // when the workspace was prepared for another layout (no counting kernel adds to it, so the
 // caller's word is written here); the item queues and the total restart
@@ -387,9 +378,6 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     int2 *cells = L.cell_shift >= 0 ? at<int2>(ws, L.eu) : nullptr;
     uint32_t *ph = at<uint32_t>(ws, L.part_hist), *po = at<uint32_t>(ws, L.part_offs);
     const uint64_t hp = (L.cell_shift >= 0 ? 512ull : 256ull) * L.part_tiles;
-    hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, s, ctl, L.finger,
-                       m > 0 && L.part_tiles ? ph + hp : nullptr);
-    TC_LAUNCH_CHECK();
     const bool onesweep = L.opt.sort_onesweep != 0;
     const bool row_sort = L.opt.row_sort && L.mf < kRowSortMaxEdges;
     const uint64_t l1 = L.lists + 1;
@@ -397,9 +385,18 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     uint32_t *hrow = at<uint32_t>(ws, L.hrow);
     uint32_t *lrs = at<uint32_t>(ws, L.lrs), *lre = at<uint32_t>(ws, L.lre);
     uint16_t *hcol = at<uint16_t>(ws, L.hcol);
-    // everything that later kernels add to or mark, cleared by one launch
+    // small graphs take counting sorts (small.hip); the options that pick steps of the general path
+    // keep it
+    const bool small = m > 0 && n <= small_vertices() && m <= small_entries() && row_sort &&
+                       L.opt.degree_partition && !onesweep && L.nblk == 1;
+    const bool part = m > 0 && L.part_tiles && !small;
+    // the control words with the layout's fingerprint, and everything that later kernels add to
+    // or mark (the word after the degree partition's table is scanned with it), by one launch
     {
         FillList f;
+        f.add(ctl, 0u, kCtlFinger);
+        f.add(ctl + kCtlFinger, L.finger, kCtlWords - kCtlFinger);
+        if (part) f.add(ph + hp, 0u, 1);
         f.add(deg, 0u, n);
         if (mf == 0) {
             f.add(row_ptr, 0u, n1);
@@ -417,7 +414,9 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
         }
         TC_HIP(fill_all(f, s));
     }
-    if (m > 0 && L.part_tiles) {
+    if (small) {
+        TC_HIP(small_order(d_edges, m, n, both, deg, perm, rank, status, s));
+    } else if (part) {
         const uint32_t tiles = L.part_tiles;
         // the endpoints' offsets inside their buckets, 2 bytes each when a bucket holds at most
         // 2^16 ids, else 4 (either fits the 8-byte key buffer)
@@ -452,12 +451,12 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
         TC_LAUNCH_CHECK();
     }
     // the order of Section 2.2 as ranks: stable sort of (degree << b | id) on the degree bits
-    if (n > 0) {
+    if (n > 0 && !small) {
         // the first pass reads the degrees, the last one writes perm and rank
         TC_HIP(sort_ranks(deg, ka, kb, n, b, perm, rank, sort_scr, nullptr, s));
     }
     uint64_t *sorted = ka;
-    if (m > 0) {
+    if (m > 0 && !small) {
         if (cells) {
             hipLaunchKernelGGL(k_orient_cells, dim3(kOrientGrid), dim3(256), 0, s, cells,
                                (uint64_t)m, n, rank, b, ka, status);
@@ -479,14 +478,17 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     // node array: row boundaries -> row lengths -> exclusive scan
     uint32_t *rchunk = at<uint32_t>(ws, L.rchunk);
     // 4 entries per thread (prep.hip, kCsrKeys)
-    if (row_sort)
+    if (small)
+        TC_HIP(small_rows(d_edges, m, n, both, mf, rank, (uint2 *)ka, rs, re, row_ptr, col, src,
+                          rchunk, ctl + kCtlBoth, scan_scr, status, s));
+    else if (row_sort)
         hipLaunchKernelGGL(k_row_bounds, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, src, mf,
                            n, rs, re, rchunk, status);
     else
         hipLaunchKernelGGL(k_csr, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, sorted, mf, n,
                            b, L.hbase, col, src, rs, re, hrow, status);
     TC_LAUNCH_CHECK();
-    TC_HIP(scan_row_bounds(rs, re, n, row_ptr, scan_scr, s));
+    if (!small) TC_HIP(scan_row_bounds(rs, re, n, row_ptr, scan_scr, s));
     if (row_sort) {  // every row sorted in place, with the duplicate check and hrow
         const uint32_t chunks = ceil_div(mf, row_sort_chunk());
         uint32_t *long_rows = at<uint32_t>(ws, L.long_rows);
@@ -535,16 +537,21 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
                        src, row_ptr, hrow, hstart, L.hbase, pr, mf, n, L.nblk, L.p0,
                        count_panel(), L.h0, cid, eu, hcol, status);
     TC_LAUNCH_CHECK();
-    // sorted into (list id, cbeg) pairs: the list ids land in ck or ck2 (as 32-bit words);
-    // the in-edges of no list are dropped by the first pass (ctl[kCtlKept] of them remain)
-    uint32_t *clist = nullptr;
-    TC_HIP(sort_lists(cid, (uint32_t)L.lists, mf, id_bits_for64(l1), ck, ck2,
-                      at<uint32_t>(ws, L.cbeg), ctl + kCtlKept, sort_scr, status, s, &clist));
-    hipLaunchKernelGGL(k_csc_final, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, clist, mf,
-                       ctl + kCtlKept, L.lists, lrs, lre,
-                       status);  // 4 ids per thread (prep.hip, kCscFinalKeys)
-    TC_LAUNCH_CHECK();
-    TC_HIP(scan_row_bounds(lrs, lre, L.lists, cptr, scan_scr, s));
+    if (small) {
+        TC_HIP(small_lists(cid, mf, (uint32_t)L.lists, lrs, lre, (uint32_t *)ck, cptr,
+                           at<uint32_t>(ws, L.cbeg), scan_scr, status, s));
+    } else {
+        // sorted into (list id, cbeg) pairs: the list ids land in ck or ck2 (as 32-bit words);
+        // the in-edges of no list are dropped by the first pass (ctl[kCtlKept] of them remain)
+        uint32_t *clist = nullptr;
+        TC_HIP(sort_lists(cid, (uint32_t)L.lists, mf, id_bits_for64(l1), ck, ck2,
+                          at<uint32_t>(ws, L.cbeg), ctl + kCtlKept, sort_scr, status, s, &clist));
+        hipLaunchKernelGGL(k_csc_final, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, clist, mf,
+                           ctl + kCtlKept, L.lists, lrs, lre,
+                           status);  // 4 ids per thread (prep.hip, kCscFinalKeys)
+        TC_LAUNCH_CHECK();
+        TC_HIP(scan_row_bounds(lrs, lre, L.lists, cptr, scan_scr, s));
+    }
     const tc_options &o = L.opt;
     const uint32_t wl_pv = o.wave_list_max < count_wave_list(true) ? o.wave_list_max
                                                                      : count_wave_list(true);

@@ -182,7 +182,7 @@ struct Fill {
     uint32_t value;
 };
 struct FillList {
-    Fill a[10];
+    Fill a[12];
     int count = 0;
     void add(uint32_t *p, uint32_t value, uint64_t words) {
         if (words) a[count++] = Fill{p, words, value};
@@ -190,6 +190,22 @@ struct FillList {
 };
 hipError_t fill_all(const FillList &f, hipStream_t s);
 hipError_t fill_u32(uint32_t *p, uint32_t value, uint64_t count, hipStream_t s);
+
+// preprocessing of small graphs (small.hip): at most small_vertices() vertices, small_entries()
+// entries.  Degrees (deg cleared) and order; rows (re and counter cleared, rs zero) in any order
+// inside, with rchunk for the row sort; in-edge lists from the in-edges' list ids (lre cleared, lrs
+// zero; lre[c] = the entries of list c)
+uint32_t small_vertices();
+uint32_t small_entries();
+hipError_t small_order(const int32_t *edges, uint32_t m, uint32_t n, bool both, uint32_t *deg,
+                       uint32_t *perm, uint32_t *rank, int32_t *status, hipStream_t s);
+hipError_t small_rows(const int32_t *edges, uint32_t m, uint32_t n, bool both, uint32_t mf,
+                      const uint32_t *rank, uint2 *tmp, const uint32_t *rs, uint32_t *re,
+                      uint32_t *row_ptr, uint32_t *col, uint32_t *src, uint32_t *rchunk,
+                      uint32_t *counter, uint32_t *scan_scratch, int32_t *status, hipStream_t s);
+hipError_t small_lists(const uint32_t *cid, uint32_t mf, uint32_t lists, const uint32_t *lrs,
+                       uint32_t *lre, uint32_t *pos, uint32_t *cptr, uint32_t *cbeg,
+                       uint32_t *scan_scratch, int32_t *status, hipStream_t s);
 
 int device_cu_count();
 
