@@ -90,8 +90,10 @@ const char *tc_strerror(int status);
  *                     default 65536.
  * Per-item structure of N+(v) (the defaults are the largest values the LDS holds; lower values
  * send items to the other forms, which the tests use to reach every form on small graphs):
- * Vertices v below the panels with at most 64 in-edges and at most 64 entries in N+(v) are counted
- * edge by edge, outside the queues, while wave_bitmap_span and wave_list_max have their defaults.
+ * Unless the panel region takes in the whole graph, and while wave_bitmap_span and wave_list_max
+ * have their defaults, vertices with at most 64 edges are not counted in panels, and vertices v
+ * below the panels with at most 64 in-edges and at most 64 entries in N+(v) are counted edge by
+ * edge, outside the queues.
  *   wave_bitmap_span  a wave item tests membership in an LDS bitmap when the rank span of
  *                     N+(v) is below this; 0..65504, default 65504.
  *   wave_list_max     otherwise a sorted LDS list when N+(v) has at most this many entries

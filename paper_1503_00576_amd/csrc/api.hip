@@ -36,17 +36,18 @@ __global__ void k_row_sort(uint32_t *, const uint32_t *, const uint32_t *, uint3
 __global__ void k_row_sort_long(uint32_t *, const uint32_t *, const uint32_t *,
                                 const uint32_t *, uint32_t, uint32_t *, int32_t *);
 __global__ void k_panel_range(const uint32_t *, const uint32_t *, uint32_t, uint32_t, uint32_t,
-                              uint64_t *);
+                              const uint32_t *, const uint32_t *, uint32_t, uint32_t *,
+                              uint64_t *, const int32_t *);
 __global__ void k_csc_keys(const uint32_t *, const uint32_t *, const uint32_t *,
                            const uint32_t *, const uint32_t *, uint32_t, const uint64_t *,
-                           uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t,
-                           uint32_t *, uint4 *, uint16_t *, const int32_t *);
+                           uint32_t, uint32_t, uint32_t, uint32_t, const uint32_t *, uint32_t,
+                           uint32_t, uint32_t *, uint4 *, uint16_t *, const int32_t *);
 __global__ void k_csc_final(const uint32_t *, uint32_t, const uint32_t *, uint64_t, uint32_t *,
                             uint32_t *, const int32_t *);
 __global__ void k_items(const uint32_t *, const uint32_t *, const uint32_t *, const uint32_t *,
-                        uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t,
-                        uint32_t, uint32_t, uint32_t *, uint32_t *, uint32_t *, uint32_t *,
-                        const int32_t *);
+                        uint32_t, uint32_t, const uint32_t *, uint32_t, uint32_t, uint32_t,
+                        uint32_t, uint32_t, uint32_t, uint32_t *, uint32_t *, uint32_t *,
+                        uint32_t *, const int32_t *);
 __global__ void k_item_fill(const ItemLists, uint64_t, const int32_t *);
 __global__ void k_pv_out(const unsigned long long *, const uint32_t *, uint32_t,
                          unsigned long long *);
@@ -94,7 +95,7 @@ struct Layout {
 // two item queues, the fingerprint of the prepared layout, status of the current count
 enum {
     kCtlStatus = 0, kCtlBoth = 1, kCtlQueueA = 2, kCtlQueueB = 3, kCtlRun = 5, kCtlQueueC = 6,
-    kCtlLongRows = 7, kCtlKept = 8, kCtlFinger = 60, kCtlWords = 64
+    kCtlLongRows = 7, kCtlKept = 8, kCtlFirstPanel = 56, kCtlFinger = 60, kCtlWords = 64
 };
 // start of a count on a prepared workspace: its status is the preprocessing's, or a mismatch
 // when the workspace was prepared for another layout (no counting kernel adds to it, so the
@@ -309,10 +310,12 @@ static bool make_layout(int64_t n, int64_t m, uint32_t flags, const tc_options *
     return true;
 }
 
-// Lists of at most this many in-edges and entries are light (count.hip); with a form limit of the
-// wave items lowered they are wave items as well, so that small graphs reach those forms
+// Lists of at most this many in-edges and entries are light (count.hip).  None when the panel region
+// holds the whole graph: one launch then counts everything (17 us for 8,009 vertices and 100,003
+// edges, where the light lists' own launch took 34 more).  None with a form limit of the wave
+// items lowered: they are wave items as well then, so that small graphs reach those forms.
 static uint32_t light_lists(const Layout &L) {
-    return L.opt.wave_bitmap_span == count_wave_span() &&
+    return L.p0 > 0 && L.opt.wave_bitmap_span == count_wave_span() &&
                    L.opt.wave_list_max == count_wave_list(false)
                ? count_light_list()
                : 0u;
@@ -394,7 +397,8 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     // or mark (the word after the degree partition's table is scanned with it), by one launch
     {
         FillList f;
-        f.add(ctl, 0u, kCtlFinger);
+        f.add(ctl, 0u, kCtlFirstPanel);
+        f.add(ctl + kCtlFirstPanel, L.p0, kCtlFinger - kCtlFirstPanel);
         f.add(ctl + kCtlFinger, L.finger, kCtlWords - kCtlFinger);
         if (part) f.add(ph + hp, 0u, 1);
         f.add(deg, 0u, n);
@@ -530,11 +534,13 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     uint64_t *pr = at<uint64_t>(ws, L.prange);
     if (L.panels) {
         hipLaunchKernelGGL(k_panel_range, dim3(grid_for(32ull * L.panels, 256)), dim3(256), 0, s,
-                           row_ptr, col, n, L.p0, L.panels, pr);
+                           row_ptr, col, n, L.p0, L.panels, deg, perm, light_lists(L),
+                           ctl + kCtlFirstPanel, pr, status);
         TC_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(k_csc_keys, dim3(grid_for(mf, 256 * kCscPerThread)), dim3(256), 0, s, col,
                        src, row_ptr, hrow, hstart, L.hbase, pr, mf, n, L.nblk, L.p0,
+                       ctl + kCtlFirstPanel,
                        count_panel(), L.h0, cid, eu, hcol, status);
     TC_LAUNCH_CHECK();
     if (small) {
@@ -556,7 +562,7 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     const uint32_t wl_pv = o.wave_list_max < count_wave_list(true) ? o.wave_list_max
                                                                      : count_wave_list(true);
     hipLaunchKernelGGL(k_items, dim3(grid_for(l1, 256)), dim3(256), 0, s, row_ptr, col, lrs, lre,
-                       n, L.nblk, L.p0, o.wave_bitmap_span, o.wave_list_max, wl_pv,
+                       n, L.nblk, ctl + kCtlFirstPanel, o.wave_bitmap_span, o.wave_list_max, wl_pv,
                        o.wave_item_edges, o.block_item_edges, light_lists(L), q.items[0],
                        q.items[1], q.items[2], q.items[3], status);
     TC_LAUNCH_CHECK();
@@ -610,6 +616,7 @@ static int run_count_prepared(void *ws, const Layout &L, hipStream_t s, uint64_t
         a.tpv = tpv;
         a.n1 = n + 1;
         a.p0 = L.p0;
+        a.first_panel = ctl + kCtlFirstPanel;
         const tc_options &o = L.opt;
         a.wave_bits = o.wave_bitmap_span;
         a.block_bits = o.block_bitmap_span;

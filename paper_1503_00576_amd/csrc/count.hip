@@ -70,6 +70,7 @@ constexpr uint32_t kLightPiece = 8;
 // and 128 measured slower at R-MAT 20 (2041 and 2353 us a count against 1960)
 constexpr uint32_t kLightList = 64;
 constexpr uint32_t kLightListWindow = 512;  // staged entries per wave
+constexpr uint32_t kLightLists = 16;        // lists per wave
 constexpr int kLightThreads = 256;
 constexpr int kLightWaves = kLightThreads / kWave;
 
@@ -912,7 +913,8 @@ __global__ __launch_bounds__(kThreads) void k_count_panel_pv(
     const uint4 *__restrict__ er, const uint32_t *__restrict__ item_v_b,
     const uint32_t *__restrict__ item_off_b, const uint32_t *__restrict__ n_items_b_ptr,
     uint32_t *__restrict__ queue_c, unsigned long long *__restrict__ total,
-    unsigned long long *__restrict__ tpv, uint32_t n1, uint32_t p0, uint32_t kitem_b,
+    unsigned long long *__restrict__ tpv, uint32_t n1, const uint32_t *__restrict__ first_panel,
+    uint32_t kitem_b,
     const uint16_t *__restrict__ hcol, uint32_t hbase, const int32_t *__restrict__ status) {
     __shared__ uint32_t s_mem[kLdsWords];
     __shared__ WaveScratch s_ws[kWaves];
@@ -937,7 +939,7 @@ __global__ __launch_bounds__(kThreads) void k_count_panel_pv(
         if (q >= n_items_b) break;
         q = n_items_b - 1 - q;
         const ItemRange it = item_range(q, kitem_b, n1, item_v_b, item_off_b, cptr, row_ptr);
-        if (it.v < p0) continue;  // left to k_count<true>
+        if (it.v < *first_panel) continue;  // left to k_count<true>
         const uint32_t P = it.v, np = min(kPanel, n1 - 1 - P);
         uint32_t cnt = 0, pieces = 0;
         // window of ranks [lo, lo + wn) above P (rank P itself is in no out-list of the panel)
@@ -999,7 +1001,8 @@ __global__ __launch_bounds__(kThreads) void k_count(
     const uint32_t *__restrict__ item_v_b, const uint32_t *__restrict__ item_off_b,
     const uint32_t *__restrict__ n_items_b_ptr, uint32_t *__restrict__ queue_a,
     uint32_t *__restrict__ queue_b, unsigned long long *__restrict__ total,
-    unsigned long long *__restrict__ tpv, uint32_t n1, uint32_t p0, uint32_t wave_bits,
+    unsigned long long *__restrict__ tpv, uint32_t n1, const uint32_t *__restrict__ first_panel,
+    uint32_t wave_bits,
     uint32_t block_bits, uint32_t block_list, uint32_t kitem_a, uint32_t kitem_b,
     const uint16_t *__restrict__ hcol, const uint32_t *__restrict__ hrow, uint32_t hbase,
     const unsigned long long *__restrict__ light_total, const int32_t *__restrict__ status) {
@@ -1015,6 +1018,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
     uint64_t acc = 0;
     if (blockIdx.x == 0 && t < kLightTotals) acc = light_total[t * kLightTotalStep];
 
+    const uint32_t p0 = *first_panel;
     // phase 1: workgroup items
     const uint32_t n_items_b = *n_items_b_ptr;
     for (;;) {
@@ -1503,8 +1507,9 @@ __global__ __launch_bounds__(kLightThreads, 8) void k_count_light(const BatchKer
 
 // ------------------------------------------------------------------ light middle vertices
 //
-// The lists of vertices v below the panels with few in-edges and a short N+(v) (kLightList): a wave
-// takes 64 consecutive lists, stages their N+(v) in LDS (whole lists, a window at a time) and
+// The lists of vertices v below the first panel with few in-edges and a short N+(v) (kLightList): a
+// wave takes kLightLists consecutive lists (16: at R-MAT 20 the densest waves of 64 lists ran on
+// for 100 us after the others, 1960 against 1913 us a count; 8 lists: the same), stages their N+(v) in LDS (whole lists, a window at a time) and
 // takes their in-edges u -> v one per lane, whatever list they belong to: the suffix of N+(u)
 // after v (short as well: u comes before v in the order of degrees) is looked up in N+(v) by
 // binary search, its first piece on the edge's own lane, further pieces in full rounds.
@@ -1515,7 +1520,8 @@ template <bool PV>
 __global__ __launch_bounds__(kLightThreads) void k_count_light_lists(
     const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ col,
     const uint32_t *__restrict__ cptr, const uint32_t *__restrict__ cbeg,
-    const uint4 *__restrict__ er, uint32_t lists, uint32_t n1, uint32_t p0, uint32_t light,
+    const uint4 *__restrict__ er, uint32_t lists, uint32_t n1,
+    const uint32_t *__restrict__ first_panel, uint32_t light,
     unsigned long long *__restrict__ light_total, unsigned long long *__restrict__ tpv,
     const int32_t *__restrict__ status) {
     __shared__ uint32_t s_mark[kLightWaves][kWave];
@@ -1524,12 +1530,12 @@ __global__ __launch_bounds__(kLightThreads) void k_count_light_lists(
     if (*status) return;
     const uint32_t w = threadIdx.x / kWave, lane = lane_id();
     const uint32_t tile = xcd_stretch_tile(blockIdx.x, gridDim.x);
-    const uint32_t c = (tile * kLightWaves + w) * kWave + lane;
+    const uint32_t c = lane < kLightLists ? (tile * kLightWaves + w) * kLightLists + lane : lists;
     uint32_t *mark = s_mark[w], *list = s_list[w], *cnt3 = s_cnt[w];
     uint32_t cb = 0, in_edges = 0, r0 = 0, d = 0, v = 0;
     if (c < lists) {
         v = c < n1 ? c : c % n1;
-        if (v < p0) {
+        if (v < *first_panel) {
             cb = cptr[c];
             in_edges = cptr[c + 1] - cb;
             r0 = row_ptr[v];
@@ -1682,17 +1688,16 @@ uint32_t count_light_list() { return kLightList; }
 
 hipError_t launch_count(const CountArgs &x, bool per_vertex, hipStream_t s) {
     const dim3 grid(device_cu_count() * kWgsPerCu), block(kThreads);
-    if (x.light && x.p0 > 0) {  // before k_count, which adds their totals
-        // with one row block only the lists below the panels can be light
-        const uint32_t lists = x.lists <= x.n1 ? x.p0 : x.lists;
-        const dim3 lg(ceil_div(lists, kLightThreads)), lb(kLightThreads);
+    if (x.light) {  // before k_count, which adds their totals
+        const uint32_t lists = x.lists;
+        const dim3 lg(ceil_div(lists, kLightWaves * kLightLists)), lb(kLightThreads);
         if (per_vertex)
             hipLaunchKernelGGL(k_count_light_lists<true>, lg, lb, 0, s, x.row_ptr, x.col, x.cptr,
-                               x.cbeg, x.er, lists, x.n1, x.p0, x.light, x.light_total, x.tpv,
+                               x.cbeg, x.er, lists, x.n1, x.first_panel, x.light, x.light_total, x.tpv,
                                x.status);
         else
             hipLaunchKernelGGL(k_count_light_lists<false>, lg, lb, 0, s, x.row_ptr, x.col, x.cptr,
-                               x.cbeg, x.er, lists, x.n1, x.p0, x.light, x.light_total, x.tpv,
+                               x.cbeg, x.er, lists, x.n1, x.first_panel, x.light, x.light_total, x.tpv,
                                x.status);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1700,7 +1705,7 @@ hipError_t launch_count(const CountArgs &x, bool per_vertex, hipStream_t s) {
     if (per_vertex && x.p0 + 1 < x.n1) {  // panels: those that fit first, on their own queue
         hipLaunchKernelGGL(k_count_panel_pv, grid, block, 0, s, x.row_ptr, x.col, x.cptr,
                            x.cbeg, x.er, x.item_v_b, x.item_off_b,
-                           x.n_items_b, x.queue_c, x.total, x.tpv, x.n1, x.p0, x.kitem_b,
+                           x.n_items_b, x.queue_c, x.total, x.tpv, x.n1, x.first_panel, x.kitem_b,
                            x.hcol, x.hbase, x.status);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1709,13 +1714,13 @@ hipError_t launch_count(const CountArgs &x, bool per_vertex, hipStream_t s) {
         hipLaunchKernelGGL(k_count<true>, grid, block, 0, s, x.row_ptr, x.col, x.cptr, x.cbeg,
                            x.er, x.item_v_a, x.item_off_a, x.n_items_a,
                            x.item_v_b, x.item_off_b, x.n_items_b, x.queue_a, x.queue_b, x.total,
-                           x.tpv, x.n1, x.p0, x.wave_bits, x.block_bits, x.block_list,
+                           x.tpv, x.n1, x.first_panel, x.wave_bits, x.block_bits, x.block_list,
                            x.kitem_a, x.kitem_b, x.hcol, x.hrow, x.hbase, x.light_total, x.status);
     else
         hipLaunchKernelGGL(k_count<false>, grid, block, 0, s, x.row_ptr, x.col, x.cptr, x.cbeg,
                            x.er, x.item_v_a, x.item_off_a, x.n_items_a,
                            x.item_v_b, x.item_off_b, x.n_items_b, x.queue_a, x.queue_b, x.total,
-                           x.tpv, x.n1, x.p0, x.wave_bits, x.block_bits, x.block_list,
+                           x.tpv, x.n1, x.first_panel, x.wave_bits, x.block_bits, x.block_list,
                            x.kitem_a, x.kitem_b, x.hcol, x.hrow, x.hbase, x.light_total, x.status);
     return hipGetLastError();
 }

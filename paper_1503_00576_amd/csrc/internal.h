@@ -182,7 +182,7 @@ struct Fill {
     uint32_t value;
 };
 struct FillList {
-    Fill a[12];
+    Fill a[13];
     int count = 0;
     void add(uint32_t *p, uint32_t value, uint64_t words) {
         if (words) a[count++] = Fill{p, words, value};
@@ -235,6 +235,7 @@ struct CountArgs {
     unsigned long long *total, *tpv;
     uint32_t n1;
     uint32_t p0;          // first rank of the panel region (n: no panels)
+    const uint32_t *first_panel;  // first rank counted in panels (from p0 on; k_panel_range)
     uint32_t wave_bits;   // wave items use a bitmap below this rank span
     uint32_t block_bits;  // workgroup items use a bitmap below this rank span (totals)
     uint32_t block_list;  // ... else an LDS list of at most this many entries (<= kBlockList)

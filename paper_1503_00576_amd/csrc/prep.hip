@@ -726,10 +726,35 @@ uint32_t row_sort_wave() { return kRowWave; }
 
 // Rank span of the union of the out-lists of every panel (ranks p0 + i * 32 .. + 31):
 // (min << 32) | max, or 0xFFFFFFFF00000000 (min > max) if all are empty.  32 lanes per panel.
+//
+// The first workgroup's last wave also finds the first panel that is used (*first, a rank; the
+// ranks are sorted by degree): vertices of at most `light` edges have light lists (count.hip) also
+// in the panel region, where a panel costs about 10 us whatever it holds.  A graph of 100,003
+// vertices by preferential attachment has 4,000 of larger degree: its per-vertex counts took 241
+// us with all 1023 panels and takes 126.  (64 ranks are looked at per step, three steps for 32,736.)
 __global__ __launch_bounds__(256) void k_panel_range(const uint32_t *__restrict__ row_ptr,
                                                      const uint32_t *__restrict__ col, uint32_t n,
                                                      uint32_t p0, uint32_t panels,
-                                                     uint64_t *__restrict__ pr) {
+                                                     const uint32_t *__restrict__ deg,
+                                                     const uint32_t *__restrict__ perm,
+                                                     uint32_t light,
+                                                     uint32_t *__restrict__ first,
+                                                     uint64_t *__restrict__ pr,
+                                                     const int32_t *__restrict__ status) {
+    if (*status) return;
+    if (blockIdx.x == 0 && threadIdx.x >= 192 && light) {
+        uint32_t lo = p0, len = n - p0;  // the first rank of a larger degree is in [lo, lo + len]
+        while (len) {
+            const uint32_t step = (len + kWave - 1) / kWave, r = lo + lane_id() * step;
+            const uint64_t larger = __ballot(r >= lo + len || deg[perm[r]] > light);
+            const uint32_t f = larger ? (uint32_t)__ffsll((long long)larger) - 1 : (uint32_t)kWave;
+            if (f == 0) break;
+            const uint32_t next = lo + (f - 1) * step + 1;
+            len = min(step - 1, lo + len - next);
+            lo = next;
+        }
+        if (lane_id() == 0) *first = p0 + (lo - p0) / 32u * 32u;
+    }
     const uint32_t i = (blockIdx.x * 256u + threadIdx.x) / 32u, j = threadIdx.x % 32u;
     const uint32_t v = p0 + i * 32u + j;
     uint32_t lo = 0xFFFFFFFFu, hi = 0;
@@ -772,10 +797,13 @@ __global__ void k_csc_keys(const uint32_t *__restrict__ col, const uint32_t *__r
                            const uint32_t *__restrict__ hrow,
                            const uint32_t *__restrict__ hstart, uint32_t hbase,
                            const uint64_t *__restrict__ pr, uint32_t mf, uint32_t n,
-                           uint32_t nblk, uint32_t p0, uint32_t kp, uint32_t h0,
+                           uint32_t nblk, uint32_t p0, const uint32_t *__restrict__ first_panel,
+                           uint32_t kp, uint32_t h0,
                            uint32_t *__restrict__ ckey, uint4 *__restrict__ eu,
                            uint16_t *__restrict__ hcol, const int32_t *__restrict__ status) {
     if (*status) return;
+    // panels are aligned to p0; the ones before the first used (k_panel_range) have lists per vertex
+    const uint32_t pfirst = *first_panel;
     // kp is a power of two; row blocks are rare (nblk > 1 only when asked for)
     const uint32_t kp_shift = __builtin_ctz(kp);
     const uint64_t e0 = (uint64_t)blockIdx.x * blockDim.x * kCscEdges + threadIdx.x;
@@ -803,7 +831,7 @@ __global__ void k_csc_keys(const uint32_t *__restrict__ col, const uint32_t *__r
 #pragma unroll
     for (uint32_t k = 0; k < kCscEdges; ++k) {
         const uint64_t e = e0 + (uint64_t)k * blockDim.x;
-        const bool pan = e + 1 < re[k] && u[k] < h0 && v[k] >= p0;
+        const bool pan = e + 1 < re[k] && u[k] < h0 && v[k] >= pfirst;
         last[k] = pan ? col[re[k] - 1] : 0u;
         r[k] = pan ? pr[(v[k] - p0) >> kp_shift] : 0xFFFFFFFF00000000ull;
     }
@@ -819,7 +847,7 @@ __global__ void k_csc_keys(const uint32_t *__restrict__ col, const uint32_t *__r
         if (e + 1 < end_u && u[k] < h0) {  // triangles whose lowest vertex is a hub: hub.hip
             uint32_t list = v[k];
             bool keep = true, run_start = false;
-            if (v[k] >= p0) {
+            if (v[k] >= pfirst) {
                 list = p0 + (((v[k] - p0) >> kp_shift) << kp_shift);
                 run_start = e == rb[k] || prv[k] < list;
                 const uint32_t lo = (uint32_t)(r[k] >> 32), hi = (uint32_t)r[k];
@@ -831,7 +859,7 @@ __global__ void k_csc_keys(const uint32_t *__restrict__ col, const uint32_t *__r
                 // where the suffix's entries >= hbase start, in col (outside the panels, in
                 // place of the mask) and in hcol; a panel suffix is high throughout
                 const uint32_t hb = v[k] >= hbase ? (uint32_t)e + 1u : min(hr[k], end_u);
-                if (v[k] < p0) mask = hb;
+                if (v[k] < pfirst) mask = hb;
                 if (hb < end_u) hpos = hs[k] + (hb - hr[k]);
                 if (run_start) {  // the run's mask: u's consecutive entries inside the panel
                     mask = 1u << (v[k] - list);
@@ -890,11 +918,11 @@ __global__ void k_csc_final(const uint32_t *__restrict__ list, uint32_t mf,
 // to the per-wave queue when the vertex's out-list fits one wave's LDS slice (as a bitmap over
 // its rank span or as a sorted list; for per-vertex counts as a list with counters),
 // otherwise to the per-workgroup queue.  Both classifications are prepared, so a prepared
-// graph can be counted either way.  Panel lists (first rank >= p0) always go to the
+// graph can be counted either way.  Panel lists (first rank >= *first_panel) always go to the
 // per-workgroup queue; light lists (at most `light` in-edges and entries) to neither.
 __global__ void k_items(const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ col,
                         const uint32_t *__restrict__ lrs, const uint32_t *__restrict__ lre,
-                        uint32_t n, uint32_t nblk, uint32_t p0,
+                        uint32_t n, uint32_t nblk, const uint32_t *__restrict__ first_panel,
                         uint32_t wave_span, uint32_t wave_list, uint32_t wave_list_pv,
                         uint32_t ka, uint32_t kb, uint32_t light,
                         uint32_t *__restrict__ ia, uint32_t *__restrict__ ib,
@@ -907,7 +935,7 @@ __global__ void k_items(const uint32_t *__restrict__ row_ptr, const uint32_t *__
     uint32_t a = 0, b = 0, apv = 0, bpv = 0;
     const uint32_t v = c < total ? (uint32_t)(c % (n + 1)) : n;
     const uint32_t cnt = v < n ? lre[c] - lrs[c] : 0u;  // in-edges
-    if (cnt > 0 && v >= p0) {
+    if (cnt > 0 && v >= *first_panel) {
         b = bpv = (cnt + kb - 1) / kb;
     } else if (cnt > 0 && row_ptr[v + 1] > row_ptr[v]) {  // N+(v) non-empty
         const uint32_t r0 = row_ptr[v], d = row_ptr[v + 1] - r0;

@@ -579,3 +579,18 @@ def test_light_lists_at_their_limits(k, row_blocks):
     n = base + 81
     check_vs_oracle(np.array(edges, dtype=np.int32), n,
                     options={"panel_ranks": 0, "row_blocks": row_blocks}, prepared_pv=True)
+
+
+@pytest.mark.parametrize("options", [None, {"panel_ranks": 96}, {"high_ranks": 0}])
+@pytest.mark.parametrize("sizes", [(60, 66, 70), (64, 65, 65, 65, 66), (10, 20, 30), (66, 80, 90),
+                                   (65,), (66,)])
+def test_first_panel_by_degree(sizes, options):
+    """Panels start at the first vertex of more than 64 edges, aligned to the panels: cliques with
+    degrees around it, none above it and none below it, with two hubs over all of them."""
+    for hubs in (0, 2):
+        edges, base = [], hubs
+        for size in sizes:
+            edges += [(base + i, base + j) for i in range(size) for j in range(i + 1, size)]
+            base += size
+        edges += [(h, x) for h in range(hubs) for x in range(h + 1, base)]
+        check_vs_oracle(np.array(edges, dtype=np.int32), base, options=options, prepared_pv=True)
