@@ -29,6 +29,8 @@
 // Per-vertex counts (T(x) = triangles through x) use sorted lists in LDS instead of bitmaps
 // so that a hit's position indexes an LDS counter: T(w) for the third vertex is flushed once
 // per item, T(u) once per in-edge, T(v) once per item and wave.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace tc {
@@ -73,6 +75,15 @@ constexpr uint32_t kLightListWindow = 512;  // staged entries per wave
 constexpr uint32_t kLightLists = 16;        // lists per wave
 constexpr int kLightThreads = 256;
 constexpr int kLightWaves = kLightThreads / kWave;
+
+// LDS access by byte address (32-bit LDS pointers)
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ uint32_t lds_word(uint32_t addr) {
+    return *(const lds_u32 *)(uintptr_t)addr;
+}
+__device__ __forceinline__ uint32_t lds_addr(const uint32_t *p) {
+    return (uint32_t)(uintptr_t)(const lds_u32 *)p;
+}
 
 // ------------------------------------------------------------------ membership probes
 
@@ -121,7 +132,41 @@ __device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t *list, uint32
     return base + ((len == 1 && list[base] < w) ? 1u : 0u);
 }
 
-struct ListProbe {  // sorted list in LDS or in global memory (d >= 1)
+// A sorted list in LDS (d >= 1, uniform): the searches of a piece's kPiece entries advance in
+// lockstep, three vector operations and one LDS read per step (byte addresses; the steps are the
+// same for all lanes).  After search(), at[i] is the address of the last entry <= wv[i] (the
+// list's start when none is) and bit kPiece - 1 - i of the result is set when it equals wv[i].
+struct LdsListProbe {
+    uint32_t list;  // LDS byte address
+    uint32_t d;
+    static constexpr bool kBranchFree = false;
+    static constexpr bool kMasked = false;
+    static constexpr bool kList = true;
+    static constexpr bool kLow = true;
+    static constexpr bool kMaskHigh = true;
+    static constexpr bool kPanel = false;
+    __device__ __forceinline__ uint32_t search(const uint32_t (&wv)[kPiece],
+                                               uint32_t (&at)[kPiece]) const {
+#pragma unroll
+        for (uint32_t i = 0; i < kPiece; ++i) at[i] = list;
+        for (uint32_t left = (uint32_t)__builtin_amdgcn_readfirstlane((int)d); left > 1;) {
+            const uint32_t half = left >> 1;
+#pragma unroll
+            for (uint32_t i = 0; i < kPiece; ++i) {
+                const uint32_t mid = at[i] + half * 4u;
+                at[i] = lds_word(mid) <= wv[i] ? mid : at[i];
+            }
+            left -= half;
+        }
+        uint32_t packed = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < kPiece; ++i)
+            packed = packed + packed + (lds_word(at[i]) == wv[i] ? 1u : 0u);
+        return packed;
+    }
+};
+
+struct ListProbe {  // sorted list in global memory (d >= 1)
     const uint32_t *list;
     uint32_t d;
     static constexpr bool kBranchFree = false;
@@ -258,12 +303,28 @@ __device__ __forceinline__ uint32_t run_batch(uint32_t eb, uint32_t e1, const Se
                     const uint32_t c = probe.count(wv[i], r);
                     hits += (i >= lo_i && i < hi_i) ? c : 0u;
                 }
+            } else if constexpr (std::is_same_v<Probe, LdsListProbe>) {
+                // per-vertex counts credit the third vertex of every hit by its position
+                uint32_t at[kPiece];
+                const uint32_t found = probe.search(wv, at);
+                const uint32_t lo_i = first > start ? first - start : 0u;
+                const uint32_t hi_i = min(stop - start, kPiece);
+                // (bit kPiece - 1 - i for entry i)
+                const uint32_t packed = found & (((1u << kPiece) - 1u) >> lo_i) &
+                                        ~((1u << (kPiece - hi_i)) - 1u);
+                hits = __popc(packed);
+                if (PV && packed) {
+#pragma unroll
+                    for (uint32_t i = 0; i < kPiece; ++i)
+                        if ((packed >> (kPiece - 1 - i)) & 1u)
+                            atomicAdd(&tcnt[(at[i] - probe.list) >> 2], 1u);
+                }
             } else if constexpr (Probe::kList) {
+                // a list in memory:
                 // the piece's 16 lookups as binary searches in lockstep (the list length is
                 // uniform), so that every step issues independent reads; position pos is the
                 // first entry >= w, and w is in the list iff that entry equals w.  Per-vertex
-                // counts credit the third vertex of every hit: an LDS counter by position, or
-                // a global counter when the list is not in LDS.
+                // counts credit the third vertex of every hit.
                 uint32_t base[kPiece];
 #pragma unroll
                 for (uint32_t i = 0; i < kPiece; ++i) base[i] = 0;
@@ -288,10 +349,7 @@ __device__ __forceinline__ uint32_t run_batch(uint32_t eb, uint32_t e1, const Se
                 if (PV && packed) {
 #pragma unroll
                     for (uint32_t i = 0; i < kPiece; ++i) {
-                        if ((packed >> i) & 1u) {
-                            if (tcnt) atomicAdd(&tcnt[base[i]], 1u);
-                            else atomicAdd(&tpv[wv[i]], 1ull);
-                        }
+                        if ((packed >> i) & 1u) atomicAdd(&tpv[wv[i]], 1ull);
                     }
                 }
             } else if constexpr (!PV && Probe::kBranchFree) {
@@ -330,15 +388,6 @@ __device__ __forceinline__ uint32_t run_batch(uint32_t eb, uint32_t e1, const Se
         wave_lds_sync();
     }
     return hits_total;
-}
-
-// LDS access by byte address (32-bit LDS pointers)
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-__device__ __forceinline__ uint32_t lds_word(uint32_t addr) {
-    return *(const lds_u32 *)(uintptr_t)addr;
-}
-__device__ __forceinline__ uint32_t lds_addr(const uint32_t *p) {
-    return (uint32_t)(uintptr_t)(const lds_u32 *)p;
 }
 
 // ------------------------------------------------------------------ totals streaming
@@ -416,7 +465,11 @@ __device__ __forceinline__ uint32_t masked_hits(const Probe &probe, const uint32
                                                 uint32_t start, uint32_t first, uint32_t stop) {
     const uint32_t mask = piece_mask(start, first, stop);
     uint32_t packed = 0;
-    if constexpr (Probe::kList) {
+    if constexpr (std::is_same_v<Probe, LdsListProbe>) {
+        uint32_t at[kPiece];
+        // (bit kPiece - 1 - i for entry i)
+        return __popc(probe.search(wv, at) & (__brev(mask) >> (32u - kPiece)));
+    } else if constexpr (Probe::kList) {
         // the piece's lookups as binary searches in lockstep (the list length is uniform)
         uint32_t base[kPiece];
 #pragma unroll
@@ -1079,7 +1132,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
                 cnt += stream_t(first, it.e1, step, segs, col, hcol, hbase, probe, ws);
             }
         } else if (mode == 1) {
-            const ListProbe probe{s_mem, it.d};
+            const LdsListProbe probe{lds_addr(s_mem), it.d};
             uint32_t *tc = PV ? s_mem + kBlockListPV : nullptr;
             if constexpr (PV) {
                 for (uint32_t eb = first; eb < it.e1; eb += step)
@@ -1165,7 +1218,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
                 if (dlo > 0) {
                     for (uint32_t i = lane; i < dlo; i += kWave) mem[i] = col[it.r0 + i];
                     wave_lds_sync();
-                    const ListProbe lp{mem, dlo};
+                    const LdsListProbe lp{lds_addr(mem), dlo};
                     cnt += stream_t<1>(it.e0, it.e1, kWave, segs, col, hcol, hbase, lp, ws);
                     for (uint32_t i = lane; i < dlo; i += kWave) mem[i] = 0;
                     wave_lds_sync();
@@ -1184,7 +1237,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
             } else {  // a wide span, but a list that fits the slice (see k_items)
                 for (uint32_t i = lane; i < it.d; i += kWave) mem[i] = col[it.r0 + i];
                 wave_lds_sync();
-                const ListProbe probe{mem, it.d};
+                const LdsListProbe probe{lds_addr(mem), it.d};
                 cnt += stream_t(it.e0, it.e1, kWave, segs, col, hcol, hbase, probe, ws);
                 for (uint32_t i = lane; i < it.d; i += kWave) mem[i] = 0;
             }
@@ -1193,7 +1246,7 @@ __global__ __launch_bounds__(kThreads) void k_count(
             uint32_t *list = mem, *tc = mem + kWaveListPV;
             for (uint32_t i = lane; i < it.d; i += kWave) list[i] = col[it.r0 + i];
             wave_lds_sync();
-            const ListProbe probe{list, it.d};
+            const LdsListProbe probe{lds_addr(list), it.d};
             for (uint32_t eb = it.e0; eb < it.e1; eb += kWave)
                 cnt += run_batch<true>(eb, it.e1, segs, col, probe, ws, tc, tpv);
             for (uint32_t i = lane; i < it.d; i += kWave) {
@@ -1281,7 +1334,7 @@ __global__ __launch_bounds__(kThreads) void k_count_u(const BatchKernelArgs a) {
             uint32_t *list = mem, *tc = PV ? mem + kWaveListPV : nullptr;
             for (uint32_t i = lane; i < d; i += kWave) list[i] = fcol[r0 + i];
             wave_lds_sync();
-            const ListProbe probe{list, d};
+            const LdsListProbe probe{lds_addr(list), d};
             for (uint32_t eb = e0; eb < e1; eb += kWave)
                 cnt += run_batch<PV>(eb, e1, segs, fcol, probe, ws, tc, tpv);
             for (uint32_t i = lane; i < d; i += kWave) {

@@ -66,42 +66,46 @@ static_assert(kScanRows * kScanWaves == kWave, "one wave scans the row-wave tota
 
 // What a scan adds up: an array, or values formed from the arrays behind them, so that they need
 // no launch and no array of their own.  at(y, i, N): elements i .. i + 3 of sequence y (0 from N on).
+// (in 16-byte loads: with one 4-byte load per element a scan of 100,003 rows took 10 us instead
+// of 3)
+__device__ __forceinline__ uint4 load_four(const uint32_t *in, uint64_t i, uint64_t N) {
+    if (i + 4 <= N) return *reinterpret_cast<const uint4 *>(in + i);
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    if (i < N) x.x = in[i];
+    if (i + 1 < N) x.y = in[i + 1];
+    if (i + 2 < N) x.z = in[i + 2];
+    return x;
+}
 struct ScanArrays {  // sequence y: an array (16-byte aligned)
     const uint32_t *p[4];
     __device__ __forceinline__ uint4 at(uint32_t y, uint64_t i, uint64_t N) const {
-        const uint32_t *in = p[y];
-        if (i + 4 <= N) return *reinterpret_cast<const uint4 *>(in + i);
-        uint4 x = make_uint4(0u, 0u, 0u, 0u);
-        if (i < N) x.x = in[i];
-        if (i + 1 < N) x.y = in[i + 1];
-        if (i + 2 < N) x.z = in[i + 2];
-        return x;
+        return load_four(p[y], i, N);
     }
 };
-template <class F>
-__device__ __forceinline__ uint4 four(const F f, uint64_t i, uint64_t N) {
-    return make_uint4(i < N ? f(i) : 0u, i + 1 < N ? f(i + 1) : 0u, i + 2 < N ? f(i + 2) : 0u,
-                      i + 3 < N ? f(i + 3) : 0u);
-}
 struct ScanRows {  // row lengths from the rows' bounds (both 0 for an empty row)
     const uint32_t *rs, *re;
     __device__ __forceinline__ uint4 at(uint32_t, uint64_t i, uint64_t N) const {
-        return four([&](uint64_t r) { return re[r] - rs[r]; }, i, N);
+        const uint4 a = load_four(rs, i, N), b = load_four(re, i, N);
+        return make_uint4(b.x - a.x, b.y - a.y, b.z - a.z, b.w - a.w);
     }
 };
 // Room of every row's entries >= hbase in hcol: none for a row without such entries, else their
 // number rounded up to a multiple of 8, plus `pad` zeros (the counting kernel's pieces, read
-// from 8-aligned positions inside the row's part, never leave it).
+// from 8-aligned positions inside the row's part, never leave it).  row_ptr has N + 1 elements.
 struct ScanHigh {
     const uint32_t *row_ptr, *hrow;
     uint32_t pad;
+    __device__ __forceinline__ uint32_t room(uint32_t end, uint32_t h) const {
+        return h != ~0u ? ((end - h + 7u) & ~7u) + pad : 0u;
+    }
     __device__ __forceinline__ uint4 at(uint32_t, uint64_t i, uint64_t N) const {
-        return four(
-            [&](uint64_t r) {
-                const uint32_t h = hrow[r];
-                return h != ~0u ? ((row_ptr[r + 1] - h + 7u) & ~7u) + pad : 0u;
-            },
-            i, N);
+        if (i >= N) return make_uint4(0u, 0u, 0u, 0u);
+        const uint4 h = load_four(hrow, i, N), r = load_four(row_ptr, i, N + 1);
+        uint4 x = make_uint4(room(r.y, h.x), 0u, 0u, 0u);
+        if (i + 1 < N) x.y = room(r.z, h.y);
+        if (i + 2 < N) x.z = room(r.w, h.z);
+        if (i + 3 < N) x.w = room(row_ptr[i + 4], h.w);
+        return x;
     }
 };
 struct ScanOut {
