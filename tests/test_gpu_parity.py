@@ -594,3 +594,19 @@ def test_first_panel_by_degree(sizes, options):
             base += size
         edges += [(h, x) for h in range(hubs) for x in range(h + 1, base)]
         check_vs_oracle(np.array(edges, dtype=np.int32), base, options=options, prepared_pv=True)
+
+
+@pytest.mark.parametrize("row_blocks", [1, 3])
+@pytest.mark.parametrize("k", [66, 300, 510, 513, 516, 767, 770])
+def test_per_vertex_wave_items(k, row_blocks):
+    """Per-vertex counts of middle vertices below the panels (panel_ranks = 0) with lists of up to
+    k entries: a clique of k (every entry a hit), a sparse random graph (few hits) and a star
+    over both, with vertices on both sides of the highest 768 ranks."""
+    rng = np.random.default_rng(k)
+    edges = [(i, j) for i in range(k) for j in range(i + 1, k)]
+    m = 400
+    mask = np.triu(rng.random((m, m)) < 0.35, 1)
+    edges += [(k + i, k + j) for i, j in zip(*np.nonzero(mask))]
+    edges += [(k + m, i) for i in range(k + m)]
+    check_vs_oracle(np.array(edges, dtype=np.int32), k + m + 1,
+                    options={"panel_ranks": 0, "row_blocks": row_blocks}, prepared_pv=True)
