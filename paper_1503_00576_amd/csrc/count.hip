@@ -45,11 +45,15 @@ constexpr uint32_t kLdsWords = 32768;                 // 128 KiB per workgroup
 constexpr uint32_t kSliceWords = kLdsWords / kWaves;  // 8 KiB per wave
 constexpr uint32_t kWaveBits = kSliceWords * 32 - 32; // wave bitmap: span < 65504
 constexpr uint32_t kWaveListPV = kSliceWords / 2;     // per-vertex: list + counters per wave
+// per-vertex wave items with a bit filter: list, counters, filter and hit queue in a quarter of
+// the slice each
+constexpr uint32_t kFilterList = kSliceWords / 4;
+constexpr uint32_t kFilterBits = kFilterList * 32;
+constexpr uint32_t kHitQueue = kFilterList / 2;       // (entry, segment) pairs
 // per-vertex counts: the highest ranks' credits as third vertices are summed in LDS per
 // workgroup, in what LDS is left.  Nearly every wave item credits the very highest of them, and
-// atomics on one address take 11 ns each: of the 3.8 ms of 247,000 items at R-MAT 22, 2.7.
-// Per-vertex counts at R-MAT 20, 21 and 23: 1.47, 3.25 and 30.4 ms before, 1.21, 2.79 and 28.4
-// with the sums
+// atomics on one address take 11 ns each, 2.7 ms for the 247,000 items at R-MAT 22.  Per-vertex
+// counts at R-MAT 20, 21 and 23: 1.47, 3.25 and 30.4 ms before, 1.21, 2.79 and 28.4 with the sums
 constexpr uint32_t kHotRanks = 768;
 constexpr uint32_t kBlockBits = kLdsWords * 32 - 32;  // workgroup bitmap: span < 1048544
 constexpr uint32_t kBlockList = kLdsWords;            // workgroup sorted list
@@ -169,6 +173,16 @@ struct LdsListProbe {
         for (uint32_t i = 0; i < kPiece; ++i)
             packed = packed + packed + (lds_word(at[i]) == wv[i] ? 1u : 0u);
         return packed;
+    }
+    // one entry per lane: the address of the last entry <= w
+    __device__ __forceinline__ uint32_t search_one(uint32_t w) const {
+        uint32_t at = list;
+        for (uint32_t left = (uint32_t)__builtin_amdgcn_readfirstlane((int)d); left > 1;) {
+            const uint32_t half = left >> 1, mid = at + half * 4u;
+            at = lds_word(mid) <= w ? mid : at;
+            left -= half;
+        }
+        return at;
     }
 };
 
@@ -863,6 +877,107 @@ __device__ __forceinline__ uint32_t run_panel_pv(uint32_t eb, uint32_t e1,
     return hits_total;
 }
 
+// Per-vertex wave items with N+(v) of at most kFilterList entries.  Nearly every entry streamed
+// is no hit, and a lockstep search costs log2(d) LDS reads and three times that many vector
+// operations per entry (at R-MAT 22, 800 LDS and 2,780 vector instructions per item, 290 and
+// 1,500 with the filter; per-vertex counts 11.05 -> 10.37 ms with the preprocessing, at R-MAT 23
+// 28.4 -> 25.3 ms without; now 3.9 TB/s of missed lines at R-MAT 22).  So the slice also holds a filter, bit w mod kFilterBits of every
+// w in N+(v): one read per entry passes the hits and d in kFilterBits of the others.  The
+// entries passed are queued with their segments, and every lane searches one of them per step.
+// A round that passes more entries than the queue holds is searched in lockstep.  Longer lists
+// (0.3 percent of the items at R-MAT 22) keep the lockstep search: the slice has no room for more.
+// mem: list, counters, filter (zero but for N+(v)'s bits) and queue.
+__device__ __forceinline__ uint32_t run_filter_pv(uint32_t eb, uint32_t e1,
+                                                  const InEdgeSegs &segs,
+                                                  const uint32_t *__restrict__ col,
+                                                  uint32_t *mem, uint32_t d, WaveScratch &ws,
+                                                  unsigned long long *__restrict__ tpv) {
+    const uint32_t lane = lane_id();
+    uint32_t *tc = mem + kFilterList;
+    const uint32_t *filter = mem + 2 * kFilterList;
+    uint2 *queue = reinterpret_cast<uint2 *>(mem + 3 * kFilterList);
+    const LdsListProbe probe{lds_addr(mem), d};
+    const SegRec r = eb + lane < e1 ? segs.rec(eb + lane) : SegRec{0u, 0u, 0u, 0u, 0u};
+    const uint32_t a0 = r.b & ~3u;
+    const uint32_t p = r.en > r.b ? (r.en - a0 + kPiece - 1) / kPiece : 0u;
+    const uint32_t incl = wave_incl_scan(p);
+    const uint32_t Q = wave_bcast(incl, kWave - 1);
+    const uint32_t my_off = incl - p;
+    ws.off[lane] = 0u;  // the rounds' marker table
+    ws.beg[lane] = a0;
+    ws.first[lane] = r.b;
+    ws.end[lane] = r.en;
+    ws.cnt[lane] = 0u;
+    ws.tag[lane] = r.owner;
+    wave_lds_sync();
+    uint32_t hits = 0, carry = 0, round = 0;
+    for (uint32_t q0 = 0; q0 < Q; q0 += kWave) {
+        const uint32_t k = round_owner(ws.off, my_off, p, q0, ++round, carry) - 1u;
+        const uint32_t off_k = wave_bcast_from(my_off, k);
+        const uint32_t q = q0 + lane;
+        uint32_t wv[kPiece];
+#pragma unroll
+        for (uint32_t i = 0; i < kPiece; ++i) wv[i] = 0u;
+        uint32_t packed = 0;  // bit kPiece - 1 - i for entry i
+        if (q < Q) {
+            const uint32_t start = ws.beg[k] + (q - off_k) * kPiece;
+            const uint32_t first = ws.first[k], stop = ws.end[k];
+            const uint4 *p4 = reinterpret_cast<const uint4 *>(col + start);
+#pragma unroll
+            for (uint32_t j = 0; j < kPiece / 4; ++j) {
+                const uint4 x = p4[j];
+                wv[4 * j] = x.x;
+                wv[4 * j + 1] = x.y;
+                wv[4 * j + 2] = x.z;
+                wv[4 * j + 3] = x.w;
+            }
+#pragma unroll
+            for (uint32_t i = 0; i < kPiece; ++i)
+                packed = packed + packed +
+                         __builtin_amdgcn_ubfe(filter[(wv[i] & (kFilterBits - 1u)) >> 5], wv[i],
+                                               1u);
+            const uint32_t lo_i = first > start ? first - start : 0u;
+            const uint32_t hi_i = min(stop - start, kPiece);
+            packed &= (((1u << kPiece) - 1u) >> lo_i) & ~((1u << (kPiece - hi_i)) - 1u);
+        }
+        const uint32_t np = (uint32_t)__popc(packed);
+        const uint32_t upto = wave_incl_scan(np);
+        const uint32_t passed = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+        if (passed <= kHitQueue) {
+            uint32_t at = upto - np;
+#pragma unroll
+            for (uint32_t i = 0; i < kPiece; ++i)
+                if ((packed >> (kPiece - 1 - i)) & 1u) queue[at++] = make_uint2(wv[i], k);
+            wave_lds_sync();
+            for (uint32_t j = lane; j < passed; j += kWave) {
+                const uint2 x = queue[j];
+                const uint32_t pos = probe.search_one(x.x);
+                if (lds_word(pos) == x.x) {
+                    ++hits;
+                    atomicAdd(&tc[(pos - probe.list) >> 2], 1u);
+                    atomicAdd(&ws.cnt[x.y], 1u);
+                }
+            }
+            wave_lds_sync();
+        } else {
+            uint32_t at[kPiece];
+            packed &= probe.search(wv, at);
+            if (packed) {
+                hits += (uint32_t)__popc(packed);
+                atomicAdd(&ws.cnt[k], (uint32_t)__popc(packed));
+#pragma unroll
+                for (uint32_t i = 0; i < kPiece; ++i)
+                    if ((packed >> (kPiece - 1 - i)) & 1u)
+                        atomicAdd(&tc[(at[i] - probe.list) >> 2], 1u);
+            }
+        }
+    }
+    wave_lds_sync();
+    if (ws.cnt[lane]) atomicAdd(&tpv[ws.tag[lane]], (unsigned long long)ws.cnt[lane]);
+    wave_lds_sync();
+    return hits;
+}
+
 // first position in hcol[b, e) (ascending) whose entry is >= x
 __device__ __forceinline__ uint32_t hcol_lower_bound(const uint16_t *__restrict__ hcol,
                                                      uint32_t b, uint32_t e, uint32_t x) {
@@ -1264,16 +1379,36 @@ __global__ __launch_bounds__(kThreads) void k_count(
             }
             wave_lds_sync();
         } else {
-            uint32_t *list = mem, *tc = mem + kWaveListPV;
-            for (uint32_t i = lane; i < it.d; i += kWave) list[i] = col[it.r0 + i];
-            wave_lds_sync();
-            const LdsListProbe probe{lds_addr(list), it.d};
-            for (uint32_t eb = it.e0; eb < it.e1; eb += kWave)
-                cnt += run_batch<true>(eb, it.e1, segs, col, probe, ws, tc, tpv);
+            // with the filter up to kFilterList entries, else list and counters in half a slice
+            // each; the counters and the filter are zero between items
+            const bool filtered = it.d <= kFilterList;
+            uint32_t *list = mem, *tc = mem + (filtered ? kFilterList : kWaveListPV);
+            uint32_t *filter = mem + 2 * kFilterList;
             for (uint32_t i = lane; i < it.d; i += kWave) {
-                uint32_t c = tc[i];
+                const uint32_t x = col[it.r0 + i];
+                list[i] = x;
+                if (filtered)
+                    atomicOr(&filter[(x & (kFilterBits - 1u)) >> 5], 1u << (x & 31u));
+                else
+                    tc[i] = 0;  // (the hit queue's words)
+            }
+            wave_lds_sync();
+            if (filtered) {
+                for (uint32_t eb = it.e0; eb < it.e1; eb += kWave)
+                    cnt += run_filter_pv(eb, it.e1, segs, col, mem, it.d, ws, tpv);
+            } else {
+                const LdsListProbe probe{lds_addr(list), it.d};
+                for (uint32_t eb = it.e0; eb < it.e1; eb += kWave)
+                    cnt += run_batch<true>(eb, it.e1, segs, col, probe, ws, tc, tpv);
+            }
+            for (uint32_t i = lane; i < it.d; i += kWave) {
+                const uint32_t x = list[i], c = tc[i];
+                if (filtered)
+                    filter[(x & (kFilterBits - 1u)) >> 5] = 0;
+                else
+                    list[i] = 0;  // (the counters of filtered items)
                 if (c) {
-                    credit_third(list[i], c, hot0, s_hot, tpv);
+                    credit_third(x, c, hot0, s_hot, tpv);
                     tc[i] = 0;
                 }
             }
