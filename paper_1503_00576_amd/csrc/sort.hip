@@ -15,6 +15,8 @@
 // which saves the upsweep's read of every key and the scan per pass.  A tile only waits on
 // tiles that started before it and publish before they wait themselves, so the waits end;
 // every wait is also bounded and reports TC_E_HIP if the bound is ever reached.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace tc {
@@ -235,14 +237,15 @@ constexpr int kSortItems = 16;
 constexpr int kSortWaves = kSortThreads / kWave;     // 8
 constexpr int kSortTile = kSortThreads * kSortItems;  // 8192 keys per tile
 
-// Lanes holding the same 8-bit digit as the calling lane: returns the mask of such (valid)
+// Lanes holding the same kBits-bit digit as the calling lane: returns the mask of such (valid)
 // lanes.  Per bit: m = all ones where the lane's bit is set, the ballot of that bit, and
 // peers &= ~(ballot ^ m) on both halves.
+template <int kBits>
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
     const uint64_t v = __ballot(valid);
     uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < kBits; ++b) {
         const uint32_t m = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
         const uint64_t bb = __ballot(m != 0u);
         lo &= ~((uint32_t)bb ^ m);
@@ -344,64 +347,78 @@ __device__ __forceinline__ uint32_t load_tile_keys(const Src in, uint32_t count,
     return vmask;
 }
 
-// Per-wave digit counts of the wave's rows into cnt[256] (the wave's own row of counters,
+// Digits of 8 bits, or 9 where that saves a pass (digit_bits).  With counters of 16 bits the
+// state of a tile with 512 digits (76 KB; a tile has 8192 keys) leaves room for two workgroups
+// per CU as with 256.
+template <int kBits>
+using TileCount = std::conditional_t<kBits == 8, uint32_t, uint16_t>;
+
+// Per-wave digit counts of the wave's rows into cnt[] (the wave's own row of counters,
 // zero on entry), and each key's rank among the wave's earlier keys of the same digit.
+template <int kBits>
 __device__ __forceinline__ void wave_rank_rows(const uint64_t (&keys)[kSortItems], uint32_t vmask,
-                                               int shift, uint32_t mask, uint32_t *cnt,
+                                               int shift, uint32_t mask, TileCount<kBits> *cnt,
                                                uint32_t (&ranks)[kSortItems]) {
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
         const bool valid = (vmask >> r) & 1u;
         const uint32_t d = (uint32_t)(keys[r] >> shift) & mask;
-        const uint64_t peers = match_digit(d, valid);
+        const uint64_t peers = match_digit<kBits>(d, valid);
         const uint32_t below = lanes_below(peers);
         const uint32_t prev = valid ? cnt[d] : 0u;
         ranks[r] = prev + below;
-        if (valid && below == 0) cnt[d] = prev + (uint32_t)__popcll(peers);
+        if (valid && below == 0) cnt[d] = (TileCount<kBits>)(prev + (uint32_t)__popcll(peers));
         wave_lds_sync();  // this row's counter updates before the next row's reads
     }
 }
 
 // Shared state of one tile's stable placement in digit order.
+template <int kBits>
 struct SortTileLds {
+    static constexpr uint32_t kDigits = 1u << kBits;
+    static_assert(kDigits <= kSortThreads, "one thread per digit");
     uint64_t stage[kSortTile];
-    uint32_t wcnt[kSortWaves][256];  // per-wave digit counts, then per-wave digit offsets
-    uint32_t loc[256];               // tile-local start of each digit
-    uint32_t glob[256];              // global start minus local start of each digit
-    uint32_t dsum[4];                // per-wave sums of the digit scan (digits by 4 waves)
+    // per-wave digit counts, then per-wave digit offsets
+    TileCount<kBits> wcnt[kSortWaves][kDigits];
+    uint32_t loc[kDigits];           // tile-local start of each digit
+    uint32_t glob[kDigits];          // global start minus local start of each digit
+    uint32_t dsum[kDigits / kWave];  // per-wave sums of the digit scan
     uint32_t gsum[4];                // the same for the global digit counts (single sweep)
     uint32_t gwave[kSortWaves];      // per-wave sums of the global counts (few tiles)
     uint32_t total;                  // keys of the tile that take part
 };
 
 // Block part of the placement (all threads, after the waves' counts are in wcnt): turns wcnt
-// into per-wave digit offsets, fills loc, and returns the tile's count of digit t (t < 256).
-__device__ __forceinline__ uint32_t tile_digit_offsets(SortTileLds &L) {
+// into per-wave digit offsets, fills loc, and returns the tile's count of digit t.
+template <int kBits>
+__device__ __forceinline__ uint32_t tile_digit_offsets(SortTileLds<kBits> &L) {
+    constexpr uint32_t kDigits = 1u << kBits;
     const uint32_t t = threadIdx.x;
     __syncthreads();
     uint32_t c = 0;
-    if (t < 256) {
+    if (t < kDigits) {
 #pragma unroll
         for (int k = 0; k < kSortWaves; ++k) {
             const uint32_t x = L.wcnt[k][t];
-            L.wcnt[k][t] = c;
+            L.wcnt[k][t] = (TileCount<kBits>)c;
             c += x;
         }
     }
-    const uint32_t incl = wave_incl_scan(t < 256 ? c : 0u);
-    if (t < 256 && lane_id() == kWave - 1) L.dsum[t / kWave] = incl;
+    const uint32_t incl = wave_incl_scan(t < kDigits ? c : 0u);
+    if (t < kDigits && lane_id() == kWave - 1) L.dsum[t / kWave] = incl;
     __syncthreads();
-    if (t < 256) {
+    if (t < kDigits) {
         uint32_t before = 0;
         for (uint32_t k = 0; k < t / kWave; ++k) before += L.dsum[k];
         L.loc[t] = before + incl - c;
-        if (t == 255) L.total = before + incl;
+        if (t == kDigits - 1) L.total = before + incl;
     }
     return c;
 }
 
 // Places the wave's keys in L.stage (after tile_digit_offsets and a barrier).
-__device__ __forceinline__ void stage_keys(SortTileLds &L, const uint64_t (&keys)[kSortItems],
+template <int kBits>
+__device__ __forceinline__ void stage_keys(SortTileLds<kBits> &L, const uint64_t (&keys)[kSortItems],
                                            const uint32_t (&ranks)[kSortItems], uint32_t vmask,
                                            uint32_t w, int shift, uint32_t mask) {
 #pragma unroll
@@ -415,8 +432,8 @@ __device__ __forceinline__ void stage_keys(SortTileLds &L, const uint64_t (&keys
 
 // Writes the staged tile (L.total keys): consecutive threads write consecutive positions of
 // one digit's run (L.glob[d] + j is the output position of staged key j of digit d).
-template <class Dst>
-__device__ __forceinline__ void write_staged(const SortTileLds &L, const Dst out, uint32_t count,
+template <int kBits, class Dst>
+__device__ __forceinline__ void write_staged(const SortTileLds<kBits> &L, const Dst out, uint32_t count,
                                              int shift, uint32_t mask, int32_t *status) {
     const uint32_t ntile = L.total;
 #pragma unroll
@@ -437,16 +454,16 @@ __device__ __forceinline__ void write_staged(const SortTileLds &L, const Dst out
     }
 }
 
-template <bool kFull, class Src>
+template <int kBits, bool kFull, class Src>
 __device__ __forceinline__ void hist_tile(const Src in, uint32_t count, int shift,
                                           uint32_t mask, uint32_t *__restrict__ hist,
                                           uint32_t tiles, uint32_t tile,
-                                          uint32_t (&h)[kSortWaves][256]) {
+                                          uint32_t (&h)[kSortWaves][1 << kBits]) {
     const uint32_t t = threadIdx.x, w = t / kWave;
     const uint64_t base = (uint64_t)tile * kSortTile;
     uint64_t keys[kSortItems];
     const uint32_t vmask = load_tile_keys<kFull>(in, count, base, w, keys);
-    for (uint32_t k = lane_id(); k < 256; k += kWave) h[w][k] = 0;
+    for (uint32_t k = lane_id(); k < 1u << kBits; k += kWave) h[w][k] = 0;
     wave_lds_sync();
     // counts only (no ranks): the keys of a row that share the first lane's digit are added
     // with one LDS atomic, the others one atomic each, into the wave's own counters (skewed
@@ -462,7 +479,7 @@ __device__ __forceinline__ void hist_tile(const Src in, uint32_t count, int shif
         if (valid && d != d0) atomicAdd(&h[w][d], 1u);
     }
     __syncthreads();
-    if (t < 256) {
+    if (t < 1u << kBits) {
         uint32_t sum = 0;
 #pragma unroll
         for (int k = 0; k < kSortWaves; ++k) sum += h[k][t];
@@ -472,7 +489,7 @@ __device__ __forceinline__ void hist_tile(const Src in, uint32_t count, int shif
 
 // dcount (nullable): the number of keys, read from the device (a bound set by an earlier pass
 // that dropped keys; count is then the capacity the grid was sized for)
-template <class Src>
+template <int kBits, class Src>
 __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const Src in, uint32_t count,
                                                              const uint32_t *__restrict__ dcount,
                                                              int shift, uint32_t nbits,
@@ -481,13 +498,13 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const Src in, uint3
                                                              const int32_t *__restrict__ status) {
     if (status && *status) return;
     if (dcount) count = min(count, *dcount);
-    __shared__ uint32_t h[kSortWaves][256];
+    __shared__ uint32_t h[kSortWaves][1 << kBits];
     const uint32_t tile = xcd_tile(blockIdx.x, tiles);
     const uint32_t mask = (1u << nbits) - 1u;
     if ((uint64_t)(tile + 1) * kSortTile <= count)
-        hist_tile<true>(in, count, shift, mask, hist, tiles, tile, h);
+        hist_tile<kBits, true>(in, count, shift, mask, hist, tiles, tile, h);
     else
-        hist_tile<false>(in, count, shift, mask, hist, tiles, tile, h);
+        hist_tile<kBits, false>(in, count, shift, mask, hist, tiles, tile, h);
 }
 
 // How a scatter finds where its tile's digit runs start.  Few tiles (at most kRawTiles): from the
@@ -501,47 +518,53 @@ constexpr uint32_t kRawTiles = 128;
 // Global minus local start of every digit into L.glob (all threads; loc filled).
 // (kFew: at most kRawTiles tiles; an instance of its own, since its registers would halve the
 // occupancy of the other)
-template <bool kFew>
-__device__ __forceinline__ void tile_digit_starts(SortTileLds &L, const uint32_t *__restrict__ table,
+template <int kBits, bool kFew>
+__device__ __forceinline__ void tile_digit_starts(SortTileLds<kBits> &L,
+                                                  const uint32_t *__restrict__ table,
                                                   uint32_t tiles, uint32_t tile) {
+    constexpr uint32_t kDigits = 1u << kBits;
     const uint32_t t = threadIdx.x;
     if constexpr (!kFew) {
-        if (t < 256) L.glob[t] = table[(uint64_t)t * tiles + tile] - L.loc[t];
+        if (t < kDigits) L.glob[t] = table[(uint64_t)t * tiles + tile] - L.loc[t];
     } else if (tiles == 1) {
-        if (t < 256) L.glob[t] = 0;
+        if (t < kDigits) L.glob[t] = 0;
     } else {
-        // a wave sums 32 digits' rows, lanes along the tiles; lane i keeps its digit i's sums
-        constexpr uint32_t kDigits = 256 / kSortWaves;
+        // a wave sums its digits' rows, 32 at a time, lanes along the tiles; lane i keeps its
+        // digit i's sums
+        constexpr uint32_t kMine = kDigits / kSortWaves, kStep = 32;
         const uint32_t w = t / kWave, lane = lane_id();
         uint32_t sum = 0, below = 0;
-        for (uint32_t k0 = 0; k0 < tiles; k0 += kWave) {
-            const uint32_t k = k0 + lane;
-            uint32_t x[kDigits];  // (all loads in flight together)
+        for (uint32_t i0 = 0; i0 < kMine; i0 += kStep) {
+            for (uint32_t k0 = 0; k0 < tiles; k0 += kWave) {
+                const uint32_t k = k0 + lane;
+                uint32_t x[kStep];  // (all loads in flight together)
 #pragma unroll
-            for (uint32_t i = 0; i < kDigits; ++i)
-                x[i] = k < tiles ? table[(w * kDigits + i) * tiles + k] : 0u;
+                for (uint32_t i = 0; i < kStep; ++i)
+                    x[i] = k < tiles ? table[(w * kMine + i0 + i) * tiles + k] : 0u;
 #pragma unroll
-            for (uint32_t i = 0; i < kDigits; ++i) {
-                const uint32_t in = wave_incl_scan(x[i]);
-                const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)in, kWave - 1);
-                // the tiles before this one: all of the 64, or those up to its own lane
-                const uint32_t part =
-                    tile >= k0 + kWave ? all
-                    : tile > k0 ? (uint32_t)__builtin_amdgcn_readlane((int)in, (int)(tile - 1 - k0))
-                                : 0u;
-                if (lane == i) {
-                    sum += all;
-                    below += part;
+                for (uint32_t i = 0; i < kStep; ++i) {
+                    const uint32_t in = wave_incl_scan(x[i]);
+                    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)in, kWave - 1);
+                    // the tiles before this one: all of the 64, or those up to its own lane
+                    const uint32_t part =
+                        tile >= k0 + kWave ? all
+                        : tile > k0
+                            ? (uint32_t)__builtin_amdgcn_readlane((int)in, (int)(tile - 1 - k0))
+                            : 0u;
+                    if (lane == i0 + i) {
+                        sum += all;
+                        below += part;
+                    }
                 }
             }
         }
-        const uint32_t incl = wave_incl_scan(sum);  // (lanes from kDigits on hold 0)
+        const uint32_t incl = wave_incl_scan(sum);  // (lanes from kMine on hold 0)
         if (lane == kWave - 1) L.gwave[w] = incl;
         __syncthreads();
         uint32_t before = 0;
         for (uint32_t k = 0; k < w; ++k) before += L.gwave[k];
-        if (lane < kDigits) {
-            const uint32_t d = w * kDigits + lane;
+        if (lane < kMine) {
+            const uint32_t d = w * kMine + lane;
             L.glob[d] = before + incl - sum + below - L.loc[d];
         }
     }
@@ -551,46 +574,47 @@ __device__ __forceinline__ void tile_digit_starts(SortTileLds &L, const uint32_t
 // tile-local counting sort), then written out digit run by digit run.
 //   table: digit-major per-tile digit counts, scanned when there are more than kRawTiles tiles
 //   total: nullable, receives the number of keys of all tiles
-template <bool kFull, bool kFew, class Src, class Dst>
+template <int kBits, bool kFull, bool kFew, class Src, class Dst>
 __device__ __forceinline__ void scatter_tile(const Src in, const Dst out, uint32_t count,
                                              int shift, uint32_t mask,
                                              const uint32_t *__restrict__ table, uint32_t tiles,
                                              uint32_t tile, uint32_t *__restrict__ total,
-                                             SortTileLds &L) {
+                                             SortTileLds<kBits> &L) {
     const uint32_t t = threadIdx.x, w = t / kWave;
     const uint64_t base = (uint64_t)tile * kSortTile;
     uint64_t keys[kSortItems];
     const uint32_t vmask = load_tile_keys<kFull>(in, count, base, w, keys);
-    for (uint32_t k = lane_id(); k < 256; k += kWave) L.wcnt[w][k] = 0;
+    for (uint32_t k = lane_id(); k < 1u << kBits; k += kWave) L.wcnt[w][k] = 0;
     wave_lds_sync();
     uint32_t ranks[kSortItems];
-    wave_rank_rows(keys, vmask, shift, mask, L.wcnt[w], ranks);
+    wave_rank_rows<kBits>(keys, vmask, shift, mask, L.wcnt[w], ranks);
     const uint32_t c = tile_digit_offsets(L);
     __syncthreads();
-    tile_digit_starts<kFew>(L, table, tiles, tile);
+    tile_digit_starts<kBits, kFew>(L, table, tiles, tile);
     __syncthreads();
     // the last tile's last run ends at the number of keys
-    if (total && tile == tiles - 1 && t == 255) *total = L.glob[255] + L.loc[255] + c;
+    constexpr uint32_t kLast = (1u << kBits) - 1u;
+    if (total && tile == tiles - 1 && t == kLast) *total = L.glob[kLast] + L.loc[kLast] + c;
     stage_keys(L, keys, ranks, vmask, w, shift, mask);
     __syncthreads();
     write_staged(L, out, count, shift, mask, nullptr);
 }
 
-template <bool kFew, class Src, class Dst>
+template <int kBits, bool kFew, class Src, class Dst>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const Src in, const Dst out, uint32_t count, const uint32_t *__restrict__ dcount, int shift,
     uint32_t nbits, const uint32_t *__restrict__ table, uint32_t tiles,
     uint32_t *__restrict__ total, const int32_t *__restrict__ status) {
     if (status && *status) return;
     if (dcount) count = min(count, *dcount);
-    __shared__ SortTileLds L;
+    __shared__ SortTileLds<kBits> L;
     const uint32_t tile = xcd_tile(blockIdx.x, tiles);
     if ((uint64_t)tile * kSortTile >= count) return;  // past the keys (a device count)
     const uint32_t mask = (1u << nbits) - 1u;
     if ((uint64_t)(tile + 1) * kSortTile <= count)
-        scatter_tile<true, kFew>(in, out, count, shift, mask, table, tiles, tile, total, L);
+        scatter_tile<kBits, true, kFew>(in, out, count, shift, mask, table, tiles, tile, total, L);
     else
-        scatter_tile<false, kFew>(in, out, count, shift, mask, table, tiles, tile, total, L);
+        scatter_tile<kBits, false, kFew>(in, out, count, shift, mask, table, tiles, tile, total, L);
 }
 
 // ---------------------------------------------------------------- single-sweep variant
@@ -633,7 +657,7 @@ __device__ __forceinline__ void onesweep_tile(const uint64_t *__restrict__ in,
                                               int shift, uint32_t mask,
                                               const uint32_t *__restrict__ ghist,
                                               uint32_t *__restrict__ flags, uint32_t tile,
-                                              int32_t *__restrict__ status, SortTileLds &L) {
+                                              int32_t *__restrict__ status, SortTileLds<8> &L) {
     const uint32_t t = threadIdx.x, w = t / kWave;
     const uint64_t base = (uint64_t)tile * kSortTile;
     uint64_t keys[kSortItems];
@@ -641,7 +665,7 @@ __device__ __forceinline__ void onesweep_tile(const uint64_t *__restrict__ in,
     for (uint32_t k = lane_id(); k < 256; k += kWave) L.wcnt[w][k] = 0;
     wave_lds_sync();
     uint32_t ranks[kSortItems];
-    wave_rank_rows(keys, vmask, shift, mask, L.wcnt[w], ranks);
+    wave_rank_rows<8>(keys, vmask, shift, mask, L.wcnt[w], ranks);
     const uint32_t c = tile_digit_offsets(L);
     if (t < 256)
         __hip_atomic_store(&flags[(uint64_t)tile * 256 + t], (tile == 0 ? kLbIncl : kLbAgg) | c,
@@ -706,7 +730,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_onesweep(
     const uint64_t *__restrict__ in, uint64_t *__restrict__ out, uint32_t count, int shift,
     uint32_t nbits, const uint32_t *__restrict__ ghist, uint32_t *__restrict__ flags,
     uint32_t *__restrict__ tile_counter, int32_t *__restrict__ status) {
-    __shared__ SortTileLds L;
+    __shared__ SortTileLds<8> L;
     __shared__ uint32_t s_tile;
     __shared__ int s_stop;
     if (threadIdx.x == 0) {
@@ -732,40 +756,62 @@ size_t sort_scratch_bytes(uint64_t count) {
     return 2 * align_up(hist * 4, 256) + align_up(scan_scratch_words(hist) * 4, 256);
 }
 
-// One stable two-kernel pass on the digit at `shift` (at most 8 bits, below hi_bit) from the
-// keys `in` yields to dst.  dcount (nullable): the number of keys on the device (count: the
-// capacity); total (nullable): receives the number of keys written (the kept ones).
-template <class Src, class Dst>
-static hipError_t radix_pass(const Src in, const Dst dst, uint32_t count, int shift, int hi_bit,
-                             void *scratch, int32_t *status, hipStream_t s,
-                             const uint32_t *dcount = nullptr, uint32_t *total = nullptr) {
+// Bits per digit of the passes over a key of `bits` bits: 9 where that takes fewer passes than 8
+// (9, 17, 18, 25 to 27, 33 to 36 bits), and 8 elsewhere: a pass with 512 digits has a ninth
+// ballot per key, twice the table and half the run length.  Preprocessing with digits of 8 and
+// of 9 bits, us: 200,003 vertices and 3,000,001 edges 458 and 400, 262,144 and 20 million 1474
+// and 1386, 2^25 and 100 million 11,840 and 11,080, 2^26 and 120 million 16,250 and 15,320.
+// (Digits of 10 bits would need twice the scratch, and LDS for one workgroup per CU.)
+static int digit_bits(int bits) { return (bits + 8) / 9 < (bits + 7) / 8 ? 9 : 8; }
+
+template <int kBits, class Src, class Dst>
+static hipError_t radix_pass_bits(const Src in, const Dst dst, uint32_t count, int shift,
+                                  uint32_t nbits, void *scratch, int32_t *status, hipStream_t s,
+                                  const uint32_t *dcount, uint32_t *total) {
     const uint32_t tiles = ceil_div(count, kSortTile);
-    const uint64_t hist_n = 256ull * tiles;
+    // scratch: two tables of 256 digits, or one of 512 that is scanned in place
+    const size_t table_bytes = align_up(1024ull * tiles, 256);
     uint32_t *hist = (uint32_t *)scratch;
-    uint32_t *offs = (uint32_t *)((char *)scratch + align_up(hist_n * 4, 256));
-    uint32_t *scan_scratch = (uint32_t *)((char *)scratch + 2 * align_up(hist_n * 4, 256));
-    const uint32_t nbits = (uint32_t)((hi_bit - shift) < 8 ? (hi_bit - shift) : 8);
+    uint32_t *offs = kBits == 8 ? (uint32_t *)((char *)scratch + table_bytes) : hist;
+    uint32_t *scan_scratch = (uint32_t *)((char *)scratch + 2 * table_bytes);
     hipError_t e;
     if (tiles > 1) {
-        hipLaunchKernelGGL(k_radix_hist<Src>, dim3(tiles), dim3(kSortThreads), 0, s, in, count,
-                           dcount, shift, nbits, hist, tiles, status);
+        hipLaunchKernelGGL((k_radix_hist<kBits, Src>), dim3(tiles), dim3(kSortThreads), 0, s, in,
+                           count, dcount, shift, nbits, hist, tiles, status);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (tiles > kRawTiles) {
-        e = scan_exclusive_u32(hist, offs, hist_n, scan_scratch, s);
+        e = scan_exclusive_u32(hist, offs, (uint64_t)tiles << kBits, scan_scratch, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_radix_scatter<false, Src, Dst>), dim3(tiles), dim3(kSortThreads), 0,
-                           s, in, dst, count, dcount, shift, nbits, offs, tiles, total, status);
+        hipLaunchKernelGGL((k_radix_scatter<kBits, false, Src, Dst>), dim3(tiles),
+                           dim3(kSortThreads), 0, s, in, dst, count, dcount, shift, nbits, offs,
+                           tiles, total, status);
     } else {
-        hipLaunchKernelGGL((k_radix_scatter<true, Src, Dst>), dim3(tiles), dim3(kSortThreads), 0,
-                           s, in, dst, count, dcount, shift, nbits, hist, tiles, total, status);
+        hipLaunchKernelGGL((k_radix_scatter<kBits, true, Src, Dst>), dim3(tiles),
+                           dim3(kSortThreads), 0, s, in, dst, count, dcount, shift, nbits, hist,
+                           tiles, total, status);
     }
     return hipGetLastError();
 }
 
-hipError_t sort_u64(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, int hi_bit,
-                    void *scratch, int32_t *status, hipStream_t s, uint64_t **result,
-                    bool onesweep) {
+// One stable two-kernel pass on the digit of up to `digit` bits at `shift` (below hi_bit) from
+// the keys `in` yields to dst.  dcount (nullable): the number of keys on the device (count: the
+// capacity); total (nullable): receives the number of keys written (the kept ones).
+template <class Src, class Dst>
+static hipError_t radix_pass(const Src in, const Dst dst, uint32_t count, int digit, int shift,
+                             int hi_bit, void *scratch, int32_t *status, hipStream_t s,
+                             const uint32_t *dcount = nullptr, uint32_t *total = nullptr) {
+    const uint32_t nbits = (uint32_t)((hi_bit - shift) < digit ? (hi_bit - shift) : digit);
+    return digit == 9 ? radix_pass_bits<9>(in, dst, count, shift, nbits, scratch, status, s,
+                                           dcount, total)
+                      : radix_pass_bits<8>(in, dst, count, shift, nbits, scratch, status, s,
+                                           dcount, total);
+}
+
+// sort_u64 with digits of `digit` bits
+static hipError_t sort_passes(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit,
+                              int hi_bit, int digit, void *scratch, int32_t *status,
+                              hipStream_t s, uint64_t **result, bool onesweep) {
     *result = keys;
     if (count <= 1 || hi_bit <= lo_bit) return hipSuccess;
     uint32_t tiles = ceil_div(count, kSortTile);
@@ -798,9 +844,9 @@ hipError_t sort_u64(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, i
         *result = src;
         return hipSuccess;
     }
-    for (int shift = lo_bit; shift < hi_bit; shift += 8) {
+    for (int shift = lo_bit; shift < hi_bit; shift += digit) {
         hipError_t e =
-            radix_pass(Keys64{src}, Out64{dst}, count, shift, hi_bit, scratch, status, s);
+            radix_pass(Keys64{src}, Out64{dst}, count, digit, shift, hi_bit, scratch, status, s);
         if (e != hipSuccess) return e;
         uint64_t *x = src;
         src = dst;
@@ -810,17 +856,27 @@ hipError_t sort_u64(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, i
     return hipSuccess;
 }
 
+hipError_t sort_u64(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, int hi_bit,
+                    void *scratch, int32_t *status, hipStream_t s, uint64_t **result,
+                    bool onesweep) {
+    return sort_passes(keys, tmp, count, lo_bit, hi_bit, digit_bits(hi_bit - lo_bit), scratch,
+                       status, s, result, onesweep);
+}
+
 hipError_t sort_unzip(uint64_t *keys, uint64_t *tmp, uint32_t count, int lo_bit, int hi_bit,
                       int b, uint32_t *col, uint32_t *src, void *scratch, int32_t *status,
                       hipStream_t s, bool onesweep) {
     if (count == 0) return hipSuccess;
-    const int passes = hi_bit > lo_bit ? (hi_bit - lo_bit + 7) / 8 : 1;
-    const int last = hi_bit > lo_bit ? lo_bit + 8 * (passes - 1) : hi_bit;
+    // (a single sweep has digits of 8 bits)
+    const int digit = onesweep ? 8 : digit_bits(hi_bit - lo_bit);
+    const int passes = hi_bit > lo_bit ? (hi_bit - lo_bit + digit - 1) / digit : 1;
+    const int last = hi_bit > lo_bit ? lo_bit + digit * (passes - 1) : hi_bit;
     uint64_t *mid = keys;
-    hipError_t e = sort_u64(keys, tmp, count, lo_bit, last, scratch, status, s, &mid, onesweep);
+    hipError_t e = sort_passes(keys, tmp, count, lo_bit, last, digit, scratch, status, s, &mid,
+                               onesweep);
     if (e != hipSuccess) return e;
-    return radix_pass(Keys64{mid}, OutColSrc{col, src, (1ull << b) - 1, b}, count, last, hi_bit,
-                      scratch, status, s);
+    return radix_pass(Keys64{mid}, OutColSrc{col, src, (1ull << b) - 1, b}, count, digit, last,
+                      hi_bit, scratch, status, s);
 }
 
 hipError_t sort_ranks(const uint32_t *deg, uint64_t *keys, uint64_t *tmp, uint32_t n, int b,
@@ -829,18 +885,19 @@ hipError_t sort_ranks(const uint32_t *deg, uint64_t *keys, uint64_t *tmp, uint32
     if (n == 0) return hipSuccess;
     const KeysDegree first{deg, b};
     const OutPermRank last{perm, rank, (1ull << b) - 1};
-    if (b <= 8) return radix_pass(first, last, n, b, 2 * b, scratch, status, s);
-    hipError_t e = radix_pass(first, Out64{keys}, n, b, 2 * b, scratch, status, s);
+    const int digit = digit_bits(b);
+    if (b <= digit) return radix_pass(first, last, n, digit, b, 2 * b, scratch, status, s);
+    hipError_t e = radix_pass(first, Out64{keys}, n, digit, b, 2 * b, scratch, status, s);
     uint64_t *src = keys, *dst = tmp;
-    int shift = b + 8;
-    for (; e == hipSuccess && shift + 8 < 2 * b; shift += 8) {
-        e = radix_pass(Keys64{src}, Out64{dst}, n, shift, 2 * b, scratch, status, s);
+    int shift = b + digit;
+    for (; e == hipSuccess && shift + digit < 2 * b; shift += digit) {
+        e = radix_pass(Keys64{src}, Out64{dst}, n, digit, shift, 2 * b, scratch, status, s);
         uint64_t *x = src;
         src = dst;
         dst = x;
     }
     if (e != hipSuccess) return e;
-    return radix_pass(Keys64{src}, last, n, shift, 2 * b, scratch, status, s);
+    return radix_pass(Keys64{src}, last, n, digit, shift, 2 * b, scratch, status, s);
 }
 
 hipError_t sort_lists(const uint32_t *cid, uint32_t drop, uint32_t count, int bits,
@@ -849,26 +906,27 @@ hipError_t sort_lists(const uint32_t *cid, uint32_t drop, uint32_t count, int bi
     *list = (uint32_t *)a;
     if (count == 0) return fill_u32(kept, 0u, 1, s);
     const int hi_bit = 32 + (bits > 0 ? bits : 0);
-    const int passes = bits > 0 ? (bits + 7) / 8 : 1;
+    const int digit = digit_bits(bits);
+    const int passes = bits > 0 ? (bits + digit - 1) / digit : 1;
     const KeysHiIndex first{cid, drop};
     if (passes == 1)  // one pass from the ids to the split output
-        return radix_pass(first, OutListBeg{*list, cbeg}, count, 32, hi_bit, scratch, status, s,
+        return radix_pass(first, OutListBeg{*list, cbeg}, count, digit, 32, hi_bit, scratch, status, s,
                           nullptr, kept);
     hipError_t e =
-        radix_pass(first, Out64{a}, count, 32, hi_bit, scratch, status, s, nullptr, kept);
+        radix_pass(first, Out64{a}, count, digit, 32, hi_bit, scratch, status, s, nullptr, kept);
     if (e != hipSuccess) return e;
     uint64_t *src = a, *dst = b;
     for (int p = 1; p < passes - 1; ++p) {  // the middle passes, on the kept keys
-        e = radix_pass(Keys64{src}, Out64{dst}, count, 32 + 8 * p, hi_bit, scratch, status, s,
-                       kept);
+        e = radix_pass(Keys64{src}, Out64{dst}, count, digit, 32 + digit * p, hi_bit, scratch,
+                       status, s, kept);
         if (e != hipSuccess) return e;
         uint64_t *x = src;
         src = dst;
         dst = x;
     }
     *list = (uint32_t *)dst;  // the buffer the last pass does not read
-    return radix_pass(Keys64{src}, OutListBeg{*list, cbeg}, count, 32 + 8 * (passes - 1), hi_bit,
-                      scratch, status, s, kept);
+    return radix_pass(Keys64{src}, OutListBeg{*list, cbeg}, count, digit,
+                      32 + digit * (passes - 1), hi_bit, scratch, status, s, kept);
 }
 
 }  // namespace tc

@@ -24,6 +24,18 @@ def test_sort_at_tile_edges(count, bits):
     assert torch.equal(got, want)
 
 
+@pytest.mark.parametrize("bits", [9, 17, 18, 19, 25, 27, 28])
+@pytest.mark.parametrize("count", [TILE + 1, RAW * TILE, RAW * TILE + 1])
+def test_sort_with_wide_digits(bits, count):
+    """Widths on both sides of the ones that take digits of 9 bits."""
+    gen = torch.Generator().manual_seed(count + bits)
+    keys = torch.randint(0, 1 << 40, (count,), generator=gen, dtype=torch.int64)
+    keys[: count // 3] &= ~0x1FF  # a crowded digit
+    keys[count // 2:] |= 0x3FFFF  # and its opposite
+    want = keys[torch.argsort(keys & ((1 << bits) - 1), stable=True)]
+    assert torch.equal(api.sort_u64(keys.to(DEV), bits).cpu(), want)
+
+
 @pytest.mark.parametrize("n", [2, 255, 256, 257, 16383, 16384, 16385, 3 * 16384 + 1])
 def test_counts_at_scan_edges(n):
     """n + 1 row offsets on both sides of one scan tile (16384), one and two vertex passes."""
