@@ -41,7 +41,7 @@ __global__ void k_panel_range(const uint32_t *, const uint32_t *, uint32_t, uint
 __global__ void k_csc_keys(const uint32_t *, const uint32_t *, const uint32_t *,
                            const uint32_t *, const uint32_t *, uint32_t, const uint64_t *,
                            uint32_t, uint32_t, uint32_t, uint32_t, const uint32_t *, uint32_t,
-                           uint32_t, uint32_t *, uint4 *, uint16_t *, const int32_t *);
+                           uint32_t, uint32_t *, uint4 *, uint16_t *, uint32_t, const int32_t *);
 __global__ void k_csc_final(const uint32_t *, uint32_t, const uint32_t *, uint64_t, uint32_t *,
                             uint32_t *, const int32_t *);
 __global__ void k_items(const uint32_t *, const uint32_t *, const uint32_t *, const uint32_t *,
@@ -408,7 +408,6 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
             f.add(rs, 0u, n1);
             f.add(re, 0u, n1);
             f.add(hrow, ~0u, n);
-            f.add((uint32_t *)hcol, 0u, L.hcap / 2);  // zeros, the parts' padding
             f.add(lrs, 0u, l1);
             f.add(lre, 0u, l1);
             if (L.hp) {
@@ -541,7 +540,7 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     hipLaunchKernelGGL(k_csc_keys, dim3(grid_for(mf, 256 * kCscPerThread)), dim3(256), 0, s, col,
                        src, row_ptr, hrow, hstart, L.hbase, pr, mf, n, L.nblk, L.p0,
                        ctl + kCtlFirstPanel,
-                       count_panel(), L.h0, cid, eu, hcol, status);
+                       count_panel(), L.h0, cid, eu, hcol, count_hcol_pad(), status);
     TC_LAUNCH_CHECK();
     if (small) {
         TC_HIP(small_lists(cid, mf, (uint32_t)L.lists, lrs, lre, (uint32_t *)ck, cptr,
