@@ -76,3 +76,17 @@ def test_two_direction_compaction_at_tile_edges(m):
             assert api.count(entries.to(DEV), n, both=True,
                              options={"degree_partition": part}) == want
     assert api.count(e.to(DEV), n, options={"degree_partition": 0}) == want
+
+
+@pytest.mark.parametrize("k", [1024, 1025, 1026, 1090])
+def test_rows_across_sort_chunks(k):
+    """A clique's rows, of every length up to k - 1, start at all offsets of the row sort's chunks
+    (4096 positions; rows above 1024 entries are sorted by another kernel) and reach into the next."""
+    gen = torch.Generator().manual_seed(k)
+    a, b = torch.triu_indices(k, k, 1)
+    e = torch.stack([a, b], 1)[torch.randperm(a.numel(), generator=gen)].to(torch.int32)
+    out = api.preprocess(e.to(DEV), k)
+    col, rp = out["col"].cpu().numpy(), out["row_ptr"].cpu().numpy()
+    assert np.array_equal(rp[1:] - rp[:-1], np.arange(k - 1, -1, -1))
+    assert all(np.array_equal(col[rp[r]:rp[r + 1]], np.arange(r + 1, k)) for r in range(k))
+    assert api.count(e.to(DEV), k) == k * (k - 1) * (k - 2) // 6
