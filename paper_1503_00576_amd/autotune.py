@@ -1,7 +1,7 @@
 """Autotuners for the work distribution of the counting kernels.
 
-Batched plans (tune_batched): "chunk_e", the number of consecutive forward edges in one work
-item of the edge-per-lane path, "items_k", the number of out-neighbours of one larger vertex
+Batched plans (tune_batched): "chunk_e", the number of forward entries staged at a time by a wave
+of the edge-per-lane path, "items_k", the number of out-neighbours of one larger vertex
 handled by one work item, and "light_max", the forward degree up to which a vertex takes the
 edge-per-lane path.  The tuner captures one plan per candidate and replays it on the caller's
 batch.

@@ -455,6 +455,16 @@ struct HighMaskedProbe {
     static constexpr bool kPanel = false;
 };
 
+// Both in one pass, with the entries of N+(v) below hbase as a sorted list (1 to kWave entries, in
+// the wave's scratch).
+struct LowHighProbe {
+    LdsListProbe low;
+    HighMaskedProbe high;
+    static constexpr bool kLow = true;
+    static constexpr bool kMaskHigh = true;
+    static constexpr bool kPanel = false;
+};
+
 // Panel table over ranks [P, n) (as PanelProbe) read with 16-bit entries: rank hbase + x is
 // word x - c (c = P - hbase), ranks below P saturate onto word 0 (rank P, in no out-list of
 // the panel), and no entry exceeds word n - 1 - P.  An entry of u's row up to u's first panel
@@ -556,6 +566,17 @@ __device__ __forceinline__ uint32_t high_hits_u(const PanelHighProbe &probe,
     for (uint32_t i = 0; i < kPieceHigh / 2; ++i)
         hits += probe.count(pr[i] & 0xFFFFu, r) + probe.count(pr[i] >> 16, r);
     return hits;
+}
+
+__device__ __forceinline__ uint32_t low_hits(const LowHighProbe &probe,
+                                             const uint32_t (&wv)[kPiece], uint32_t start,
+                                             uint32_t first, uint32_t stop) {
+    return low_hits(probe.low, wv, start, first, stop);
+}
+__device__ __forceinline__ uint32_t high_hits(const LowHighProbe &probe,
+                                              const uint32_t (&pr)[kPiece / 2], uint32_t hbase,
+                                              uint32_t start, uint32_t first, uint32_t stop) {
+    return high_hits(probe.high, pr, hbase, start, first, stop);
 }
 
 // The calling wave streams one batch of up to 64 segments (r: this lane's record, all zero
@@ -879,13 +900,14 @@ __device__ __forceinline__ uint32_t run_panel_pv(uint32_t eb, uint32_t e1,
 
 // Per-vertex wave items with N+(v) of at most kFilterList entries.  Nearly every entry streamed
 // is no hit, and a lockstep search costs log2(d) LDS reads and three times that many vector
-// operations per entry (at R-MAT 22, 800 LDS and 2,780 vector instructions per item, 290 and
-// 1,500 with the filter; per-vertex counts 11.05 -> 10.37 ms with the preprocessing, at R-MAT 23
-// 28.4 -> 25.3 ms without; now 3.9 TB/s of missed lines at R-MAT 22).  So the slice also holds a filter, bit w mod kFilterBits of every
-// w in N+(v): one read per entry passes the hits and d in kFilterBits of the others.  The
-// entries passed are queued with their segments, and every lane searches one of them per step.
-// A round that passes more entries than the queue holds is searched in lockstep.  Longer lists
-// (0.3 percent of the items at R-MAT 22) keep the lockstep search: the slice has no room for more.
+// operations per entry: at R-MAT 22, 800 LDS and 2,780 vector instructions per item.  So the
+// slice also holds a filter, bit w mod kFilterBits of every w in N+(v): one read per entry passes
+// the hits and d in kFilterBits of the others.  The entries passed are queued with their segments,
+// and every lane searches one of them per step (290 and 1,500 instructions).  A round that passes
+// more entries than the queue holds is searched in lockstep.  Longer lists (0.3 percent of the
+// items at R-MAT 22) keep the lockstep search: the slice has no room for more.  Per-vertex counts,
+// R-MAT 22 with the preprocessing 11.05 -> 10.37 ms, R-MAT 23 without 28.4 -> 25.3 ms; bound by
+// missed lines now (3.9 TB/s at R-MAT 22).
 // mem: list, counters, filter (zero but for N+(v)'s bits) and queue.
 __device__ __forceinline__ uint32_t run_filter_pv(uint32_t eb, uint32_t e1,
                                                   const InEdgeSegs &segs,
@@ -1347,11 +1369,19 @@ __global__ __launch_bounds__(kThreads) void k_count(
             } else if (hbase + 1 < n1 && slices_aligned) {
                 // a wide span (a list of at most wave_list_max <= kSliceWords entries, see
                 // k_items): the suffixes' entries below hbase against N+(v)'s entries below
-                // hbase as a sorted list in the slice, then their entries >= hbase against
-                // N+(v)'s in the high-region bitmap (no pass for a part N+(v) lacks)
+                // hbase as a sorted list, their entries >= hbase against N+(v)'s in the
+                // high-region bitmap; with the list in the slice too, which the bitmap fills, one
+                // after the other (no pass for a part N+(v) lacks)
                 const uint32_t hr = hrow[it.v];
                 const uint32_t dlo = hr == ~0u ? it.d : hr - it.r0;
-                if (dlo > 0) {
+                // up to kWave entries below hbase fit the wave's scratch: one pass, which gathers
+                // the records once (missed lines are what these items are bound by).  R-MAT 23,
+                // where 93 percent of the 561,000 wide lists are that short: 26.37 ms a step with
+                // two passes for all, 25.91 with one for these
+                const bool both = dlo > 0 && dlo <= kWave && dlo < it.d;
+                if (both) {
+                    if (lane < dlo) ws.cnt[lane] = col[it.r0 + lane];
+                } else if (dlo > 0) {
                     for (uint32_t i = lane; i < dlo; i += kWave) mem[i] = col[it.r0 + i];
                     wave_lds_sync();
                     const LdsListProbe lp{lds_addr(mem), dlo};
@@ -1364,8 +1394,11 @@ __global__ __launch_bounds__(kThreads) void k_count(
                     atomicOr(&mem[x >> 5], 1u << (x & 31u));
                 }
                 wave_lds_sync();
-                if (dlo < it.d) {
-                    const HighMaskedProbe probe{HighBitmapProbe{lds_addr(mem)}};
+                const HighMaskedProbe probe{HighBitmapProbe{lds_addr(mem)}};
+                if (both) {
+                    const LowHighProbe lh{LdsListProbe{lds_addr(ws.cnt), dlo}, probe};
+                    cnt += stream_t(it.e0, it.e1, kWave, segs, col, hcol, hbase, lh, ws);
+                } else if (dlo < it.d) {
                     cnt += stream_t<2>(it.e0, it.e1, kWave, segs, col, hcol, hbase, probe, ws);
                 }
                 for (uint32_t i = dlo + lane; i < it.d; i += kWave)
@@ -1720,12 +1753,13 @@ __global__ __launch_bounds__(kLightThreads, 8) void k_count_light(const BatchKer
 
 // ------------------------------------------------------------------ light middle vertices
 //
-// The lists of vertices v below the first panel with few in-edges and a short N+(v) (kLightList): a
-// wave takes kLightLists consecutive lists (16: at R-MAT 20 the densest waves of 64 lists ran on
-// for 100 us after the others, 1960 against 1913 us a count; 8 lists: the same), stages their N+(v) in LDS (whole lists, a window at a time) and
-// takes their in-edges u -> v one per lane, whatever list they belong to: the suffix of N+(u)
-// after v (short as well: u comes before v in the order of degrees) is looked up in N+(v) by
-// binary search, its first piece on the edge's own lane, further pieces in full rounds.
+// The lists of vertices v below the first panel with few in-edges and a short N+(v) (kLightList):
+// a wave takes kLightLists consecutive lists (16: at R-MAT 20 the densest waves of 64 lists ran on
+// for 100 us after the others, 1960 against 1913 us a count; 8 lists: the same), stages their
+// N+(v) in LDS (whole lists, a window at a time) and takes their in-edges u -> v one per lane,
+// whatever list they belong to: the suffix of N+(u) after v (short as well: u comes before v in
+// the order of degrees) is looked up in N+(v) by binary search, its first piece on the edge's own
+// lane, further pieces in full rounds.
 //
 // Per-vertex counts: a hit credits an LDS counter of N+(v)'s entry (added to T(w) once per entry,
 // and their sum to T(v)) and T(u) once per piece.

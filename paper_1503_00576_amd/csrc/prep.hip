@@ -21,7 +21,8 @@
 //                built by a radix sort of (list << 32 | e) keys, so no atomics are needed;
 //                from rank p0 on, one list per panel of consecutive middle vertices, with the
 //                mask of u's panel vertices per entry
-//   k_items_*    work items of the counting kernels (see count.hip)
+//   k_items, k_item_fill   work items of the counting kernels (see count.hip)
+//   (small.hip)  counting sorts in place of all this for small graphs
 //
 // Working with ranks instead of ids makes the order test a plain comparison, groups the
 // high-degree vertices (whose lists are read most often) into one contiguous region, and

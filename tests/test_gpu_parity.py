@@ -610,3 +610,15 @@ def test_per_vertex_wave_items(k, row_blocks):
     edges += [(k + m, i) for i in range(k + m)]
     check_vs_oracle(np.array(edges, dtype=np.int32), k + m + 1,
                     options={"panel_ranks": 0, "row_blocks": row_blocks}, prepared_pv=True)
+
+
+@pytest.mark.parametrize("high", [1, 60, 130, 199])
+def test_wide_lists_by_their_low_entries(high):
+    """Lists whose span takes no bitmap, with 0 to 199 entries below the high region: up to 64 of
+    them are matched in the same pass as the high ones.  A clique and a random graph."""
+    options = {"panel_ranks": 0, "wave_bitmap_span": 0, "high_ranks": high}
+    clique = np.stack(np.triu_indices(200, 1), 1).astype(np.int32)
+    rng = np.random.default_rng(high)
+    sparse = np.stack(np.nonzero(np.triu(rng.random((300, 300)) < 0.4, 1)), 1).astype(np.int32)
+    check_vs_oracle(clique, 200, options=options)
+    check_vs_oracle(sparse, 300, options=options)
