@@ -30,9 +30,9 @@ __global__ void k_both_check(const uint32_t *, uint32_t, int32_t *);
 __global__ void k_csr(const uint64_t *, uint32_t, uint32_t, int, uint32_t, uint32_t *,
                       uint32_t *, uint32_t *, uint32_t *, uint32_t *, int32_t *);
 __global__ void k_row_bounds(const uint32_t *, uint32_t, uint32_t, uint32_t *, uint32_t *,
-                             uint32_t *, const int32_t *);
+                             uint32_t *, uint32_t, const int32_t *);
 __global__ void k_row_sort(uint32_t *, const uint32_t *, const uint32_t *, uint32_t, uint32_t,
-                           uint32_t, uint32_t *, uint32_t *, uint32_t *, int32_t *);
+                           uint32_t, uint32_t, uint32_t *, uint32_t *, uint32_t *, int32_t *);
 __global__ void k_row_sort_long(uint32_t *, const uint32_t *, const uint32_t *,
                                 const uint32_t *, uint32_t, uint32_t *, int32_t *);
 __global__ void k_panel_range(const uint32_t *, const uint32_t *, uint32_t, uint32_t, uint32_t,
@@ -275,7 +275,7 @@ static bool make_layout(int64_t n, int64_t m, uint32_t flags, const tc_options *
     L.hstart = take(n1 * 4);
     L.src = take((size_t)L.mf * 4);
     // rows sorted in place after a sort by source only: chunk table and the long rows' list
-    L.rchunk = take(((size_t)L.mf / row_sort_chunk() + 2) * 4);
+    L.rchunk = take(((size_t)L.mf / row_sort_chunk(L.mf) + 2) * 4);
     L.long_rows = take(((size_t)L.mf / (row_sort_wave() + 1) + 2) * 4);
     L.prange = take((size_t)L.panels * 8);
     L.eu = take((size_t)L.mf * 16);  // also the cell-ordered edges (8 bytes per entry)
@@ -480,25 +480,26 @@ static int run_preprocess(const int32_t *d_edges, uint32_t flags, void *ws, cons
     if (mf == 0) return TC_OK;
     // node array: row boundaries -> row lengths -> exclusive scan
     uint32_t *rchunk = at<uint32_t>(ws, L.rchunk);
+    const uint32_t chunk = row_sort_chunk(mf);
     // 4 entries per thread (prep.hip, kCsrKeys)
     if (small)
         TC_HIP(small_rows(d_edges, m, n, both, mf, rank, (uint2 *)ka, rs, re, row_ptr, col, src,
                           rchunk, ctl + kCtlBoth, scan_scr, status, s));
     else if (row_sort)
         hipLaunchKernelGGL(k_row_bounds, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, src, mf,
-                           n, rs, re, rchunk, status);
+                           n, rs, re, rchunk, chunk, status);
     else
         hipLaunchKernelGGL(k_csr, dim3(grid_for(mf, 256 * 4)), dim3(256), 0, s, sorted, mf, n,
                            b, L.hbase, col, src, rs, re, hrow, status);
     TC_LAUNCH_CHECK();
     if (!small) TC_HIP(scan_row_bounds(rs, re, n, row_ptr, scan_scr, s));
     if (row_sort) {  // every row sorted in place, with the duplicate check and hrow
-        const uint32_t chunks = ceil_div(mf, row_sort_chunk());
+        const uint32_t chunks = ceil_div(mf, chunk);
         uint32_t *long_rows = at<uint32_t>(ws, L.long_rows);
         // a simple graph's rows hold fewer than sqrt(2 mf) entries
         const bool any_long = 2 * (uint64_t)mf > (uint64_t)row_sort_wave() * row_sort_wave();
         hipLaunchKernelGGL(k_row_sort, dim3(chunks), dim3(256), 0, s, col, row_ptr, rchunk,
-                           chunks, n, L.hbase, hrow, long_rows,
+                           chunk, chunks, n, L.hbase, hrow, long_rows,
                            any_long ? ctl + kCtlLongRows : nullptr, status);
         TC_LAUNCH_CHECK();
         if (any_long) {

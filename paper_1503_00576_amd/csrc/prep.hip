@@ -390,7 +390,7 @@ __global__ void k_both_check(const uint32_t *__restrict__ counter, uint32_t expe
 }
 
 constexpr uint32_t kCsrKeys = 4;
-constexpr uint32_t kRowChunk = 4096;  // CSR positions per workgroup of k_row_sort
+constexpr uint32_t kRowChunk = 4096;  // CSR positions per workgroup of k_row_sort, at most
 
 // Unzip the sorted keys into the neighbour array (Section 3.2, step 7) and mark where every
 // non-empty row starts and ends; row lengths and their prefix sum give the node array.
@@ -432,12 +432,14 @@ __global__ void k_csr(const uint64_t *__restrict__ keys, uint32_t mf, uint32_t n
 
 // With the keys sorted by source only and unzipped by the sort's last pass (col, src): where
 // every non-empty row starts and ends, and rchunk[c] = the first row starting at or after
-// position c * kRowChunk (the chunks of k_row_sort, which sorts the rows, checks them for
+// position c * chunk (a power of two; the chunks of k_row_sort, which sorts the rows, checks them for
 // duplicates and records hrow).
 __global__ void k_row_bounds(const uint32_t *__restrict__ src, uint32_t mf, uint32_t n,
                              uint32_t *__restrict__ rs, uint32_t *__restrict__ re,
-                             uint32_t *__restrict__ rchunk, const int32_t *__restrict__ status) {
+                             uint32_t *__restrict__ rchunk, uint32_t chunk,
+                             const int32_t *__restrict__ status) {
     if (*status) return;
+    const uint32_t cshift = __builtin_ctz(chunk);
     const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x * kCsrKeys + threadIdx.x;
     uint32_t x[kCsrKeys], xp[kCsrKeys], xn[kCsrKeys];
 #pragma unroll
@@ -454,7 +456,7 @@ __global__ void k_row_bounds(const uint32_t *__restrict__ src, uint32_t mf, uint
         if (i >= mf || s >= n) continue;  // (s >= n only for invalid input, reported elsewhere)
         const bool row_start = i == 0 || xp[t] != s;
         if (row_start) rs[s] = (uint32_t)i;
-        if ((i & (kRowChunk - 1)) == 0) rchunk[i / kRowChunk] = row_start ? s : s + 1;
+        if ((i & (chunk - 1)) == 0) rchunk[i >> cshift] = row_start ? s : s + 1;
         if (i == mf - 1 || xn[t] != s) re[s] = (uint32_t)(i + 1);
     }
 }
@@ -464,7 +466,7 @@ __global__ void k_row_bounds(const uint32_t *__restrict__ src, uint32_t mf, uint
 // With the edge keys sorted by source only (three radix passes instead of six), every row of
 // col holds its targets in input order; these kernels sort each row ascending, then check it
 // for duplicates and record hrow (as k_csr does for fully sorted keys).  A workgroup takes
-// the rows starting in one chunk of kRowChunk positions: rows of at most kRowWave entries by
+// the rows starting in one chunk of positions: rows of at most kRowWave entries by
 // groups of lanes sized to the row (a bitonic network over the group's registers, 16 entries
 // per lane, the smaller strides in registers and the others across the group's lanes; a
 // short row takes one lane, so that small rows do not pay for a whole wave's network),
@@ -636,8 +638,8 @@ __device__ __forceinline__ uint32_t row_class(uint32_t len) {  // len >= 1
 __global__ __launch_bounds__(256) void k_row_sort(uint32_t *__restrict__ col,
                                                   const uint32_t *__restrict__ row_ptr,
                                                   const uint32_t *__restrict__ rchunk,
-                                                  uint32_t chunks, uint32_t n, uint32_t hbase,
-                                                  uint32_t *__restrict__ hrow,
+                                                  uint32_t chunk, uint32_t chunks, uint32_t n,
+                                                  uint32_t hbase, uint32_t *__restrict__ hrow,
                                                   uint32_t *__restrict__ long_rows,
                                                   uint32_t *__restrict__ n_long,
                                                   int32_t *__restrict__ status) {
@@ -651,8 +653,8 @@ __global__ __launch_bounds__(256) void k_row_sort(uint32_t *__restrict__ col,
     const uint32_t t = threadIdx.x;
     if (r0 >= r1) return;  // (inside a long row)
     // (a long row's part beyond the stage is not touched, and what is staged of it stays as it is)
-    const StagedCol staged{stage, c * kRowChunk};
-    const uint32_t p0 = row_ptr[r0], p1 = min(row_ptr[r1], c * kRowChunk + kRowStage);
+    const StagedCol staged{stage, c * chunk};
+    const uint32_t p0 = row_ptr[r0], p1 = min(row_ptr[r1], c * chunk + chunk + kRowWave);
     if (t < kRowClasses) ccount[t] = 0;
 #pragma unroll 4
     for (uint32_t p = p0 + t; p < p1; p += 256) staged(p) = col[p];
@@ -753,7 +755,13 @@ __global__ __launch_bounds__(1024) void k_row_sort_long(uint32_t *__restrict__ c
     }
 }
 
-uint32_t row_sort_chunk() { return kRowChunk; }
+// CSR positions per workgroup of the row sort: fewer where 4096 would leave CUs idle (256 of them).
+// Preprocessing, us, with chunks of 4096 and of this rule: 9,704 edges 66.5 and 63.0, 100,003 112.5
+// and 104.5, 200,003 236.6 and 223.7, 500,009 284 and 269.5, 900,000 328 and 314.  From 2^20 edges
+// on 2048 moves different graphs between -2 and +1 percent, and 1024 costs 5 at R-MAT 20.
+uint32_t row_sort_chunk(uint64_t mf) {
+    return mf < (1u << 18) ? 512u : mf < (1u << 20) ? 1024u : kRowChunk;
+}
 uint32_t row_sort_wave() { return kRowWave; }
 
 // Rank span of the union of the out-lists of every panel (ranks p0 + i * 32 .. + 31):

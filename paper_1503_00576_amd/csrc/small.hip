@@ -221,7 +221,7 @@ hipError_t small_rows(const int32_t *edges, uint32_t m, uint32_t n, bool both, u
     if (e != hipSuccess) return e;
     if ((e = scan_row_bounds(rs, re, n, row_ptr, scan_scratch, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_s_place, dim3(ceil_div(m, 256)), dim3(256), 0, s, tmp, m, (uint32_t)both,
-                       mf, row_sort_chunk(), row_ptr, counter, col, src, rchunk, status);
+                       mf, row_sort_chunk(mf), row_ptr, counter, col, src, rchunk, status);
     return hipGetLastError();
 }
 

@@ -78,10 +78,11 @@ def test_two_direction_compaction_at_tile_edges(m):
     assert api.count(e.to(DEV), n, options={"degree_partition": 0}) == want
 
 
-@pytest.mark.parametrize("k", [1024, 1025, 1026, 1090])
+@pytest.mark.parametrize("k", [40, 500, 723, 724, 725, 1024, 1025, 1026, 1090, 1448, 1449])
 def test_rows_across_sort_chunks(k):
     """A clique's rows, of every length up to k - 1, start at all offsets of the row sort's chunks
-    (4096 positions; rows above 1024 entries are sorted by another kernel) and reach into the next."""
+    (512 positions below 2^18 edges, 1024 below 2^20, then 4096; rows above 1024 entries are sorted
+    by another kernel) and reach into the next."""
     gen = torch.Generator().manual_seed(k)
     a, b = torch.triu_indices(k, k, 1)
     e = torch.stack([a, b], 1)[torch.randperm(a.numel(), generator=gen)].to(torch.int32)
