@@ -9,9 +9,11 @@
 // Preprocessing needs no sort: the degree of a vertex is its row length, and keeping in every
 // row only the neighbours that come later in the order of Section 2.2 ((degree, id)
 // ascending) is a stable filter, so the oriented rows stay sorted by id.  One pass over the
-// input checks it and writes every row's kept entries at the row's own place (the row's start
-// among all rows): nothing about the kept entries has to be known beforehand, so the input is
-// read once.  The counting kernels (count.hip) then stage N+(u) and stream N+(v) for the
+// input checks it and writes every row's kept entries at the row's own place in the input:
+// nothing about the other rows has to be known beforehand, so the input is read once, and a
+// graph writes only inside its own adjacency range, so that a malformed one does not reach the
+// others (its rows are left out when its offsets descend, or when its range meets an earlier
+// graph's).  The counting kernels (count.hip) then stage N+(u) and stream N+(v) for the
 // out-neighbours v.
 //
 // Every kernel reads the sizes and the caller's pointers from an argument block at the start
@@ -38,8 +40,9 @@ struct BatchArgs {
     uint32_t A;  // adjacency entries in total
 };
 
-// ctl: [0] heavy-item queue, [1] heavy items
-constexpr uint32_t kCtlWordsB = 2;
+// ctl: [0] heavy-item queue, [1] heavy items, [2] first graph whose adjacency range descends (all
+// ones: none, and then no two ranges meet)
+enum { kCtlQueueB = 0, kCtlItemsB = 1, kCtlDescentB = 2, kCtlWordsB = 3 };
 
 __device__ __forceinline__ void graph_error(const BatchArgs &a, uint32_t g, int32_t code,
                                             int32_t *gstat) {
@@ -63,7 +66,7 @@ __global__ void k_b_begin(BatchArgs *dst, const BatchArgs a, int32_t *__restrict
                           uint32_t *__restrict__ ctl) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) *dst = a;
-    if (i < kCtlWordsB) ctl[i] = 0;
+    if (i < kCtlWordsB) ctl[i] = i == kCtlDescentB ? ~0u : 0u;
     const uint32_t cap = a.per_vertex && a.N > a.G ? a.N : a.G;
     for (uint32_t x = i; x < cap; x += gridDim.x * blockDim.x) {
         if (x < a.G) {
@@ -89,36 +92,54 @@ __device__ __forceinline__ uint64_t pair_hash(uint32_t x, uint32_t y) {
 }
 
 // per vertex: its graph, and its row length once the offsets it relies on are checked (the whole
-// vertex range of its graph, whose row offsets the forward test reads); 0 for the vertices from
-// N on, so that the scan over ncap + 1 entries gives every row's place
-__global__ __launch_bounds__(256) void k_b_rows(const BatchArgs *__restrict__ args, uint32_t ncap,
+// vertex range of its graph, whose row lengths the forward test reads).  A graph with a row whose
+// offsets are bad is TC_E_ARG from here on, and k_b_setup leaves all its rows out.  per graph:
+// whether its adjacency range descends
+__global__ __launch_bounds__(256) void k_b_rows(const BatchArgs *__restrict__ args,
                                                 uint32_t *__restrict__ gid,
                                                 uint32_t *__restrict__ deg,
+                                                uint32_t *__restrict__ descent,
                                                 int32_t *__restrict__ gstat) {
     const BatchArgs a = *args;
     const uint32_t x = blockIdx.x * 256u + threadIdx.x;
-    if (x > ncap) return;
+    if (x < a.G && a.adj_off[x + 1] < a.adj_off[x]) atomicMin(descent, x);
+    if (x >= a.N) return;
     uint32_t d = 0;
-    if (x < a.N) {
-        const uint32_t g = graph_of(a.vtx_off, a.G, x);
-        gid[x] = g;
-        const int64_t v0 = a.vtx_off[g], n_g = a.vtx_off[g + 1] - v0;
-        const int64_t a0 = a.adj_off[g], alen = a.adj_off[g + 1] - a0;
-        const int64_t lx = (int64_t)x - v0;
-        // offsets arrays must be prefix sums
-        if (v0 < 0 || lx < 0 || lx >= n_g || v0 + n_g > (int64_t)a.N || a0 < 0 || alen < 0 ||
-            a0 + alen > (int64_t)a.A) {
+    const uint32_t g = graph_of(a.vtx_off, a.G, x);
+    gid[x] = g;
+    const int64_t v0 = a.vtx_off[g], n_g = a.vtx_off[g + 1] - v0;
+    const int64_t a0 = a.adj_off[g], alen = a.adj_off[g + 1] - a0;
+    const int64_t lx = (int64_t)x - v0;
+    // offsets arrays must be prefix sums
+    if (v0 < 0 || lx < 0 || lx >= n_g || v0 + n_g > (int64_t)a.N || a0 < 0 || alen < 0 ||
+        a0 + alen > (int64_t)a.A) {
+        graph_error(a, g, TC_E_ARG, gstat);
+    } else {
+        const int32_t *rp = a.row_ptr + v0 + g;
+        const int64_t r0 = rp[lx], r1 = rp[lx + 1];
+        if (r0 < 0 || r1 < r0 || r1 > alen)
             graph_error(a, g, TC_E_ARG, gstat);
-        } else {
-            const int32_t *rp = a.row_ptr + v0 + g;
-            const int64_t r0 = rp[lx], r1 = rp[lx + 1];
-            if (r0 < 0 || r1 < r0 || r1 > alen)
-                graph_error(a, g, TC_E_ARG, gstat);
-            else
-                d = (uint32_t)(r1 - r0);
-        }
+        else
+            d = (uint32_t)(r1 - r0);
     }
     deg[x] = d;
+}
+
+// Whether graph g's adjacency range meets that of an earlier graph with vertices (the calling wave,
+// g uniform; only asked for graphs after a descent).  Ranges outside the batch hold no rows.
+__device__ __forceinline__ bool meets_earlier(const BatchArgs &a, uint32_t g) {
+    const int64_t b = a.adj_off[g], e = a.adj_off[g + 1];
+    for (uint32_t h0 = 0; h0 < g; h0 += kWave) {
+        const uint32_t h = h0 + lane_id();
+        bool meets = false;
+        if (h < g) {
+            const int64_t hb = a.adj_off[h], he = a.adj_off[h + 1];
+            meets = hb >= 0 && hb < he && he <= (int64_t)a.A && hb < e && b < he &&
+                    a.vtx_off[h] < a.vtx_off[h + 1];
+        }
+        if (__ballot(meets)) return true;
+    }
+    return false;
 }
 
 // lanes a .. b - 1 of a wave (a <= b <= 64, a < 64)
@@ -131,7 +152,10 @@ __device__ __forceinline__ uint64_t lanes_from_to(uint32_t a, uint32_t b) {
 typedef const __attribute__((address_space(1))) int32_t *gptr_i32;
 
 // One pass over the rows: checks (ids in range, no self-loop, strictly ascending), the forward
-// rows written in place, and the graph's symmetry sum and forward entries.
+// rows written at the rows' places in the input, and the graph's symmetry sum and forward entries.
+// (The rows of a graph that is TC_E_ARG, by k_b_rows or because its range meets an earlier graph's,
+// are left out; the others are disjoint stretches of the input, so that no two rows write the same
+// words and fcol and the heavy items hold them all.)
 //
 // A wave takes 2^vshift consecutive vertices, graph by graph (nearly always one), and walks
 // their entries, consecutive in the input, 64 at a time: kWalkSteps steps together, whose loads
@@ -151,11 +175,11 @@ typedef const __attribute__((address_space(1))) int32_t *gptr_i32;
 // 1.24 ms, where a checking pass and a second pass that wrote the rows took 1.28 + 0.65 ms.
 constexpr int kWalkSteps = 4;
 
-__global__ __launch_bounds__(256) void k_b_setup(const BatchArgs *__restrict__ args, uint32_t acap,
+__global__ __launch_bounds__(256) void k_b_setup(const BatchArgs *__restrict__ args,
                                                  uint32_t vshift,
                                                  const uint32_t *__restrict__ gid,
                                                  const uint32_t *__restrict__ deg,
-                                                 const uint32_t *__restrict__ start,
+                                                 const uint32_t *__restrict__ descent,
                                                  uint32_t light_max, uint32_t kitem,
                                                  uint2 *__restrict__ frow,
                                                  uint32_t *__restrict__ fcol,
@@ -177,9 +201,15 @@ __global__ __launch_bounds__(256) void k_b_setup(const BatchArgs *__restrict__ a
     uint32_t g = ~0u, d = 0, s = 0;
     if (in) {
         g = gid[x];
-        d = deg[x];
-        s = start[x];
-        if (d > acap || s > acap - d) {  // only when the graphs' ranges overlap
+        d = gstat[g] == TC_E_ARG ? 0u : deg[x];
+    }
+    // (no graph comes after a descent in offsets that are prefix sums)
+    const uint32_t first_descent = *descent;
+    for (uint64_t late = __ballot(d > 0 && g > first_descent); late;) {
+        const uint32_t gc = (uint32_t)__builtin_amdgcn_readlane((int)g, __ffsll((long long)late) - 1);
+        late &= ~__ballot(g == gc);
+        if (!meets_earlier(a, gc)) continue;
+        if (g == gc) {
             graph_error(a, g, TC_E_ARG, gstat);
             d = 0;
         }
@@ -202,9 +232,8 @@ __global__ __launch_bounds__(256) void k_b_setup(const BatchArgs *__restrict__ a
         const uint32_t dm = mine ? d : 0u;
         const uint32_t incl = wave_incl_scan(dm), off = incl - dm;
         const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-        // the row's place in the input, less its place in the walk
-        const uint32_t in_at =
-            mine ? (uint32_t)(a.adj_off[gc] + rp[(uint32_t)(lx0 + lane)]) - off : 0u;
+        if (mine) s = (uint32_t)(a.adj_off[gc] + rp[(uint32_t)(lx0 + lane)]);
+        const uint32_t in_at = s - off;  // the row's place in the input, less its place in the walk
         uint32_t carry = 0, carry_f = 0;
         int32_t y_last = -1;
         uint64_t hsum = 0;
@@ -345,8 +374,8 @@ __global__ __launch_bounds__(256) void k_b_finish(const BatchArgs *__restrict__ 
 // ------------------------------------------------------------------ workspace + plan
 
 struct BatchLayout {
-    size_t args, ctl, gstat, ghash, gfwd, gid, deg, start, frow, fcol, items, whash, wfwd, wtotal,
-        scan, total;
+    size_t args, ctl, gstat, ghash, gfwd, gid, deg, frow, fcol, items, whash, wfwd, wtotal,
+        total;
 };
 
 constexpr uint32_t kMinItemEdges = 16;
@@ -407,23 +436,20 @@ static BatchLayout batch_layout(uint32_t gcap, uint32_t ncap, uint64_t acap) {
         off = align_up(off + (bytes ? bytes : 1), 256);
         return at;
     };
-    const uint64_t n1 = (uint64_t)ncap + 1;
     L.args = take(sizeof(BatchArgs));
     L.ctl = take(64 * 4);
     L.gstat = take((size_t)gcap * 4);
     L.ghash = take((size_t)gcap * 8);
     L.gfwd = take((size_t)gcap * 4);
     L.gid = take((size_t)ncap * 4);
-    L.deg = take(n1 * 4);
-    L.start = take(n1 * 4);
+    L.deg = take((size_t)ncap * 4);
     L.frow = take((size_t)ncap * 8);
     L.fcol = take((size_t)acap * 4 + count_col_pad_bytes());
-    L.items = take(((size_t)acap / kMinItemEdges + n1) * 8);
+    L.items = take(((size_t)acap / kMinItemEdges + ncap + 1) * 8);
     const size_t parts = 2 * (((size_t)ncap >> batch_vshift(ncap)) + 1);
     L.whash = take(parts * 8);
     L.wfwd = take(parts * 4);
     L.wtotal = take(parts * 8);
-    L.scan = take(scan_scratch_words(n1) * 4);
     L.total = off;
     return L;
 }
@@ -440,29 +466,28 @@ static int batch_enqueue(tc_plan *p, bool pv, hipStream_t s) {
     unsigned long long *wtotal = (unsigned long long *)(ws + L.wtotal);
     uint32_t *gfwd = (uint32_t *)(ws + L.gfwd), *wfwd = (uint32_t *)(ws + L.wfwd);
     uint32_t *gid = (uint32_t *)(ws + L.gid), *deg = (uint32_t *)(ws + L.deg);
-    uint32_t *start = (uint32_t *)(ws + L.start), *fcol = (uint32_t *)(ws + L.fcol);
+    uint32_t *fcol = (uint32_t *)(ws + L.fcol);
     uint2 *frow = (uint2 *)(ws + L.frow), *items = (uint2 *)(ws + L.items);
-    const uint32_t ncap = p->ncap, n1 = ncap + 1, vshift = batch_vshift(ncap);
-    auto grid = [](uint64_t n) { return dim3((uint32_t)((n + 255) / 256)); };
-    hipLaunchKernelGGL(k_b_rows, grid(n1), dim3(256), 0, s, args, ncap, gid, deg, gstat);
+    const uint32_t ncap = p->ncap, vshift = batch_vshift(ncap);
+    const uint32_t rows = ncap > p->gcap ? ncap : p->gcap;
+    hipLaunchKernelGGL(k_b_rows, dim3(ceil_div(rows, 256)), dim3(256), 0, s, args, gid, deg,
+                       ctl + kCtlDescentB, gstat);
     if (hipGetLastError() != hipSuccess) return TC_E_HIP;
-    if (scan_exclusive_u32(deg, start, n1, (uint32_t *)(ws + L.scan), s) != hipSuccess)
-        return TC_E_HIP;
     const uint32_t waves = ceil_div(ncap > 0 ? ncap : 1, 1ull << vshift);
     hipLaunchKernelGGL(k_b_setup, dim3(ceil_div(waves, 4)), dim3(256), 0, s, args,
-                       (uint32_t)p->acap, vshift, gid, deg, start, p->light_max, p->kitem, frow,
-                       fcol, items, ctl + 1, ghash, gfwd, whash, wfwd, gstat);
+                       vshift, gid, deg, ctl + kCtlDescentB, p->light_max, p->kitem, frow, fcol,
+                       items, ctl + kCtlItemsB, ghash, gfwd, whash, wfwd, gstat);
     if (hipGetLastError() != hipSuccess) return TC_E_HIP;
     BatchKernelArgs ka;
     ka.frow = frow;
     ka.fcol = fcol;
     ka.gid = gid;
     ka.items = items;
-    ka.n_items = ctl + 1;
+    ka.n_items = ctl + kCtlItemsB;
     ka.n = &args->N;
     ka.vtx_off_pp = &args->vtx_off;
     ka.wtotal = wtotal;
-    ka.queue = ctl;
+    ka.queue = ctl + kCtlQueueB;
     ka.totals_pp = &args->totals;
     ka.tpv_pp = &args->per_vertex;
     ka.kitem = p->kitem;

@@ -394,3 +394,82 @@ def test_light_rows_at_window_edges(tuning, many):
     for pv in (True, False):
         check(plan.run_async(b, per_vertex=pv), gs, want, per_vertex=pv)
     plan.close()
+
+
+def ring(n):
+    return torch.tensor([(i, (i + 1) % n) for i in range(n)] + [(i, (i + 2) % n) for i in range(n)],
+                        dtype=torch.int32), n
+
+
+def splice(packed, g, row_ptr, col):
+    """The batch with graph g's row offsets (its n + 1) and entries replaced."""
+    vo, ao = packed["vtx_off"].tolist(), packed["adj_off"].tolist()
+    n, G = len(row_ptr) - 1, packed["G"]
+    grow_n, grow_a = n - (vo[g + 1] - vo[g]), len(col) - (ao[g + 1] - ao[g])
+    rp = packed["row_ptr"]
+    return {"G": G, "n_total": packed["n_total"] + grow_n, "adj_total": packed["adj_total"] + grow_a,
+            "vtx_off": torch.tensor([v + (grow_n if k > g else 0) for k, v in enumerate(vo)]),
+            "adj_off": torch.tensor([v + (grow_a if k > g else 0) for k, v in enumerate(ao)]),
+            "row_ptr": torch.cat([rp[:vo[g] + g], torch.as_tensor(row_ptr, dtype=torch.int32),
+                                  rp[vo[g + 1] + g + 1:]]),
+            "col": torch.cat([packed["col"][:ao[g]], torch.as_tensor(col, dtype=torch.int32),
+                              packed["col"][ao[g + 1]:]])}
+
+
+def check_isolated(packed, want, bad):
+    """Statuses E_ARG for the graphs `bad` and 0 for the others, whose counts are `want`'s: one-shot
+    and in a plan with room, totals and per-vertex."""
+    b = as_batch(packed)
+    plan = api.BatchPlan(b.G + 3, b.n_total + 5000, 2 * b.adj_total + 100000, device=DEV)
+    vo = packed["vtx_off"].tolist()
+    for pv in (True, False):
+        for res in (api.count_batched_async(b, per_vertex=pv), plan.run_async(b, per_vertex=pv)):
+            assert res.status.tolist() == [api.E_ARG if g in bad else 0 for g in range(b.G)]
+            for g, (t, per) in enumerate(want):
+                if g in bad:
+                    continue
+                assert int(res.totals[g]) == t, g
+                if pv:
+                    got = res.per_vertex[vo[g]:vo[g + 1]].cpu().numpy().astype(np.uint64)
+                    assert np.array_equal(got, per), g
+    plan.close()
+
+
+@pytest.mark.parametrize("before,after", [(5, 7), (40, 300), (3000, 2000)])
+@pytest.mark.parametrize("row_ptr", [[0, 5, 3, 8], [0, 8, 0, 8], [8, 0, 8, 0], [3, 2, 1, 8]])
+def test_descending_row_offsets_stay_in_their_graph(row_ptr, before, after):
+    """A descent in one graph's row offsets makes its rows' lengths add up to more than its
+    entries: the graph is reported, the valid ones before and after it keep status and counts."""
+    gs = [ring(before), (torch.tensor([(0, 1)], dtype=torch.int32), 3), ring(after)]
+    packed = splice(synth.pack_symmetric(gs), 1, row_ptr, [1, 2, 0, 2, 0, 1, 1, 2])
+    check_isolated(packed, oracle_per_graph(gs), {1})
+
+
+@pytest.mark.parametrize("kind", ["no forward entry", "all forward"])
+def test_row_lengths_beyond_32_bits_stay_in_their_graph(kind):
+    """Row offsets that swing between 0 and 65,536 over 131,071 vertices: the lengths of the rows
+    that ascend add up to 2^32 - 6, six entries (the first graph's) short of a wrap.  Entries that
+    name only the rows that descend, or the first vertices in order (long forward rows)."""
+    k = 1 << 16
+    tri = torch.tensor([(0, 1), (1, 2), (0, 2)], dtype=torch.int32)
+    gs = [(tri, 3), ring(9), (tri, 3), ring(50)]
+    row_ptr = np.tile(np.array([0, k], np.int32), k)
+    row_ptr[0] = 6
+    col = np.minimum(np.arange(k) * 2 + 1, 2 * k - 3) if kind == "no forward entry" else np.arange(k)
+    packed = splice(synth.pack_symmetric(gs), 1, row_ptr, col.astype(np.int32))
+    check_isolated(packed, oracle_per_graph(gs), {1})
+
+
+@pytest.mark.parametrize("where,bad", [("inside the graph before", {1, 2}), ("far out", {1, 2}),
+                                       ("at the start", {1, 2}), ("negative", {1, 2})])
+def test_descending_adjacency_offsets_stay_in_their_graphs(where, bad):
+    """One adjacency offset moved before the range of the graph that ends there: that graph
+    descends, and the next one's range meets the first graph's.  Or moved out of the batch.  The
+    graphs around them keep status and counts."""
+    gs = [ring(40), ring(30), ring(20), ring(300), ring(5)]
+    packed = dict(synth.pack_symmetric(gs))
+    ao = packed["adj_off"].clone()
+    ao[2] = {"inside the graph before": int(ao[1]) - 4, "far out": 1 << 40, "at the start": 0,
+             "negative": -8}[where]
+    packed["adj_off"] = ao
+    check_isolated(packed, oracle_per_graph(gs), bad)
