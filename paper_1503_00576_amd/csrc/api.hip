@@ -50,7 +50,7 @@ __global__ void k_items(const uint32_t *, const uint32_t *, const uint32_t *, co
                         uint32_t *, const int32_t *);
 __global__ void k_item_fill(const ItemLists, uint64_t, const int32_t *);
 __global__ void k_pv_out(const unsigned long long *, const uint32_t *, uint32_t,
-                         unsigned long long *);
+                         unsigned long long *, const int32_t *);
 __global__ void k_zero_u64(unsigned long long *, uint64_t);
 
 __global__ void k_copy_status(const int32_t *__restrict__ src, int32_t *__restrict__ dst) {
@@ -634,7 +634,7 @@ static int run_count_prepared(void *ws, const Layout &L, hipStream_t s, uint64_t
     }
     if (pv && n > 0) {
         hipLaunchKernelGGL(k_pv_out, dim3(grid_for(n, 256)), dim3(256), 0, s, tpv,
-                           at<uint32_t>(ws, L.perm), n, (unsigned long long *)d_pv);
+                           at<uint32_t>(ws, L.perm), n, (unsigned long long *)d_pv, status);
         TC_LAUNCH_CHECK();
     }
     return TC_OK;

@@ -1026,12 +1026,18 @@ __global__ void k_item_fill(const ItemLists q, uint64_t total, const int32_t *__
     for (uint32_t j = 0; j < k; ++j) q.list[blockIdx.y][o + j] = (uint32_t)c;
 }
 
-// per-vertex counts back from rank space to vertex ids
+// per-vertex counts back from rank space to vertex ids.  After an error they are zeros: perm holds
+// no order then (a small graph's is not written, a mismatched workspace has something else there).
 __global__ void k_pv_out(const unsigned long long *__restrict__ t_rank,
                          const uint32_t *__restrict__ perm, uint32_t n,
-                         unsigned long long *__restrict__ out) {
+                         unsigned long long *__restrict__ out,
+                         const int32_t *__restrict__ status) {
     uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < n) out[perm[r]] = t_rank[r];
+    if (r >= n) return;
+    if (*status)
+        out[r] = 0ull;
+    else
+        out[perm[r]] = t_rank[r];
 }
 
 __global__ void k_zero_u64(unsigned long long *__restrict__ p, uint64_t count) {

@@ -100,3 +100,46 @@ def test_small_path_in_a_captured_graph():
         g.replay()
         assert int(out.total.item()) == want and int(out.status.item()) == 0
         torch.randn(1 << 16, device=DEV).sum().item()
+
+
+def guarded(n):
+    """int64[n] between two guards of 4096 words of -7"""
+    room = torch.full((n + 8192,), -7, dtype=torch.int64, device=DEV)
+    return room, room[4096:4096 + n]
+
+
+@pytest.mark.parametrize("n", [200, 16384, 20000])
+@pytest.mark.parametrize("kind", ["range", "self_loop", "dup_edge", "asymmetric"])
+def test_per_vertex_counts_after_an_error(kind, n):
+    """The order of the vertices is missing after an error: the counts are zeros and nothing beside
+    them is written, whatever the workspace held before."""
+    base = synth.watts_strogatz(200, 5, 0.1, 3).numpy()
+    extra = {"range": [[0, n]], "self_loop": [[5, 5]], "dup_edge": base[:1, ::-1],
+             "asymmetric": base[:2]}[kind]
+    both = kind == "asymmetric"
+    e = torch.tensor(np.concatenate([base, np.array(extra, np.int32)]), device=DEV)
+    if both and e.shape[0] % 2:
+        e = e[1:].contiguous()
+    ws = api.alloc_workspace(n, e.shape[0], both, DEV).fill_(0xFF)
+    room, pv = guarded(n)
+    out = api.Result(torch.empty(1, dtype=torch.int64, device=DEV),
+                     torch.empty(1, dtype=torch.int32, device=DEV), pv)
+    api.count_async(e, n, both, per_vertex=True, workspace=ws, out=out)
+    assert api.STATUS_NAMES[int(out.status.item())] == kind
+    assert not pv.any()
+    assert (room[:4096] == -7).all() and (room[4096 + n:] == -7).all()
+
+
+def test_per_vertex_counts_on_a_mismatched_workspace():
+    """Prepared for 200 vertices, counted as a graph of 3000."""
+    e = synth.watts_strogatz(200, 5, 0.1, 3).to(DEV)
+    ws = api.alloc_workspace(3000, 9000, device=DEV).fill_(0xFF)
+    p = api.Prepared(e, 200, workspace=ws)
+    p.n, p.m = 3000, 9000
+    room, pv = guarded(3000)
+    out = api.Result(torch.empty(1, dtype=torch.int64, device=DEV),
+                     torch.empty(1, dtype=torch.int32, device=DEV), pv)
+    p.count_async(per_vertex=True, out=out)
+    assert int(out.status.item()) == api.E_MISMATCH
+    assert not pv.any()
+    assert (room[:4096] == -7).all() and (room[4096 + 3000:] == -7).all()
