@@ -630,6 +630,15 @@ __device__ __forceinline__ void sort_row_class(const StagedCol col,
 // loaded and stored in place touch 64 different 64-byte blocks per instruction, one cycle each (R-MAT
 // 20, 23 and a small world of 1,000,003 vertices: 99, 1003 and 72 us in place, 88, 922 and 63
 // staged; with 512 threads 102, 1216 and 56).
+//
+// The row sorts report repeated edges in the status word that they read at their start, so the waves
+// of a workgroup may read different values.  All go on or none: one that went on alone would meet
+// counters and staged rows that the others had not filled.  So every wave notes what it read before
+// the barrier that follows the staging.  (The word is read through the caches, which costs nothing: a
+// stale value is an earlier one.  Read at agent scope by every workgroup, it took 200 us at R-MAT 23.)
+__device__ __forceinline__ uint32_t status_seen(const int32_t *status) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane(*status);
+}
 constexpr uint32_t kRowStage = kRowChunk + kRowWave;
 __device__ __forceinline__ uint32_t row_class(uint32_t len) {  // len >= 1
     if (len > kRowWave) return kRowClasses;
@@ -643,22 +652,29 @@ __global__ __launch_bounds__(256) void k_row_sort(uint32_t *__restrict__ col,
                                                   uint32_t *__restrict__ long_rows,
                                                   uint32_t *__restrict__ n_long,
                                                   int32_t *__restrict__ status) {
-    if (*status) return;
     static_assert(kRowLane << (kRowClasses - 1) == kRowWave, "classes cover the wave rows");
+    __shared__ uint32_t s_seen[4];
     __shared__ uint32_t list[kRowChunk];
     __shared__ uint32_t stage[kRowStage + kRowStage / 16];
     __shared__ uint32_t ccount[kRowClasses], coff[kRowClasses], ccur[kRowClasses];
     const uint32_t c = blockIdx.x;
     const uint32_t r0 = rchunk[c], r1 = c + 1 < chunks ? rchunk[c + 1] : n;
     const uint32_t t = threadIdx.x;
+    const uint32_t seen = status_seen(status);
     if (r0 >= r1) return;  // (inside a long row)
+    if (lane_id() == 0) s_seen[t / kWave] = seen;
     // (a long row's part beyond the stage is not touched, and what is staged of it stays as it is)
     const StagedCol staged{stage, c * chunk};
-    const uint32_t p0 = row_ptr[r0], p1 = min(row_ptr[r1], c * chunk + chunk + kRowWave);
+    uint32_t p0 = 0, p1 = 0;
+    if (!seen) {  // (else there may be no rows)
+        p0 = row_ptr[r0];
+        p1 = min(row_ptr[r1], c * chunk + chunk + kRowWave);
+    }
     if (t < kRowClasses) ccount[t] = 0;
 #pragma unroll 4
     for (uint32_t p = p0 + t; p < p1; p += 256) staged(p) = col[p];
     __syncthreads();
+    if (s_seen[0] | s_seen[1] | s_seen[2] | s_seen[3]) return;
     for (uint32_t r = r0 + t; r < r1; r += blockDim.x) {
         const uint32_t len = row_ptr[r + 1] - row_ptr[r];
         if (len == 0) continue;
@@ -706,9 +722,12 @@ __global__ __launch_bounds__(1024) void k_row_sort_long(uint32_t *__restrict__ c
                                                         uint32_t hbase,
                                                         uint32_t *__restrict__ hrow,
                                                         int32_t *__restrict__ status) {
-    if (*status) return;
     __shared__ uint32_t a[kRowLong];
+    __shared__ uint32_t s_seen;
     const uint32_t t = threadIdx.x, nl = *n_long;
+    if (t == 0) s_seen = status_seen(status);
+    __syncthreads();
+    if (s_seen) return;
     const uint32_t waves = blockDim.x / kWave;
     for (uint32_t q = blockIdx.x * waves + t / kWave; q < nl; q += gridDim.x * waves) {
         const uint32_t r = long_rows[q];

@@ -143,3 +143,24 @@ def test_per_vertex_counts_on_a_mismatched_workspace():
     assert int(out.status.item()) == api.E_MISMATCH
     assert not pv.any()
     assert (room[:4096] == -7).all() and (room[4096 + 3000:] == -7).all()
+
+
+@pytest.mark.parametrize("n,m", [(16000, 250000), (40000, 900000), (1 << 18, 2000000)])
+@pytest.mark.parametrize("every", [1, 997])
+def test_repeated_edges_in_many_rows(n, m, every):
+    """Repeated edges all over the rows, found by many workgroups of the row sorts while others of
+    the same launch begin, rows beyond one wave's among them: reported each time, and the same
+    workspace then counts a valid graph."""
+    e = random_graph(n, m, m + n)
+    hub = n - 1 - (np.arange(2200, dtype=np.int32))
+    clique = np.stack(np.triu_indices(1100, 1), 1).astype(np.int32) if n > 16384 else e[:0]
+    good = np.unique(np.sort(np.concatenate([e, np.stack([hub[1:], hub[:-1]], 1), clique]), 1), axis=0)
+    want = oracle.count(good, n)
+    bad = np.concatenate([good, good[::every, ::-1]])
+    bad = torch.tensor(bad[np.random.default_rng(every).permutation(len(bad))], device=DEV)
+    good = torch.tensor(good, device=DEV)
+    ws = api.alloc_workspace(n, bad.shape[0], device=DEV)
+    for _ in range(10):
+        out = api.count_async(bad, n, workspace=ws)
+        assert int(out.status.item()) == api.E_DUP_EDGE
+    assert int(api.count_async(good, n, workspace=ws).check().total.item()) == want
