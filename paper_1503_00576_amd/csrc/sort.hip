@@ -514,6 +514,12 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const Src in, uint3
 // tile needs no table at all.  More tiles: from the scanned table (every workgroup would read
 // the whole table otherwise, 128 KB at 128 tiles).
 constexpr uint32_t kRawTiles = 128;
+// Up to kColumnTiles tiles, one thread adds up a digit's row (its loads are a row apart, so their
+// lines grow with the tiles); more, a wave adds up 32 digits' rows at a time, one scan each, 64 for
+// a wave with 512 digits whatever the tiles.  A sort on 63 bits, us, by waves and by threads: 20,000
+// keys (3 tiles) 165 and 109, 131,072 (16) 169 and 136, 262,144 (32) 172 and 164, 400,000 (49) 177
+// and 195.  (With the scan's launches, as for many tiles, it takes 137 for 20,000.)
+constexpr uint32_t kColumnTiles = 32;
 
 // Global minus local start of every digit into L.glob (all threads; loc filled).
 // (kFew: at most kRawTiles tiles; an instance of its own, since its registers would halve the
@@ -528,6 +534,27 @@ __device__ __forceinline__ void tile_digit_starts(SortTileLds<kBits> &L,
         if (t < kDigits) L.glob[t] = table[(uint64_t)t * tiles + tile] - L.loc[t];
     } else if (tiles == 1) {
         if (t < kDigits) L.glob[t] = 0;
+    } else if (tiles <= kColumnTiles) {
+        constexpr uint32_t kStep = 8;
+        const uint32_t w = t / kWave;
+        uint32_t sum = 0, below = 0;
+        for (uint32_t k0 = 0; t < kDigits && k0 < tiles; k0 += kStep) {
+            uint32_t x[kStep];
+#pragma unroll
+            for (uint32_t k = 0; k < kStep; ++k)
+                x[k] = k0 + k < tiles ? table[t * tiles + k0 + k] : 0u;
+#pragma unroll
+            for (uint32_t k = 0; k < kStep; ++k) {
+                sum += x[k];
+                below += k0 + k < tile ? x[k] : 0u;
+            }
+        }
+        const uint32_t incl = wave_incl_scan(sum);
+        if (lane_id() == kWave - 1) L.gwave[w] = incl;
+        __syncthreads();
+        uint32_t before = 0;
+        for (uint32_t k = 0; k < w; ++k) before += L.gwave[k];
+        if (t < kDigits) L.glob[t] = before + incl - sum + below - L.loc[t];
     } else {
         // a wave sums its digits' rows, 32 at a time, lanes along the tiles; lane i keeps its
         // digit i's sums

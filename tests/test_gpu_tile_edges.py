@@ -91,3 +91,17 @@ def test_rows_across_sort_chunks(k):
     assert np.array_equal(rp[1:] - rp[:-1], np.arange(k - 1, -1, -1))
     assert all(np.array_equal(col[rp[r]:rp[r + 1]], np.arange(r + 1, k)) for r in range(k))
     assert api.count(e.to(DEV), k) == k * (k - 1) * (k - 2) // 6
+
+
+@pytest.mark.parametrize("tiles,extra", [(1, 1), (8, 0), (8, 1), (9, 1), (32, 0), (32, 1), (RAW, 1)])
+@pytest.mark.parametrize("bits", [16, 34, 36, 41, 45, 49, 54, 57, 63])
+def test_sort_by_ways_to_find_the_digit_starts(tiles, extra, bits):
+    """Tile counts on both sides of the rules (one thread per digit up to 32 tiles, a wave per 32
+    digits up to RAW, a scanned table) at the widths with digits of 9 bits above 32."""
+    count = tiles * TILE + extra
+    gen = torch.Generator().manual_seed(count + bits)
+    keys = torch.randint(0, 1 << 62, (count,), generator=gen, dtype=torch.int64)
+    keys[: count // 3] &= ~0x1FF  # a crowded digit
+    keys[count // 2:] |= 0x3FFFF << 40  # and full ones
+    want = keys[torch.argsort(keys & ((1 << bits) - 1), stable=True)]
+    assert torch.equal(api.sort_u64(keys.to(DEV), bits).cpu(), want)
