@@ -622,3 +622,19 @@ def test_wide_lists_by_their_low_entries(high):
     sparse = np.stack(np.nonzero(np.triu(rng.random((300, 300)) < 0.4, 1)), 1).astype(np.int32)
     check_vs_oracle(clique, 200, options=options)
     check_vs_oracle(sparse, 300, options=options)
+
+
+@pytest.mark.parametrize("row_blocks", [1, 3])
+@pytest.mark.parametrize("n", [700, 768, 769, 770, 1600])
+def test_per_vertex_light_lists_of_hubs(n, row_blocks):
+    """Light lists that share a few hubs, which take nearly all third-vertex credits: a ring of n
+    vertices joined to three of them, on both sides of the 768 ranks whose credits are summed per
+    workgroup, and a sparse random graph over all of it (third vertices below those ranks)."""
+    rng = np.random.default_rng(n)
+    ring = np.arange(3, n)
+    edges = [(h, x) for h in range(3) for x in range(h + 1, n)]
+    edges += [(x, x + 1) for x in ring[:-1]]
+    extra = np.unique(np.sort(rng.integers(3, n, (4 * n, 2)), 1), axis=0)
+    extra = extra[extra[:, 1] - extra[:, 0] > 1]
+    check_vs_oracle(np.concatenate([np.array(edges), extra]).astype(np.int32), n,
+                    options={"panel_ranks": 0, "row_blocks": row_blocks}, prepared_pv=True)
