@@ -82,7 +82,7 @@ constexpr uint32_t kLightPiece = 8;
 // and 128 measured slower at R-MAT 20 (2041 and 2353 us a count against 1960)
 constexpr uint32_t kLightList = 64;
 constexpr uint32_t kLightListWindow = 512;  // staged entries per wave
-constexpr uint32_t kLightLists = 16;        // lists per wave
+constexpr uint32_t kLightShiftMax = 4, kLightShiftMin = 2;  // lists per wave, log2 (light_shift)
 constexpr int kLightThreads = 256;
 constexpr int kLightWaves = kLightThreads / kWave;
 
@@ -1752,12 +1752,12 @@ __global__ __launch_bounds__(kLightThreads, 8) void k_count_light(const BatchKer
 // ------------------------------------------------------------------ light middle vertices
 //
 // The lists of vertices v below the first panel with few in-edges and a short N+(v) (kLightList):
-// a wave takes kLightLists consecutive lists (16: at R-MAT 20 the densest waves of 64 lists ran on
-// for 100 us after the others, 1960 against 1913 us a count; 8 lists: the same), stages their
-// N+(v) in LDS (whole lists, a window at a time) and takes their in-edges u -> v one per lane,
-// whatever list they belong to: the suffix of N+(u) after v (short as well: u comes before v in
-// the order of degrees) is looked up in N+(v) by binary search, its first piece on the edge's own
-// lane, further pieces in full rounds.
+// a wave takes up to 16 consecutive lists (at R-MAT 20 the densest waves of 64 lists ran on for 100
+// us after the others, 1960 against 1913 us a count), stages their N+(v) in LDS (whole lists, a
+// window at a time) and takes their in-edges u -> v one per lane, whatever list they belong to:
+// the suffix of N+(u) after v (short as well: u comes before v in the order of degrees) is looked
+// up in N+(v) by binary search, its first piece on the edge's own lane, further pieces in full
+// rounds.
 //
 // Per-vertex counts: a hit credits an LDS counter of N+(v)'s entry (added to T(w) once per entry,
 // and their sum to T(v)) and T(u) once per piece.  The highest ranks' T(w) go through LDS counters of
@@ -1768,7 +1768,7 @@ __global__ __launch_bounds__(kLightThreads) void k_count_light_lists(
     const uint32_t *__restrict__ row_ptr, const uint32_t *__restrict__ col,
     const uint32_t *__restrict__ cptr, const uint32_t *__restrict__ cbeg,
     const uint4 *__restrict__ er, uint32_t lists, uint32_t n1,
-    const uint32_t *__restrict__ first_panel, uint32_t light,
+    const uint32_t *__restrict__ first_panel, uint32_t light, uint32_t lshift,
     unsigned long long *__restrict__ light_total, unsigned long long *__restrict__ tpv,
     const int32_t *__restrict__ status) {
     __shared__ uint32_t s_mark[kLightWaves][kWave];
@@ -1783,7 +1783,7 @@ __global__ __launch_bounds__(kLightThreads) void k_count_light_lists(
         __syncthreads();
     }
     const uint32_t tile = xcd_stretch_tile(blockIdx.x, gridDim.x);
-    const uint32_t c = lane < kLightLists ? (tile * kLightWaves + w) * kLightLists + lane : lists;
+    const uint32_t c = (lane >> lshift) == 0 ? ((tile * kLightWaves + w) << lshift) + lane : lists;
     uint32_t *mark = s_mark[w], *list = s_list[w], *cnt3 = s_cnt[w];
     uint32_t cb = 0, in_edges = 0, r0 = 0, d = 0, v = 0;
     if (c < lists) {
@@ -1944,19 +1944,32 @@ uint32_t count_light_chunk_max() { return kLightChunkMax; }
 uint32_t count_panel_ranks() { return kPanelRanks; }
 uint32_t count_light_list() { return kLightList; }
 
+// Lists per wave: 16, or 8 or 4 where that makes fewer than 16384 waves (16 per SIMD): a wave takes
+// its lists' in-edges 64 at a time, one chain of loads after the other.  A resident graph with 16
+// lists per wave and by this rule, us: random, 40,000 vertices and 1.3 million edges 152 and 115,
+// 200,000 and 12 million 872 and 811; R-MAT, 60,001 and 900,000 91 and 78, 200,003 and 3 million 202
+// and 192.  A wave's own cost speaks against it where lists hold one or two in-edges (a wheel of
+// 200,000: 22 and 28); a limit of 32768 waves moves the two kinds further apart.
+static uint32_t light_shift(uint32_t lists) {
+    uint32_t v = kLightShiftMax;
+    while (v > kLightShiftMin && (lists >> v) < 16384u) --v;
+    return v;
+}
+
 hipError_t launch_count(const CountArgs &x, bool per_vertex, hipStream_t s) {
     const dim3 grid(device_cu_count() * kWgsPerCu), block(kThreads);
     if (x.light) {  // before k_count, which adds their totals
         const uint32_t lists = x.lists;
-        const dim3 lg(ceil_div(lists, kLightWaves * kLightLists)), lb(kLightThreads);
+        const uint32_t lshift = light_shift(lists);
+        const dim3 lg(ceil_div(lists, kLightWaves << lshift)), lb(kLightThreads);
         if (per_vertex)
             hipLaunchKernelGGL(k_count_light_lists<true>, lg, lb, 0, s, x.row_ptr, x.col, x.cptr,
-                               x.cbeg, x.er, lists, x.n1, x.first_panel, x.light, x.light_total, x.tpv,
-                               x.status);
+                               x.cbeg, x.er, lists, x.n1, x.first_panel, x.light, lshift,
+                               x.light_total, x.tpv, x.status);
         else
             hipLaunchKernelGGL(k_count_light_lists<false>, lg, lb, 0, s, x.row_ptr, x.col, x.cptr,
-                               x.cbeg, x.er, lists, x.n1, x.first_panel, x.light, x.light_total, x.tpv,
-                               x.status);
+                               x.cbeg, x.er, lists, x.n1, x.first_panel, x.light, lshift,
+                               x.light_total, x.tpv, x.status);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -638,3 +638,15 @@ def test_per_vertex_light_lists_of_hubs(n, row_blocks):
     extra = extra[extra[:, 1] - extra[:, 0] > 1]
     check_vs_oracle(np.concatenate([np.array(edges), extra]).astype(np.int32), n,
                     options={"panel_ranks": 0, "row_blocks": row_blocks}, prepared_pv=True)
+
+
+@pytest.mark.parametrize("n", [65534, 131070, 131071, 262142, 262143])
+def test_light_lists_at_the_steps_of_lists_per_wave(n):
+    """n + 1 lists on both sides of 131072 and 262144, where a wave takes 4, 8 and 16 of them: cliques of 1 to 65 vertices and vertices of none."""
+    rng = np.random.default_rng(n)
+    edges, base = [], 0
+    while base < n - 5000:
+        size = int(rng.integers(1, 66))
+        edges.append(np.stack(np.triu_indices(size, 1), 1) + base)
+        base += size
+    check_vs_oracle(np.concatenate(edges).astype(np.int32), n, prepared_pv=True)
