@@ -103,12 +103,10 @@ __device__ __forceinline__ uint32_t lds_addr(const uint32_t *p) {
 struct BitmapProbe {
     const uint32_t *bm;
     uint32_t lo, span;
-    static constexpr bool kBranchFree = true;
     __device__ __forceinline__ uint32_t bit(uint32_t w) const {
         const uint32_t o = min(w - lo, span + 1u);
         return __builtin_amdgcn_ubfe(bm[__builtin_amdgcn_ubfe(o, 5u, 27u)], o, 1u);
     }
-    __device__ __forceinline__ bool operator()(uint32_t w, uint32_t &) const { return bit(w); }
     static constexpr bool kMasked = false;
     static constexpr bool kList = false;
     // totals streamer (run_batch_t): both parts of a segment, positions tested
@@ -122,25 +120,12 @@ struct BitmapProbe {
 struct PanelProbe {
     const uint32_t *m;
     uint32_t lo, span;
-    static constexpr bool kBranchFree = true;
     static constexpr bool kMasked = true;
     static constexpr bool kList = false;
     __device__ __forceinline__ uint32_t count(uint32_t w, uint32_t r) const {
         return __popc(m[min(w - lo, span + 1u)] & r);
     }
 };
-
-// lower_bound with a lane-independent trip count (d is uniform)
-__device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t *list, uint32_t d,
-                                                    uint32_t w) {
-    uint32_t base = 0, len = d;
-    while (len > 1) {
-        uint32_t half = len >> 1;
-        base = (list[base + half - 1] < w) ? base + half : base;
-        len -= half;
-    }
-    return base + ((len == 1 && list[base] < w) ? 1u : 0u);
-}
 
 // A sorted list in LDS (d >= 1, uniform): the searches of a piece's kPiece entries advance in
 // lockstep, three vector operations and one LDS read per step (byte addresses; the steps are the
@@ -149,7 +134,6 @@ __device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t *list, uint32
 struct LdsListProbe {
     uint32_t list;  // LDS byte address
     uint32_t d;
-    static constexpr bool kBranchFree = false;
     static constexpr bool kMasked = false;
     static constexpr bool kList = true;
     static constexpr bool kLow = true;
@@ -189,22 +173,16 @@ struct LdsListProbe {
 struct ListProbe {  // sorted list in global memory (d >= 1)
     const uint32_t *list;
     uint32_t d;
-    static constexpr bool kBranchFree = false;
     static constexpr bool kMasked = false;
     static constexpr bool kList = true;
     static constexpr bool kLow = true;
     static constexpr bool kMaskHigh = true;
     static constexpr bool kPanel = false;
-    __device__ __forceinline__ bool operator()(uint32_t w, uint32_t &pos) const {
-        pos = lower_bound_u32(list, d, w);
-        return pos < d && list[pos] == w;
-    }
 };
 
 // ------------------------------------------------------------------ per-batch streaming
 
-struct WaveScratch {  // tag: the segment's owner (per-vertex counts) or its panel mask;
-                     // the batched kernel's light segments keep their N+(u) in tag and aux
+struct WaveScratch {  // tag: the segment's owner (per-vertex counts) or its panel mask, ...
     uint32_t off[kWave], beg[kWave], first[kWave], end[kWave], cnt[kWave], tag[kWave],
         aux[kWave];
 };
@@ -222,28 +200,17 @@ struct SegRec {
 // In-edge records: the in-edge u -> v at CSR position e (list entry j holds cbeg[j] = e + 1)
 // has its record at er[e] = (end of u's row, panel mask of u's run in a panel list or else
 // where the suffix's entries >= hbase start in col, where they start in hcol, u); reading
-// it is one random 16-byte gather per segment.
+// it is one random 16-byte gather per segment.  A panel's segment (u, panel) is the suffix of N+(u)
+// after u's first panel vertex, tagged with the mask R(u) of u's panel vertices; with a high region
+// every entry after a panel vertex is a rank >= p0 >= hbase.
 struct InEdgeSegs {  // middle-vertex kernel: suffix of N+(u) after v, owner u
     const uint32_t *cbeg;
     const uint4 *er;
-    __device__ __forceinline__ SegRec rec_from(uint32_t b) const {
+    __device__ __forceinline__ SegRec rec(uint32_t e) const {
+        const uint32_t b = cbeg[e];
         const uint4 x = er[b - 1];
         return SegRec{b, x.x, x.y, x.z, x.w};
     }
-    __device__ __forceinline__ SegRec rec(uint32_t e) const { return rec_from(cbeg[e]); }
-};
-
-// Panel segment (u, panel): the suffix of N+(u) after u's first panel vertex, tagged with the
-// mask R(u) of u's panel vertices; with a high region every entry after a panel vertex is a
-// rank >= p0 >= hbase.
-struct PanelSegs {
-    const uint32_t *cbeg;
-    const uint4 *er;
-    __device__ __forceinline__ SegRec rec_from(uint32_t b) const {
-        const uint4 x = er[b - 1];
-        return SegRec{b, x.x, x.y, x.z, x.w};
-    }
-    __device__ __forceinline__ SegRec rec(uint32_t e) const { return rec_from(cbeg[e]); }
 };
 
 struct OutEdgeSegs {  // u-centric kernel: the whole list N+(v) of out-neighbour v, owner v
@@ -258,7 +225,7 @@ struct OutEdgeSegs {  // u-centric kernel: the whole list N+(v) of out-neighbour
 
 // The calling wave streams segments [eb, min(eb + 64, e1)) of the current item through the
 // probe and returns this lane's hits.  PV: per-vertex accumulation -- LDS counters `tcnt`
-// indexed by the probe's position when `tcnt` is non-null, global atomics on `tpv` otherwise;
+// indexed by the probe's position for a list in LDS, global atomics on `tpv` for one in memory;
 // every segment's hits go to its owner.
 template <bool PV, class Probe, class Segs>
 __device__ __forceinline__ uint32_t run_batch(uint32_t eb, uint32_t e1, const Segs &segs,
@@ -311,8 +278,6 @@ __device__ __forceinline__ uint32_t run_batch(uint32_t eb, uint32_t e1, const Se
                 wv[4 * j + 3] = x.w;
             }
             uint32_t hits = 0;
-            // element i of the piece belongs to the suffix iff start + i - first < stop - first
-            const uint32_t rel0 = start - first, len = stop - first;
             if constexpr (!PV && Probe::kMasked) {
                 // hits of element i: panel vertices of the owner whose lists hold it
                 const uint32_t r = ws.tag[k];
@@ -372,7 +337,8 @@ __device__ __forceinline__ uint32_t run_batch(uint32_t eb, uint32_t e1, const Se
                         if ((packed >> i) & 1u) atomicAdd(&tpv[wv[i]], 1ull);
                     }
                 }
-            } else if constexpr (!PV && Probe::kBranchFree) {
+            } else {  // a bitmap
+                static_assert(!PV, "per-vertex counts need positions");
                 // the piece's valid elements are the contiguous range [lo_i, hi_i) of positions
                 uint32_t packed = 0;
 #pragma unroll
@@ -382,21 +348,6 @@ __device__ __forceinline__ uint32_t run_batch(uint32_t eb, uint32_t e1, const Se
                 const uint32_t hmask = hi_i >= 32u ? ~0u : ((1u << hi_i) - 1u);
                 const uint32_t mask = hmask & ~((1u << lo_i) - 1u);
                 hits = __popc(packed & mask);
-            } else {
-#pragma unroll
-                for (uint32_t i = 0; i < kPiece; ++i) {
-                    if (rel0 + i < len) {
-                        const uint32_t w = wv[i];
-                        uint32_t pos;
-                        if (probe(w, pos)) {
-                            ++hits;
-                            if (PV) {
-                                if (tcnt) atomicAdd(&tcnt[pos], 1u);
-                                else atomicAdd(&tpv[w], 1ull);
-                            }
-                        }
-                    }
-                }
             }
             hits_total += hits;
             if (PV && hits) atomicAdd(&ws.cnt[k], hits);
@@ -817,7 +768,7 @@ constexpr uint32_t kMidPieces = (1u << (MidCounters::kHi + 4)) / kPiece - 1;
 // lane's hits; `pieces` is the wave's bound on the pieces any lane added to mc since its last
 // flush.
 __device__ __forceinline__ uint32_t run_panel_pv(uint32_t eb, uint32_t e1,
-                                                 const PanelSegs &segs,
+                                                 const InEdgeSegs &segs,
                                                  const uint32_t *__restrict__ col,
                                                  const uint32_t *m, uint32_t *cnt3, uint32_t lo,
                                                  uint32_t span, WaveScratch &ws,
@@ -1117,7 +1068,7 @@ __global__ __launch_bounds__(kThreads) void k_count_panel_pv(
     if (*status) return;
     const uint32_t t = threadIdx.x, w = t / kWave, lane = lane_id();
     WaveScratch &ws = s_ws[w];
-    const PanelSegs psegs{cbeg, er};
+    const InEdgeSegs segs{cbeg, er};
     uint32_t *m = s_mem, *cnt3 = s_mem + kPvPanelWords;
     for (uint32_t i = t; i < kLdsWords; i += kThreads) s_mem[i] = 0;
     if (t < kPanel) s_mid[t] = 0;
@@ -1147,14 +1098,14 @@ __global__ __launch_bounds__(kThreads) void k_count_panel_pv(
             __syncthreads();
             if (P >= hbase) {  // the suffixes are in hcol
                 for (uint32_t eb = it.e0 + w * kWave; eb < it.e1; eb += kWaves * kWave) {
-                    const SegRec r = eb + lane < it.e1 ? psegs.rec(eb + lane)
+                    const SegRec r = eb + lane < it.e1 ? segs.rec(eb + lane)
                                                        : SegRec{0u, 0u, 0u, 0u, 0u};
                     cnt += run_panel_pv_high(r, hcol, m, cnt3, lo - hbase, wn, lo > P,
                                              lo + wn < n1 - 1, ws, mc, pieces, s_mid, tpv);
                 }
             } else {
                 for (uint32_t eb = it.e0 + w * kWave; eb < it.e1; eb += kWaves * kWave)
-                    cnt += run_panel_pv(eb, it.e1, psegs, col, m, cnt3, lo, wn - 1, ws, mc,
+                    cnt += run_panel_pv(eb, it.e1, segs, col, m, cnt3, lo, wn - 1, ws, mc,
                                         pieces, s_mid, tpv);
             }
             __syncthreads();
@@ -1246,15 +1197,14 @@ __global__ __launch_bounds__(kThreads) void k_count(
                     for (uint32_t i = row_ptr[P + j] + lane; i < row_ptr[P + j + 1]; i += kWave)
                         atomicOr(&s_mem[col[i] - P], 1u << j);
                 __syncthreads();
-                const PanelSegs psegs{cbeg, er};
                 uint32_t cnt = 0;
                 if (P >= hbase) {  // the suffixes are in hcol
                     const PanelHighProbe probe{s_mem, P - hbase};
-                    cnt += stream_t(first, it.e1, step, psegs, col, hcol, hbase, probe, ws);
+                    cnt += stream_t(first, it.e1, step, segs, col, hcol, hbase, probe, ws);
                 } else {  // no high region: 32-bit entries
                     const PanelProbe probe{s_mem, P, n1 - 2 - P};
                     for (uint32_t eb = first; eb < it.e1; eb += step)
-                        cnt += run_batch<false>(eb, it.e1, psegs, col, probe, ws, nullptr, tpv);
+                        cnt += run_batch<false>(eb, it.e1, segs, col, probe, ws, nullptr, tpv);
                 }
                 acc += cnt;
                 __syncthreads();
@@ -1280,11 +1230,8 @@ __global__ __launch_bounds__(kThreads) void k_count(
         __syncthreads();
         uint32_t cnt = 0;
         if (mode == 0) {
-            const BitmapProbe probe{s_mem, lo, span};
-            if constexpr (PV) {
-                for (uint32_t eb = first; eb < it.e1; eb += step)
-                    cnt += run_batch<true>(eb, it.e1, segs, col, probe, ws, nullptr, tpv);
-            } else {
+            if constexpr (!PV) {
+                const BitmapProbe probe{s_mem, lo, span};
                 cnt += stream_t(first, it.e1, step, segs, col, hcol, hbase, probe, ws);
             }
         } else if (mode == 1) {
@@ -1517,9 +1464,11 @@ __global__ __launch_bounds__(kThreads) void k_count_u(const BatchKernelArgs a) {
                 atomicOr(&mem[o >> 5], 1u << (o & 31u));
             }
             wave_lds_sync();
-            const BitmapProbe probe{mem, lo, span};
-            for (uint32_t eb = e0; eb < e1; eb += kWave)
-                cnt += run_batch<PV>(eb, e1, segs, fcol, probe, ws, nullptr, tpv);
+            if constexpr (!PV) {
+                const BitmapProbe probe{mem, lo, span};
+                for (uint32_t eb = e0; eb < e1; eb += kWave)
+                    cnt += run_batch<false>(eb, e1, segs, fcol, probe, ws, nullptr, tpv);
+            }
             for (uint32_t i = lane; i < d; i += kWave) mem[(fcol[r0 + i] - lo) >> 5] = 0;
         } else if (mode == 1) {
             uint32_t *list = mem, *tc = PV ? mem + kWaveListPV : nullptr;
