@@ -650,3 +650,40 @@ def test_light_lists_at_the_steps_of_lists_per_wave(n):
         edges.append(np.stack(np.triu_indices(size, 1), 1) + base)
         base += size
     check_vs_oracle(np.concatenate(edges).astype(np.int32), n, prepared_pv=True)
+
+
+@pytest.mark.parametrize("options", [{"panel_ranks": p, **h} for p in (31, 33, 65, 96, 129, 200)
+                                     for h in ({}, {"high_ranks": 0})])
+@pytest.mark.parametrize("sizes", [(60, 66, 70), (64, 65, 65, 65, 66), (66, 80, 90), (65, 65, 65)])
+def test_first_panel_by_degree_in_part_of_the_ranks(sizes, options):
+    """As test_first_panel_by_degree where the panel region leaves vertices below it (only then is
+    the first panel searched for), with 16-bit and with 32-bit panel entries."""
+    for hubs in (0, 2):
+        edges, base = [], hubs
+        for size in sizes:
+            edges += [(base + i, base + j) for i in range(size) for j in range(i + 1, size)]
+            base += size
+        edges += [(h, x) for h in range(hubs) for x in range(h + 1, base)]
+        edges += [(base + i, base + (i + d) % 150) for i in range(150) for d in (1, 2, 3)]
+        check_vs_oracle(np.array(edges, dtype=np.int32), base + 150, options=options,
+                        prepared_pv=True)
+
+
+@pytest.mark.parametrize("options", [None, {"high_ranks": 0}])
+@pytest.mark.parametrize("q", [0, 1, 31, 32, 33, 66, 511, 512, 513, 514, 5000, 32703, 32704, 32705,
+                               32735, 32736, 33000])
+def test_first_panel_by_degree_in_the_whole_region(q, options):
+    """33,500 vertices, the q of highest degree above 64 edges: the boundary everywhere in the
+    default panel region of 32,736 ranks, at every step of its search."""
+    n = 33500
+    low = np.arange(q, n)
+    edges = [np.stack([low[:-d], low[d:]], 1) for d in (1, 2)]
+    high = np.arange(q)
+    if q >= 200:  # a ring of degree 66
+        edges += [np.stack([high, (high + d) % q], 1) for d in range(1, 34)]
+    elif q:  # hubs with 65 neighbours of their own among the others, joined in a row
+        edges += [np.stack([np.repeat(high, 65), q + np.arange(65 * q)], 1),
+                  np.stack([high[:-1], high[1:]], 1)]
+    e = np.concatenate(edges).astype(np.int32)
+    assert (np.bincount(e.ravel(), minlength=n) > 64).sum() == q
+    check_vs_oracle(e, n, options=options, prepared_pv=True)
