@@ -690,10 +690,11 @@ def main():
     g = (golden("workloads.json") or {}).get(GOLDEN_KEYS[args.workload])
     golden_ok = None if g is None else (g["total"] == total)
 
-    # Roofline of the counting kernel.  achieved / frac: the DRAM-side bytes of one launch
-    # (rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, copy-calibrated, committed under
-    # profiles/) over the launch time measured here with HIP events; null when the committed
-    # counters were taken on other sources.  algorithmic: 4 B per element the kernel streams
+    # Roofline of the counting kernel.  achieved / frac: the bytes of one launch that leave the
+    # L2 (rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, copy-calibrated, committed under
+    # profiles/; the memory-side cache serves part of them, so this is no HBM bandwidth) over the
+    # launch time measured here with HIP events; null when the committed counters were taken on
+    # other sources.  algorithmic: 4 B per element the kernel streams
     # + 12 B per segment (its range and panel mask) + the node array and out-lists once.
     ctr = load_counters("k_count", args.workload)
     if ctr and json.loads(ctr.get("options", "{}")) != {k: full_opts[k] for k in
@@ -705,7 +706,8 @@ def main():
     alg_gbs = alg_bytes / t_s / 1e9
     traffic = ctr["hbm_bytes_per_launch"] if ctr else None
     if traffic:
-        achieved, basis = traffic / t_s / 1e9, "counter bytes (FETCH_SIZE, WRITE_SIZE) / kernel time"
+        achieved, basis = traffic / t_s / 1e9, ("counter bytes (FETCH_SIZE, WRITE_SIZE: what leaves "
+                                                "the L2) / kernel time")
     else:
         achieved, basis = alg_gbs, ("algorithmic bytes / kernel time (no counters for these "
                                     "sources and options)")

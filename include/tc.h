@@ -327,7 +327,9 @@ int tc_split_subgraph_edges(const void *h_ws, uint32_t index, int32_t *h_out,
  *   d_col    : int32[adj_total], local vertex ids 0 .. n_g - 1
  * Output: d_totals uint64[G] (triangles per graph), d_per_vertex uint64[n_total] (per vertex of
  * the union, nullable), d_status int32[G] (per-graph data error, nullable: range, self-loop,
- * duplicate or unsorted row, missing mirror entry, inconsistent offsets).
+ * duplicate or unsorted row, missing mirror entry, inconsistent offsets, which includes an
+ * adjacency range that meets an earlier graph's).  An error in a graph's rows, row offsets or
+ * adjacency range leaves the status and the counts of the other graphs as they are without it.
  * Method: degree = row length; a stable per-row filter keeps the neighbours later in the
  * order of Section 2.2, so the oriented rows stay sorted without any sort; the counting kernel
  * computes Section 2.2's intersections grouped by u: for a vertex u with more than 256 forward

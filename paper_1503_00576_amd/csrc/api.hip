@@ -311,9 +311,13 @@ static bool make_layout(int64_t n, int64_t m, uint32_t flags, const tc_options *
 }
 
 // Lists of at most this many in-edges and entries are light (count.hip).  None when the panel region
-// holds the whole graph: one launch then counts everything (17 us for 8,009 vertices and 100,003
-// edges, where the light lists' own launch took 34 more).  None with a form limit of the wave
-// items lowered: they are wave items as well then, so that small graphs reach those forms.
+// holds the whole graph, up to 32,736 vertices: one launch then counts everything.  That is the
+// better side for R-MAT graphs only (whole counts without and with light lists, us: 8,009 vertices
+// 132 and 166, 20,001 217 and 230, 30,001 273 and 281; per vertex 260 and 271, 323 and 336).  Graphs
+// of even degree lose by it, per vertex most of all (30,001 vertices of a small world 277 and 240,
+// per vertex 390 and 277; 30,000 random vertices 258 and 244, 372 and 274; by preferential attachment
+// 280 and 262, 381 and 314).  None with a form limit of the wave items lowered: they are wave
+// items as well then, so that small graphs reach those forms.
 static uint32_t light_lists(const Layout &L) {
     return L.p0 > 0 && L.opt.wave_bitmap_span == count_wave_span() &&
                    L.opt.wave_list_max == count_wave_list(false)

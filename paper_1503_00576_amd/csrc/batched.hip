@@ -278,7 +278,11 @@ __global__ __launch_bounds__(256) void k_b_setup(const BatchArgs *__restrict__ a
                 // that are not ok is reported whatever its sum)
                 const uint64_t h = pair_hash(min(lk, yu), max(lk, yu));
                 hsum += fwd ? h : 0ull - h;
-                // forward entries of the row before this one
+                // forward entries of the row before this one.  (`& 63u` changes nothing where the row
+                // starts in this step.  It has to be there, and not as min(.., 63u): with that the
+                // compiler, clang 20 of ROCm 7.2, took `begun` for true in all steps, and rows that
+                // run over steps lost what carry_f holds.  test_light_rows_at_window_edges and
+                // test_batched_one_shot have such rows.)
                 const uint64_t F = __ballot(fwd);
                 const bool begun = ok_ >= sb;  // the row starts in this step
                 const uint32_t rank = (uint32_t)__popcll(
@@ -381,7 +385,7 @@ struct BatchLayout {
 constexpr uint32_t kMinItemEdges = 16;
 
 // Vertices per wave of the setup and the light counting: 64, or fewer when that leaves the chip
-// idle (down to 8, below 8192 waves: two per SIMD).  Counting four R-MAT graphs of 15,360 vertices
+// idle (down to 8, below 8192 waves: eight for each of the 1024 SIMDs, what they hold at most).  Counting four R-MAT graphs of 15,360 vertices
 // together took 950 us when 38 waves shared them and takes 59 us with 1920.
 static uint32_t batch_vshift(uint32_t ncap) {
     uint32_t v = 6;

@@ -790,7 +790,8 @@ uint32_t row_sort_wave() { return kRowWave; }
 // ranks are sorted by degree): vertices of at most `light` edges have light lists (count.hip) also
 // in the panel region, where a panel costs about 10 us whatever it holds.  A graph of 100,003
 // vertices by preferential attachment has 4,000 of larger degree: its per-vertex counts took 241
-// us with all 1023 panels and takes 126.  (64 ranks are looked at per step, three steps for 32,736.)
+// us with all 1023 panels and takes 126.  (64 ranks are looked at per step, three steps for 32,736.
+// Only where the panel region leaves ranks below it: `light` is 0 otherwise, light_lists in api.hip.)
 __global__ __launch_bounds__(256) void k_panel_range(const uint32_t *__restrict__ row_ptr,
                                                      const uint32_t *__restrict__ col, uint32_t n,
                                                      uint32_t p0, uint32_t panels,

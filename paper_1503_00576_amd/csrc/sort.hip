@@ -2,11 +2,12 @@
 //
 // The sort replaces the library sort of packed 64-bit edge keys in the preprocessing phase
 // (Section 3.2, step 3, and the note on sorting edges as 64-bit integers): keys are ordered
-// on a bit range [lo_bit, hi_bit) with 8-bit digits, least significant digit first; every
-// pass is an upsweep (per-tile digit histograms), an exclusive scan of the digit-major
-// histogram table, and a stable scatter in which every wave ranks its own contiguous part of
-// the tile with ballots, the tile is ordered by digit in LDS, and every digit's run is
-// written out contiguously.
+// on a bit range [lo_bit, hi_bit) with digits of 8 or 9 bits (digit_bits), least significant
+// digit first; a pass is an upsweep (per-tile digit histograms), an exclusive scan of the
+// digit-major histogram table, and a stable scatter in which every wave ranks its own contiguous
+// part of the tile with ballots, the tile is ordered by digit in LDS, and every digit's run is
+// written out contiguously.  Up to kRawTiles tiles the scatter adds up the unscanned table itself,
+// and a single tile needs no upsweep either.
 //
 // Single-sweep variant (large sorts that report errors through a status word): one upfront
 // kernel counts the digits of every pass over all keys; each pass is then one kernel whose
@@ -784,7 +785,7 @@ size_t sort_scratch_bytes(uint64_t count) {
 }
 
 // Bits per digit of the passes over a key of `bits` bits: 9 where that takes fewer passes than 8
-// (9, 17, 18, 25 to 27, 33 to 36 bits), and 8 elsewhere: a pass with 512 digits has a ninth
+// (9, 17, 18, 25 to 27, 33 to 36, 41 to 45, 49 to 54, 57 to 63 bits), and 8 elsewhere: a pass with 512 digits has a ninth
 // ballot per key, twice the table and half the run length.  Preprocessing with digits of 8 and
 // of 9 bits, us: 200,003 vertices and 3,000,001 edges 458 and 400, 262,144 and 20 million 1474
 // and 1386, 2^25 and 100 million 11,840 and 11,080, 2^26 and 120 million 16,250 and 15,320.
